@@ -22,7 +22,6 @@
 
 #include <algorithm>
 #include <cstdlib>
-#include <cstring>
 #include <string>
 
 namespace csh {
@@ -48,7 +47,7 @@ __device__ __forceinline__ double step_dt(const Args& p, double* t_now)
     const Slot& sl = p.slots[p.s_in];
     *t_now = sl.t;
     if (!p.dev_dt) return p.dt_in ? *p.dt_in : p.dt;
-    return p.cfl / __longlong_as_double((long long)sl.s_bits);
+    return p.cfl / slot_rate(sl);
 }
 
 __device__ __forceinline__ V10 load(const double* __restrict__ U, size_t plane, size_t c)
@@ -152,17 +151,18 @@ __global__ __launch_bounds__(256) void sweep3_kernel(SArgs q)
     const Args& p = q.a;
     double t_now;
     const double dt = step_dt(p, &t_now);
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        p.slots[p.s_out].t = t_now + dt;
-        p.slots[p.s_reset].s_bits = 0ull;
-        if (p.dt_log) *p.dt_log = dt;
+    if (blockIdx.x == 0) {
+        slot_clear(p.slots[p.s_reset], threadIdx.x);
+        if (threadIdx.x == 0) {
+            p.slots[p.s_out].t = t_now + dt;
+            if (p.dt_log) *p.dt_log = dt;
+        }
     }
     const int lane = threadIdx.x & 63, w = wave_in_block();
     const int half = lane >> 5, col = lane & (kHalf - 1);
     const int ys = 2 * w + half;  // row slot among j0 - 1 .. j0 + 6
     const bool loader = w == 0;   // wave-uniform
     const int nx = p.n[0], ny = p.n[1], nz = p.n[2];
-    const size_t plane = (size_t)nx * ny, ncell = plane * nz;
     // with half slopes the tracing coefficients are dt/h (twice dt/2h)
     const double kx2 = dt / p.h[0], ky2 = dt / p.h[1], kz2 = dt / p.h[2];
     const double cx = kx2, cy = ky2, cz = kz2;
@@ -334,7 +334,7 @@ __global__ __launch_bounds__(256) void sweep3_kernel(SArgs q)
     }
 
     smax = wave_max(smax);
-    if (lane == 0) atomic_max_pos(&p.slots[p.s_out].s_bits, smax);
+    if (lane == 0) slot_add(p.slots[p.s_out], blockIdx.x, smax);
     if (__any(bad) && lane == 0) atomicOr(p.flag, 1);
 }
 
@@ -366,7 +366,7 @@ __global__ __launch_bounds__(256) void maxspeed3_kernel(const double* __restrict
         bad |= !physical(w);
     }
     s = wave_max(s);
-    if ((threadIdx.x & 63) == 0) atomic_max_pos(&slot->s_bits, s);
+    if ((threadIdx.x & 63) == 0) slot_add(*slot, blockIdx.x, s);
     if (__any(bad) && (threadIdx.x & 63) == 0) atomicOr(flag, 1);
 }
 
@@ -488,14 +488,12 @@ hipError_t enqueue_maxspeed3(csh3_grid* h, const double* U, hipStream_t s)
 
 int read_rate(csh3_grid* h, int slot, double* s)
 {
-    unsigned long long bits = 0;
+    Slot sl;
     int flag = 0;
-    CSH3_HIP(hipMemcpyAsync(&bits, &h->slots[slot].s_bits, sizeof(bits), hipMemcpyDeviceToHost, h->stream));
+    CSH3_HIP(hipMemcpyAsync(&sl, h->slots + slot, sizeof(Slot), hipMemcpyDeviceToHost, h->stream));
     CSH3_HIP(hipMemcpyAsync(&flag, h->flag, sizeof(int), hipMemcpyDeviceToHost, h->stream));
     CSH3_HIP(hipStreamSynchronize(h->stream));
-    double v;
-    memcpy(&v, &bits, sizeof(v));
-    *s = v;
+    *s = csh::slot_rate_host(sl);
     if (flag) return fail3(CSH_ERR_NONPHYSICAL, "a state was not physical");
     return CSH_OK;
 }

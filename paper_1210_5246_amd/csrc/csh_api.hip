@@ -153,12 +153,7 @@ int read_rate(csh_grid* h, double* s)
     CSH_HIP(hipMemcpyAsync(&sl, h->slots + h->phase, sizeof(Slot), hipMemcpyDeviceToHost, h->stream));
     CSH_HIP(hipMemcpyAsync(&flag, h->flag, sizeof(int), hipMemcpyDeviceToHost, h->stream));
     CSH_HIP(hipStreamSynchronize(h->stream));
-    union {
-        unsigned long long u;
-        double d;
-    } c;
-    c.u = sl.s_bits;
-    *s = c.d;
+    *s = csh::slot_rate_host(sl);
     if (flag) return csh_fail(CSH_ERR_NONPHYSICAL, "non-physical state (rho <= 0, stress not positive-definite or non-finite)");
     return CSH_OK;
 }

@@ -26,6 +26,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include "csh_internal.h"
+
 // host-and-device arithmetic (also exercised on the CPU by the tests)
 #define CSH_HD __host__ __device__ __forceinline__
 
@@ -622,17 +624,49 @@ __device__ __forceinline__ int wave_in_block()
     return __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
 }
 
-// max over the wavefront
-__device__ __forceinline__ double wave_max(double x)
+// max(x, x moved by a DPP control); rows left out by the mask keep x
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_max(double x)
 {
-    for (int o = 32; o > 0; o >>= 1) x = fmax(x, __shfl_xor(x, o, 64));
-    return x;
+    const int l = __double2loint(x), h = __double2hiint(x);
+    const int lo = __builtin_amdgcn_update_dpp(l, l, CTRL, ROWS, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(h, h, CTRL, ROWS, 0xf, false);
+    return fmax(x, __hiloint2double(hi, lo));
 }
 
-// positive doubles order like their bit patterns
-__device__ __forceinline__ void atomic_max_pos(unsigned long long* slot, double x)
+// x of lane `lane` on every lane
+__device__ __forceinline__ double read_lane(double x, int lane)
 {
-    atomicMax(slot, (unsigned long long)__double_as_longlong(x));
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), lane),
+                            __builtin_amdgcn_readlane(__double2loint(x), lane));
+}
+
+// The rate of a slot on every lane of a wavefront (all lanes active): lane l
+// loads part l % 8, then the maximum over eight lanes.
+__device__ __forceinline__ double slot_rate(const Slot& sl)
+{
+    static_assert(kRateParts == 8, "three DPP steps");
+    double x = __longlong_as_double((long long)sl.part[threadIdx.x % kRateParts].bits);
+    x = dpp_max<0xB1, 0xf>(x);
+    x = dpp_max<0x4E, 0xf>(x);
+    x = dpp_max<0x141, 0xf>(x);
+    return read_lane(x, 0);
+}
+
+// max over the wavefront, the same value on every lane: quad permutations, the
+// two row mirrors, then lane 15 of rows 0 and 2 into the rows above and lane 31
+// into the upper half; lane 63 holds the maximum.  DPP moves on the VALU
+// instead of six rounds through the LDS permute unit, whose latency stood at
+// the end of every wavefront (~1250 -> ~450 cycles from the last row's end).
+__device__ __forceinline__ double wave_max(double x)
+{
+    x = dpp_max<0xB1, 0xf>(x);   // quad_perm [1, 0, 3, 2]
+    x = dpp_max<0x4E, 0xf>(x);   // quad_perm [2, 3, 0, 1]
+    x = dpp_max<0x141, 0xf>(x);  // row_half_mirror
+    x = dpp_max<0x140, 0xf>(x);  // row_mirror
+    x = dpp_max<0x142, 0xa>(x);  // row_bcast:15 into rows 1 and 3
+    x = dpp_max<0x143, 0xc>(x);  // row_bcast:31 into rows 2 and 3
+    return read_lane(x, 63);
 }
 
 // ---- one-dimensional sweep of a wavefront's 64 cells ------------------------------------------

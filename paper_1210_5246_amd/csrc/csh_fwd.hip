@@ -25,8 +25,7 @@ __device__ __forceinline__ double step_dt(const StepArgs<T>& p, double* t_now)
     const double t = sl.t;
     *t_now = t;
     if (!p.dev_dt) return p.dt_in ? *p.dt_in : p.dt;
-    const double s = __longlong_as_double((long long)sl.s_bits);
-    double dt = p.cfl / s;
+    double dt = p.cfl / slot_rate(sl);
     if (p.t_end > 0.0) {
         if (t >= p.t_end) dt = 0.0;
         else if (t + dt > p.t_end) dt = p.t_end - t;
@@ -45,10 +44,12 @@ __global__ __launch_bounds__(64 * kWaves) void sweep_kernel(StepArgs<T> p)
 {
     double t_now;
     const double dt = step_dt(p, &t_now);
-    if (!FLUXES && blockIdx.x == 0 && threadIdx.x == 0) {
-        p.slots[p.s_out].t = t_now + dt;
-        p.slots[p.s_reset].s_bits = 0ull;
-        if (p.dt_log) *p.dt_log = dt;
+    if (!FLUXES && blockIdx.x == 0) {
+        slot_clear(p.slots[p.s_reset], threadIdx.x);
+        if (threadIdx.x == 0) {
+            p.slots[p.s_out].t = t_now + dt;
+            if (p.dt_log) *p.dt_log = dt;
+        }
     }
 
     const int lane = threadIdx.x & 63;
@@ -161,7 +162,7 @@ __global__ __launch_bounds__(64 * kWaves) void sweep_kernel(StepArgs<T> p)
     }
 
     smax = wave_max(smax);
-    if (lane == 0) atomic_max_pos(&p.slots[p.s_out].s_bits, smax);
+    if (lane == 0) slot_add(p.slots[p.s_out], blockIdx.x, smax);
     if (__any(bad) && lane == 0) atomicOr(p.flag, 1);
 }
 
@@ -214,8 +215,7 @@ hipError_t launch_init(const T* W, T* U, int64_t n, int* flag, hipStream_t s)
 // ---- standalone CFL-rate reduction ----------------------------------------------------------------
 
 // Two cells per thread and iteration (their loads issued together), a
-// workgroup maximum in LDS and one 64-bit atomic per workgroup (a wavefront's
-// atomic on the one slot serialises with every other's).
+// workgroup maximum in LDS and one 64-bit atomic per workgroup.
 template <typename T>
 __global__ __launch_bounds__(256) void maxspeed_kernel(const T* __restrict__ U, int64_t n, int twod,
                                                        double idx, double idy, Slot* slot, int* flag)
@@ -238,7 +238,7 @@ __global__ __launch_bounds__(256) void maxspeed_kernel(const T* __restrict__ U, 
     if (lane == 0) red[wv] = s;
     if (__any(bad) && lane == 0) atomicOr(flag, 1);
     __syncthreads();
-    if (threadIdx.x == 0) atomic_max_pos(&slot->s_bits, fmax(fmax(red[0], red[1]), fmax(red[2], red[3])));
+    if (threadIdx.x == 0) slot_add(*slot, blockIdx.x, fmax(fmax(red[0], red[1]), fmax(red[2], red[3])));
 }
 
 template <typename T>
@@ -255,11 +255,8 @@ hipError_t launch_maxspeed(const T* U, int nx, int ny, double dx, double dy, Slo
 
 __global__ void reset_kernel(Slot* slots, int nslots, double t0)
 {
-    const int i = threadIdx.x;
-    if (i < nslots) {
-        slots[i].s_bits = 0ull;
-        slots[i].t = t0;
-    }
+    for (int i = 0; i < nslots; ++i) slot_clear(slots[i], threadIdx.x);
+    if ((int)threadIdx.x < nslots) slots[threadIdx.x].t = t0;
 }
 
 hipError_t launch_reset(Slot* slots, int nslots, double t0, hipStream_t s)

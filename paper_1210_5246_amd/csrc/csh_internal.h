@@ -9,12 +9,47 @@ namespace csh {
 // Device scalars of the timestep reduction.  Step n reads slot n % 3 (the
 // rate s of its input and the time t), accumulates the rate of its output
 // into slot (n + 1) % 3 and clears slot (n + 2) % 3 for the step after.
+// The rate is kept in kRateParts partial maxima, each on a 128-byte line of its
+// own, workgroup b adding to part b % kRateParts: workgroups are dealt
+// round-robin to the 8 XCDs, so the atomics on a part come from one XCD and
+// stay in its L2.  With one word for the whole launch every wavefront's atomic
+// moved that word between the L2s, ~10 ns each at the end of the launch
+// (512^2: 576 wavefronts, the last ended at 15.4 us of a 23.5 us step).
+constexpr int kRateParts = 8;
+
 struct Slot {
-    unsigned long long s_bits;  // max CFL rate as the bit pattern of a positive double
-    double t;                   // simulation time of the state this slot describes
-    double dt;                  // timestep a multi-stage step chose in its first stage
-    double pad;
+    double t;   // simulation time of the state this slot describes
+    double dt;  // timestep a multi-stage step chose in its first stage
+    double pad[14];
+    struct {
+        unsigned long long bits;  // max CFL rate as the bit pattern of a positive double
+        unsigned long long pad[15];
+    } part[kRateParts];
 };
+
+// The rate of a host copy of a slot: the maximum over its parts.
+inline double slot_rate_host(const Slot& sl)
+{
+    double s = 0.0;
+    for (int k = 0; k < kRateParts; ++k) {
+        const double v = __builtin_bit_cast(double, sl.part[k].bits);
+        s = v > s ? v : s;
+    }
+    return s;
+}
+
+// Clears a slot's rate: threads 0 .. kRateParts - 1 of one workgroup.
+__device__ __forceinline__ void slot_clear(Slot& sl, int thread)
+{
+    if (thread < kRateParts) sl.part[thread].bits = 0ull;
+}
+
+// Adds one workgroup's (or wavefront's) rate to a slot: one lane calls this.
+// Positive doubles order like their bit patterns.
+__device__ __forceinline__ void slot_add(Slot& sl, unsigned workgroup, double s)
+{
+    atomicMax(&sl.part[workgroup % kRateParts].bits, (unsigned long long)__double_as_longlong(s));
+}
 
 constexpr int kStrip = 60;  // output columns per wavefront (64 lanes, 2 halo lanes per side)
 constexpr int kWaves = 4;   // wavefronts per workgroup of the sweep kernels

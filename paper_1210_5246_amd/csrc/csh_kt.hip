@@ -24,7 +24,7 @@ __device__ __forceinline__ double kt_dt(const StepArgs<T>& p, double* t_now)
     *t_now = sl.t;
     if (p.dt_in) return *p.dt_in;
     if (!p.dev_dt) return p.dt;
-    double dt = p.cfl / __longlong_as_double((long long)sl.s_bits);
+    double dt = p.cfl / slot_rate(sl);
     if (p.t_end > 0.0) {
         if (sl.t >= p.t_end) dt = 0.0;
         else if (sl.t + dt > p.t_end) dt = p.t_end - sl.t;
@@ -46,12 +46,12 @@ __global__ __launch_bounds__(64 * kWaves) void kt_kernel(StepArgs<T> p)
 {
     double t_now;
     const double dt = kt_dt(p, &t_now);
+    if (FINAL && blockIdx.x == 0) slot_clear(p.slots[p.s_reset], threadIdx.x);
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         if (!FINAL) {
             p.slots[p.s_in].dt = dt;
         } else {
             p.slots[p.s_out].t = t_now + dt;
-            p.slots[p.s_reset].s_bits = 0ull;
             if (p.dt_log) *p.dt_log = dt;
         }
     }
@@ -84,7 +84,7 @@ __global__ __launch_bounds__(64 * kWaves) void kt_kernel(StepArgs<T> p)
     }
     if (FINAL) {
         smax = wave_max(smax);
-        if (lane == 0) atomic_max_pos(&p.slots[p.s_out].s_bits, smax);
+        if (lane == 0) slot_add(p.slots[p.s_out], blockIdx.x, smax);
         if (__any(bad) && lane == 0) atomicOr(p.flag, 1);
     }
 }
@@ -138,10 +138,12 @@ __global__ __launch_bounds__(64 * kWaves) void kt_fused_kernel(StepArgs<T> p)
 {
     double t_now;
     const double dt = kt_dt(p, &t_now);
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        p.slots[p.s_out].t = t_now + dt;
-        p.slots[p.s_reset].s_bits = 0ull;
-        if (p.dt_log) *p.dt_log = dt;
+    if (blockIdx.x == 0) {
+        slot_clear(p.slots[p.s_reset], threadIdx.x);
+        if (threadIdx.x == 0) {
+            p.slots[p.s_out].t = t_now + dt;
+            if (p.dt_log) *p.dt_log = dt;
+        }
     }
     const int lane = threadIdx.x & 63;
     const int wid = blockIdx.x * kWaves + wave_in_block();
@@ -279,7 +281,7 @@ __global__ __launch_bounds__(64 * kWaves) void kt_fused_kernel(StepArgs<T> p)
     }
 
     smax = wave_max(smax);
-    if (lane == 0) atomic_max_pos(&p.slots[p.s_out].s_bits, smax);
+    if (lane == 0) slot_add(p.slots[p.s_out], blockIdx.x, smax);
     if (__any(bad) && lane == 0) atomicOr(p.flag, 1);
 }
 
