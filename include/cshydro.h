@@ -22,8 +22,9 @@
  *     returns a message for the calling thread's last error.  No C++ exception
  *     crosses this interface.
  *   - A handle is not thread-safe; distinct handles are independent.
- *   - Launch shape: each 2-D sweep kernel marches a wavefront over a segment
- *     of rows whose length the library chooses from the grid size; the 3-D
+ *   - Launch shape: each 2-D sweep kernel marches a wavefront, or the four
+ *     wavefronts of a workgroup one above the other, over a segment of rows
+ *     whose length the library chooses from the grid size; the 3-D
  *     sweep runs one workgroup of four wavefronts per compute unit, each
  *     marching along z through an equal share of the grid's planes.
  *     Environment variables, for tuning only, override these choices (a

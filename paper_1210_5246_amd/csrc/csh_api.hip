@@ -24,7 +24,8 @@ struct csh_grid {
     Slot* slots = nullptr;          // 3 device slots (see csh_internal.h)
     int* flag = nullptr;            // device: 1 once a non-physical state was seen
     int phase = 0;                  // slot holding the rate of the latest output
-    int ty = 32;                    // rows per wavefront segment
+    int ty = 32;                    // rows per segment of the 2-D sweep
+    int tw = 0;                     // rows per wavefront of a stacked segment (0: a wavefront per segment)
     double* adj_ws = nullptr;       // adjoint workspace, allocated on first use
     size_t adj_ws_n = 0;
     int scheme = CSH_SCHEME_MUSCL_HLL;
@@ -39,31 +40,52 @@ struct csh_grid {
 
 namespace {
 
-int rows_per_segment(int nx, int ny)
+// Work decomposition of the 2-D sweep: ty rows per segment and, for a stacked
+// segment (a workgroup of kWaves wavefronts on one strip), tw rows per
+// wavefront; tw = 0: a wavefront per segment.
+//
+// Stacked segments trace two halo rows per workgroup instead of two per
+// wavefront, at the price of two barriers and a flux exchange at their end
+// (about 0.7 of a row).  In FP64 that pays while a launch has few rows per SIMD
+// (us per step, stacked / a wavefront per segment: 64^2 5.5 / 10.3, 131 x 93
+// 6.1 / 10.5, 300 x 200 8.3 / 12.0, 512^2 13.9 / 17.0, 700 x 500 16.1 / 17.6,
+// 800^2 23.4 / 23.0, 1024^2 35.7 / 35.0): the line lies at 8 strip rows per
+// SIMD.  In FP32, whose rows are too short for the latency of one or two
+// wavefronts per SIMD, always (2048^2 66 / 86, 4096^2 240 / 242).
+void split_rows(csh_grid* h)
 {
-    if (const char* e = std::getenv("CSH_ROWS")) {
-        const int v = std::atoi(e);
-        if (v >= 1) return v;
-    }
-    // The segment length that minimises the critical path of the busiest SIMD:
-    // ceil(wavefronts / 1024 SIMDs) wavefronts in turn, each marching its rows
-    // plus the two halo rows it re-traces.  Fitted on square grids of 256^2 to
-    // 4096^2 (measured: within a few % of the best length at every size, where
-    // a fixed wavefront count had lost up to 38% at 1024^2 to halo rows).
-    // Lengths below 8 rows only when 8 would leave fewer wavefronts than CUs.
-    const long strips = (nx + csh::kStrip - 1) / csh::kStrip;
-    auto waves = [&](int t) { return strips * ((ny + t - 1) / t); };
-    const int lo = waves(8) >= 256 ? 8 : 4;
-    int best = lo;
+    const long strips = (h->nx + csh::kStrip - 1) / csh::kStrip, ny = h->ny;
+    const bool stacked = h->dtype == CSH_F32 || strips * ny <= 8L * 1024;
+    int rows = 0;
+    if (const char* e = std::getenv("CSH_ROWS")) rows = std::max(0, std::atoi(e));
     long best_cost = -1;
-    for (int t = lo; t <= 96; ++t) {
-        const long cost = ((waves(t) + 1023) / 1024) * (t + 2);
-        if (best_cost < 0 || cost < best_cost) {
-            best_cost = cost;
-            best = t;
+    if (stacked && rows == 0) {
+        // tw rows on each of the wavefronts of a CU, one workgroup after the
+        // other; a second resident workgroup fills the first one's stalls
+        // (measured 0.88 of twice the time)
+        for (int t = 1; t <= 64; ++t) {
+            const long per_cu = (strips * ((ny + csh::kWaves * t - 3) / (csh::kWaves * t - 2)) + 255) / 256;
+            const long cost = per_cu * (10 * t + 7) * (per_cu > 1 ? 22 : 25);
+            if (best_cost < 0 || cost < best_cost) {
+                best_cost = cost;
+                rows = csh::kWaves * t - 2;
+            }
+        }
+    } else if (rows == 0) {
+        // The segment length that minimises the critical path of the busiest SIMD:
+        // ceil(wavefronts / 1024 SIMDs) wavefronts in turn, each marching its rows
+        // plus the two halo rows it re-traces.
+        for (int t = 8; t <= 96; ++t) {
+            const long cost = ((strips * ((ny + t - 1) / t) + 1023) / 1024) * (t + 2);
+            if (best_cost < 0 || cost < best_cost) {
+                best_cost = cost;
+                rows = t;
+            }
         }
     }
-    return best;
+    rows = (int)std::min<long>(rows, ny);
+    h->ty = rows;
+    h->tw = stacked ? (rows + 2 + csh::kWaves - 1) / csh::kWaves : 0;
 }
 
 // Riemann solver of the characteristic sweep
@@ -84,6 +106,7 @@ csh::StepArgs<T> base_args(const csh_grid* h)
     a.dy = h->dy;
     a.nstrips = (h->nx + csh::kStrip - 1) / csh::kStrip;
     a.ty = h->ny > 1 ? h->ty : 1;
+    a.tw = h->tw;
     a.nsegs = (h->ny + a.ty - 1) / a.ty;
     a.slots = h->slots;
     a.vc2 = h->vc * h->vc;
@@ -196,7 +219,7 @@ extern "C" int csh_init_state(csh_grid** out, int nx, int ny, double dx, double 
     h->bcy = bc_y;
     h->dtype = dtype;
     h->stream = static_cast<hipStream_t>(stream);
-    h->ty = rows_per_segment(nx, ny);
+    split_rows(h);
     auto cleanup = [&](int code) {
         csh_destroy(h);
         return code;

@@ -10,11 +10,15 @@
 // and marches up a segment of rows.  Lane l holds column x0 - 2 + l, so the
 // two lanes at each edge are the stencil halo.  x neighbours come from lane
 // shuffles; the rows r-1, r, r+1 the y slopes need, the flux of the previous
-// row and the high y-face state of the cell below stay in registers.  No LDS
-// and no second pass: each input cell is read from HBM once per strip it
-// belongs to (64/60 columns) and each output cell is written once.
+// row and the high y-face state of the cell below stay in registers.  No
+// second pass: each input cell is read from HBM once per strip it belongs to
+// (64/60 columns) and each output cell is written once.  LDS carries only the
+// faces between the rows of two wavefronts (small grids).
+#include <type_traits>
+
 #include "csh_device.h"
 #include "csh_internal.h"
+#include "csh_xcd.h"
 
 namespace csh {
 
@@ -33,79 +37,167 @@ __device__ __forceinline__ double step_dt(const StepArgs<T>& p, double* t_now)
     return dt;
 }
 
+// The step's time and log, and the slot of the step after cleared (one workgroup).
 template <typename T>
-__device__ __forceinline__ void store_face(T* __restrict__ F, size_t plane, size_t idx, const Cons<T>& f)
+__device__ __forceinline__ void open_step(const StepArgs<T>& p, double t_now, double dt)
 {
-    store_cons(F, plane, idx, f);
+    if (blockIdx.x != 0) return;
+    slot_clear(p.slots[p.s_reset], threadIdx.x);
+    if (threadIdx.x == 0) {
+        p.slots[p.s_out].t = t_now + dt;
+        if (p.dt_log) *p.dt_log = dt;
+    }
 }
 
-template <typename T, bool TWOD, bool FLUXES, int RS>
-__global__ __launch_bounds__(64 * kWaves) void sweep_kernel(StepArgs<T> p)
+// The wavefront's CFL rate into the output slot, and the non-physical flag.
+template <typename T>
+__device__ __forceinline__ void close_step(const StepArgs<T>& p, int lane, double smax, bool bad)
+{
+    smax = wave_max(smax);
+    if (lane == 0) slot_add(p.slots[p.s_out], blockIdx.x, smax);
+    if (__any(bad) && lane == 0) atomicOr(p.flag, 1);
+}
+
+// One-dimensional grids: a lane per cell, 60 cells per wavefront (two halo
+// lanes per side).
+template <typename T, bool FLUXES, int RS>
+__global__ __launch_bounds__(64 * kWaves) void sweep1d_kernel(StepArgs<T> p)
 {
     double t_now;
     const double dt = step_dt(p, &t_now);
-    if (!FLUXES && blockIdx.x == 0) {
-        slot_clear(p.slots[p.s_reset], threadIdx.x);
-        if (threadIdx.x == 0) {
-            p.slots[p.s_out].t = t_now + dt;
-            if (p.dt_log) *p.dt_log = dt;
-        }
-    }
-
+    if (!FLUXES) open_step(p, t_now, dt);
     const int lane = threadIdx.x & 63;
     const int wid = blockIdx.x * kWaves + wave_in_block();
-    if (wid >= p.nstrips * p.nsegs) return;  // uniform per wavefront
-    const int sx = wid % p.nstrips, sy = wid / p.nstrips;
+    if (wid >= p.nstrips) return;  // uniform per wavefront
+    const int c = wid * kStrip - 2 + lane;  // cell of this lane
+    const Cons<T> U0 = load_cons(p.U, (size_t)p.nx, (size_t)map_index(c, p.nx, p.bcx));
+    const Cons<T> F = flux_1d<T, RS>(U0, T(dt / (2.0 * p.dx)));  // face c + 1/2
+    if constexpr (FLUXES) {
+        // lanes 1..61 hold faces x0 - 1/2 .. x0 + 59 + 1/2
+        if (lane >= 1 && lane <= 1 + kStrip && c >= -1 && c <= p.nx - 1)
+            store_cons(p.Fx, (size_t)(p.nx + 1), (size_t)(c + 1), F);
+        return;
+    }
+    double smax = 0.0;
+    bool bad = false;
+    Cons<T> Un = update(U0, T(dt / p.dx), F, lane_shift<-1>(F));
+    kick(Un, p, dt, c, 0, false);
+    if (lane >= 2 && lane < 2 + kStrip && c < p.nx) {
+        store_cons(p.Unew, (size_t)p.nx, (size_t)c, Un);
+        const Prim<T> wn = to_prim(Un);
+        smax = signal_rate<T, false>(wn, 1.0 / p.dx, 0.0);
+        bad = !physical(wn);
+    }
+    close_step(p, lane, smax, bad);
+}
+
+// Two-dimensional grids.  A row's work: the face states of its cells, the y flux
+// at their low faces (against the high states of the row below, in registers),
+// which finishes the row below, and the x fluxes.  A wavefront marches its rows
+// from the bottom up.
+//
+// STACKED: the four wavefronts of a workgroup hold the rows y0 - 1 .. y1 of one
+// strip (rows y0 .. y1 - 1 are the outputs), a quarter each.  At the face between
+// two wavefronts' rows the lower one publishes its last high states when its
+// march ends; the upper one then forms the flux from its first low states,
+// finishes its first row and publishes the flux, with which the lower one
+// finishes its last row.  So two rows per workgroup are traced twice, not two per
+// wavefront: a small grid leaves a few rows to each wavefront, and with one
+// wavefront per SIMD a row takes ~2900 cycles (2280 of them issue).
+// Else each wavefront has a segment of its own, as many independent wavefronts
+// as fit: for grids with many rows per SIMD, bound by FP64 issue (VALU busy 0.88
+// at 4096^2, 434 us per step).  The stacked workgroups are numbered XCD-aware:
+// neighbouring strips share the 128-byte lines at their edges, in reads and in
+// partial writes, and so meet in one L2 (1024^2 37.2 -> 35.1 us, FP32 2048^2
+// 70 -> 67 us against the hardware's order).
+template <typename T, bool FLUXES, int RS, bool STACKED>
+__global__ __launch_bounds__(64 * kWaves) void sweep_kernel(StepArgs<T> p)
+{
+    // per wavefront: of its first row the low y-face state, the update without
+    // its y fluxes and the flux at its high face (read by the same lane only);
+    // the high y-face state of its last row (for the wavefront above) and the
+    // flux at the low face of its first row (for the one below)
+    enum { kLow, kFirst, kFirstHigh, kHigh, kFlux, kSlots };
+    __shared__ T xch[STACKED ? kWaves : 1][kSlots][6][64];
+    double t_now;
+    const double dt = step_dt(p, &t_now);
+    if (!FLUXES) open_step(p, t_now, dt);
+
+    const int lane = threadIdx.x & 63, w = wave_in_block();
+    // STACKED: the workgroup's wavefronts share one strip and segment; else each
+    // wavefront has its own
+    unsigned unit = xcd_block(blockIdx.x, gridDim.x);
+    if constexpr (!STACKED) {
+        unit = blockIdx.x * kWaves + w;
+        if (unit >= (unsigned)(p.nstrips * p.nsegs)) return;  // uniform per wavefront
+    }
+    const int sx = unit % p.nstrips, sy = unit / p.nstrips;
     const int c = sx * kStrip - 2 + lane;  // column of this lane
     const int gc = map_index(c, p.nx, p.bcx);
     const bool own = lane >= 2 && lane < 2 + kStrip && c < p.nx;  // lane owns an output column
     const size_t plane = (size_t)p.nx * p.ny;
+    const int y0 = sy * p.ty, y1 = min(y0 + p.ty, p.ny);
+    // rows [ra, rb) of this wavefront
+    const int ra = STACKED ? y0 - 1 + w * p.tw : y0 - 1, rb = STACKED ? min(ra + p.tw, y1 + 1) : y1 + 1;
+    const bool any = !STACKED || ra < rb;
 
-    const T kx = T(dt / (2.0 * p.dx)), cx = T(dt / p.dx);
-    const double idx = 1.0 / p.dx, idy = TWOD ? 1.0 / p.dy : 0.0;
+    const T kx = T(dt / (2.0 * p.dx)), cx = T(dt / p.dx), ky = T(dt / (2.0 * p.dy)), cy = T(dt / p.dy);
+    const double idx = 1.0 / p.dx, idy = 1.0 / p.dy;
     double smax = 0.0;
     bool bad = false;
-
-    if constexpr (!TWOD) {
-        const Cons<T> U0 = load_cons(p.U, plane, (size_t)gc);
-        const Cons<T> F = flux_1d<T, RS>(U0, kx);  // face c + 1/2
-        if constexpr (FLUXES) {
-            // lanes 1..61 hold faces x0 - 1/2 .. x0 + 59 + 1/2
-            if (lane >= 1 && lane <= 1 + kStrip && c >= -1 && c <= p.nx - 1)
-                store_face(p.Fx, (size_t)(p.nx + 1), (size_t)(c + 1), F);
-            return;
-        }
-        const Cons<T> Fm = lane_shift<-1>(F);
-        Cons<T> Un = update(U0, cx, F, Fm);
-        kick(Un, p, dt, c, 0, false);
+    const Planes<T> in(p.U, plane);
+    const OutPlanes<T> out(p.Unew, plane);
+    auto put = [&](int slot, const T (&v)[6]) {
+#pragma unroll
+        for (int k = 0; k < 6; ++k) xch[w][slot][k][lane] = v[k];
+    };
+    auto put_p = [&](int slot, const Prim<T>& v) { put(slot, {v.r, v.u, v.v, v.pxx, v.pxy, v.pyy}); };
+    auto put_c = [&](int slot, const Cons<T>& v) { put(slot, {v.r, v.mx, v.my, v.exx, v.exy, v.eyy}); };
+    auto get_p = [&](int wave, int slot) -> Prim<T> {
+        const T(*q)[64] = xch[wave][slot];
+        return {q[0][lane], q[1][lane], q[2][lane], q[3][lane], q[4][lane], q[5][lane]};
+    };
+    auto get_c = [&](int wave, int slot) -> Cons<T> {
+        const T(*q)[64] = xch[wave][slot];
+        return {q[0][lane], q[1][lane], q[2][lane], q[3][lane], q[4][lane], q[5][lane]};
+    };
+    // y flux between the high state of the cell below and the low state of the cell above
+    auto y_flux = [&](const Prim<T>& below, const Prim<T>& above) -> Cons<T> {
+        return swap(riemann_x<RS>(make_face_x(swap(below)), make_face_x(swap(above))));
+    };
+    auto plus_cy = [&](const Cons<T>& a, T s, const Cons<T>& G) -> Cons<T> {
+        return {a.r + s * G.r,     a.mx + s * G.mx,   a.my + s * G.my,
+                a.exx + s * G.exx, a.exy + s * G.exy, a.eyy + s * G.eyy};
+    };
+    // cell (c, r) from its update without and the flux through its high y face
+    auto finish = [&](int r, const Cons<T>& a, const Cons<T>& G) {
+        Cons<T> Un = plus_cy(a, -cy, G);
+        kick(Un, p, dt, c, r, true);
         if (own) {
-            store_cons(p.Unew, plane, (size_t)c, Un);
-            const Prim<T> wn = to_prim(Un);
-            smax = signal_rate<T, false>(wn, idx, idy);
-            bad = !physical(wn);
+            out.store((unsigned)(r * p.nx + c), Un);
+            smax = fmax(smax, checked_rate(Un, idx, idy, bad));
         }
-    } else {
-        const T ky = T(dt / (2.0 * p.dy)), cy = T(dt / p.dy);
-        const int y0 = sy * p.ty, y1 = min(y0 + p.ty, p.ny);
-        const Planes<T> in(p.U, plane);
-        const OutPlanes<T> out(p.Unew, plane);
+    };
+
+    Cons<T> acc{};  // update of the cell below, all but its high y-face flux
+    Prim<T> yhi_prev{};  // high y-face state of the cell below (primitive, axes not exchanged)
+    if (any) {
         auto load_row = [&](int r) -> Cons<T> {
-            const int gr = map_near(r, p.ny, p.bcy);  // rows y0 - 2 .. y1 + 1, ny >= 2
+            const int gr = map_near(r, p.ny, p.bcy);  // rows ra - 1 .. rb, ny >= 2
             return in.load((unsigned)(gr * p.nx + gc));
         };
         // Row window in three rotating register sets: the set holding row r-1
         // is refilled with row r+2, so the window advances without moves.
-        Cons<T> Ua = load_row(y0 - 2), Ub = load_row(y0 - 1), Uc = load_row(y0);
+        Cons<T> Ua = load_row(ra - 1), Ub = load_row(ra), Uc = load_row(ra + 1);
         T ia = rcp(Ua.r), ib = rcp(Ub.r), ic = rcp(Uc.r);
         Prim<T> Wa = to_prim(Ua, ia), Wb = to_prim(Ub, ib), Wc = to_prim(Uc, ic);
-        Prim<T> yhi_prev{};  // high y-face state of the cell below (primitive, axes not exchanged)
-        Cons<T> acc{};       // update of the cell below, all but its high y-face flux
         Prim<T> dly = sub(Wb, Wa);  // y difference below the row: the previous row's upper one
 
-        // one row: (Um, Wm) row r-1 (refilled with row r+2), (U0, W0, ir0) row r, Wp row r+1
-        auto row = [&](int r, Cons<T>& Um, Prim<T>& Wm, T& irm, const Cons<T>& U0, const Prim<T>& W0, T ir0,
-                       const Prim<T>& Wp) {
-            const Cons<T> Unext = load_row(min(r + 2, y1 + 1));  // past the window's end: a row already read
+        // one row: (Um, Wm) row r-1 (refilled with row r+2), (U0, W0, ir0) row r, Wp row r+1;
+        // first: row ra, whose low y flux is not formed here
+        auto row = [&](auto first, int r, Cons<T>& Um, Prim<T>& Wm, T& irm, const Cons<T>& U0, const Prim<T>& W0,
+                       T ir0, const Prim<T>& Wp) {
+            const Cons<T> Unext = load_row(min(r + 2, rb));  // past the window's end: a row already read
 
             // face states of (c, r): the x differences from the right neighbour (a lane
             // shift), the left one that of the lane to the left; the y difference below
@@ -114,77 +206,97 @@ __global__ __launch_bounds__(64 * kWaves) void sweep_kernel(StepArgs<T> p)
             const Faces<T> fs = face_states_d<T, true>(W0, ir0, lane_shift<-1>(drx), drx, dly, dry, kx, ky);
             dly = dry;
 
-            if (r >= y0) {
-                // y face r - 1/2 between the cell below (its high state) and this cell (low state)
-                const Cons<T> G = swap(riemann_x<RS>(make_face_x(swap(yhi_prev)), make_face_x(swap(fs.ylo))));
+            // x faces of row r: fluxes out, or the update of (c, r) without its y fluxes
+            auto x_part = [&]() -> Cons<T> {
+                const Cons<T> F = riemann_x<RS>(make_face_x(fs.xhi), make_face_x(lane_shift<+1>(fs.xlo)));
                 if constexpr (FLUXES) {
-                    if (own) store_face(p.Fy, (size_t)p.nx * (p.ny + 1), (size_t)r * p.nx + c, G);
-                } else if (r > y0) {  // finish cell (c, r - 1)
-                    Cons<T> Un = {acc.r - cy * G.r,     acc.mx - cy * G.mx,   acc.my - cy * G.my,
-                                  acc.exx - cy * G.exx, acc.exy - cy * G.exy, acc.eyy - cy * G.eyy};
-                    kick(Un, p, dt, c, r - 1, true);
-                    if (own) {
-                        out.store((unsigned)((r - 1) * p.nx + c), Un);
-                        smax = fmax(smax, checked_rate(Un, idx, idy, bad));
-                    }
+                    if (lane >= 1 && lane <= 1 + kStrip && c >= -1 && c <= p.nx - 1)
+                        store_cons(p.Fx, (size_t)(p.nx + 1) * p.ny, (size_t)r * (p.nx + 1) + (c + 1), F);
+                    return F;
+                } else {
+                    return update(U0, cx, F, lane_shift<-1>(F));
                 }
-                if (r < y1) {
-                    // x faces of row r, then start the update of (c, r) with its low y face
-                    const Cons<T> F = riemann_x<RS>(make_face_x(fs.xhi), make_face_x(lane_shift<+1>(fs.xlo)));
-                    if constexpr (FLUXES) {
-                        if (lane >= 1 && lane <= 1 + kStrip && c >= -1 && c <= p.nx - 1)
-                            store_face(p.Fx, (size_t)(p.nx + 1) * p.ny, (size_t)r * (p.nx + 1) + (c + 1), F);
-                    } else {
-                        const Cons<T> Fm = lane_shift<-1>(F);
-                        acc = {U0.r - cx * (F.r - Fm.r) + cy * G.r,
-                               U0.mx - cx * (F.mx - Fm.mx) + cy * G.mx,
-                               U0.my - cx * (F.my - Fm.my) + cy * G.my,
-                               U0.exx - cx * (F.exx - Fm.exx) + cy * G.exx,
-                               U0.exy - cx * (F.exy - Fm.exy) + cy * G.exy,
-                               U0.eyy - cx * (F.eyy - Fm.eyy) + cy * G.eyy};
-                    }
+            };
+            if constexpr (first.value) {
+                if constexpr (STACKED) {
+                    put_p(kLow, fs.ylo);
+                    if (w > 0 && r < y1) acc = x_part();
                 }
+            } else {
+                const Cons<T> G = y_flux(yhi_prev, fs.ylo);  // y face r - 1/2
+                if constexpr (FLUXES) {
+                    if (own) store_cons(p.Fy, (size_t)p.nx * (p.ny + 1), (size_t)r * p.nx + c, G);
+                } else if (r - 1 > ra) {
+                    finish(r - 1, acc, G);
+                } else if (STACKED && w > 0) {  // the wavefront's first row: its low flux comes last
+                    put_c(kFirst, acc);
+                    put_c(kFirstHigh, G);
+                }
+                // the update of (c, r) with its x fluxes and its low y flux
+                if (r < y1) acc = plus_cy(x_part(), cy, G);
             }
             yhi_prev = fs.yhi;
             Um = Unext;  // row r + 2 takes the place of row r - 1
             irm = rcp(Unext.r);
             Wm = to_prim(Unext, irm);
         };
+        constexpr std::true_type first{};
+        constexpr std::false_type later{};
 
-        for (int r = y0 - 1; r <= y1; r += 3) {
-            row(r, Ua, Wa, ia, Ub, Wb, ib, Wc);
-            if (r + 1 > y1) break;
-            row(r + 1, Ub, Wb, ib, Uc, Wc, ic, Wa);
-            if (r + 2 > y1) break;
-            row(r + 2, Uc, Wc, ic, Ua, Wa, ia, Wb);
+        row(first, ra, Ua, Wa, ia, Ub, Wb, ib, Wc);
+        for (int r = ra + 1; r < rb; r += 3) {
+            row(later, r, Ub, Wb, ib, Uc, Wc, ic, Wa);
+            if (r + 1 >= rb) break;
+            row(later, r + 1, Uc, Wc, ic, Ua, Wa, ia, Wb);
+            if (r + 2 >= rb) break;
+            row(later, r + 2, Ua, Wa, ia, Ub, Wb, ib, Wc);
         }
-        if constexpr (FLUXES) return;
+        if constexpr (STACKED) put_p(kHigh, yhi_prev);
     }
 
-    smax = wave_max(smax);
-    if (lane == 0) slot_add(p.slots[p.s_out], blockIdx.x, smax);
-    if (__any(bad) && lane == 0) atomicOr(p.flag, 1);
+    if constexpr (STACKED) {
+        // the faces between the wavefronts' rows (wavefront w - 1's rows end where w's begin)
+        __syncthreads();
+        if (any && w > 0) {
+            const Cons<T> G = y_flux(get_p(w - 1, kHigh), get_p(w, kLow));
+            if constexpr (FLUXES) {
+                if (own) store_cons(p.Fy, (size_t)p.nx * (p.ny + 1), (size_t)ra * p.nx + c, G);
+            } else {
+                put_c(kFlux, G);
+                if (rb - ra == 1) acc = plus_cy(acc, cy, G);
+                else finish(ra, plus_cy(get_c(w, kFirst), cy, G), get_c(w, kFirstHigh));
+            }
+        }
+        if constexpr (!FLUXES) {
+            __syncthreads();
+            // the last row, unless it lies outside the outputs (then the march finished the one below it)
+            if (any && rb - 1 >= y0 && rb - 1 < y1) finish(rb - 1, acc, get_c(w + 1, kFlux));
+        }
+    }
+    if constexpr (!FLUXES) close_step(p, lane, smax, bad);
 }
 
-template <typename T, int RS>
-void launch_sweep(const StepArgs<T>& a, bool twod, bool fluxes, dim3 grid, dim3 block, hipStream_t s)
+template <typename T, bool FLUXES, int RS>
+void launch_sweep(const StepArgs<T>& a, bool twod, hipStream_t s)
 {
-    if (twod) {
-        if (fluxes) sweep_kernel<T, true, true, RS><<<grid, block, 0, s>>>(a);
-        else sweep_kernel<T, true, false, RS><<<grid, block, 0, s>>>(a);
-    } else {
-        if (fluxes) sweep_kernel<T, false, true, RS><<<grid, block, 0, s>>>(a);
-        else sweep_kernel<T, false, false, RS><<<grid, block, 0, s>>>(a);
-    }
+    const dim3 block(64 * kWaves);
+    const unsigned units = (unsigned)(a.nstrips * a.nsegs);
+    if (!twod) sweep1d_kernel<T, FLUXES, RS><<<(a.nstrips + kWaves - 1) / kWaves, block, 0, s>>>(a);
+    else if (sizeof(T) == 4 || a.tw > 0) sweep_kernel<T, FLUXES, RS, true><<<units, block, 0, s>>>(a);
+    else if constexpr (sizeof(T) == 8)
+        sweep_kernel<T, FLUXES, RS, false><<<(units + kWaves - 1) / kWaves, block, 0, s>>>(a);
 }
 
 template <typename T>
 hipError_t launch_step(const StepArgs<T>& a, bool twod, bool fluxes, int solver, hipStream_t s)
 {
-    const int nwaves = a.nstrips * a.nsegs;
-    const dim3 grid((nwaves + kWaves - 1) / kWaves), block(64 * kWaves);
-    if (solver == 1) launch_sweep<T, 1>(a, twod, fluxes, grid, block, s);
-    else launch_sweep<T, 0>(a, twod, fluxes, grid, block, s);
+    if (solver == 1) {
+        if (fluxes) launch_sweep<T, true, 1>(a, twod, s);
+        else launch_sweep<T, false, 1>(a, twod, s);
+    } else {
+        if (fluxes) launch_sweep<T, true, 0>(a, twod, s);
+        else launch_sweep<T, false, 0>(a, twod, s);
+    }
     return hipGetLastError();
 }
 

@@ -63,6 +63,7 @@ struct StepArgs {
     int nx, ny, bcx, bcy;
     double dx, dy;
     int nstrips, nsegs, ty;  // strips of kStrip columns, segments of ty rows
+    int tw;                  // 2-D sweep: rows per wavefront of a segment's ty + 2
     double dt;               // timestep when dev_dt == 0
     int dev_dt;              // 1: dt = min(cfl / s, t_end - t) from slots[s_in]
     double cfl, t_end;       // t_end <= 0: no end time
