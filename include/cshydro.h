@@ -215,6 +215,8 @@ int csh_fluxes(csh_grid *h, double dt, const void *U, void *Fx, void *Fy);
  * same size).  dt_log: device array of nsteps doubles receiving each step's
  * timestep, or NULL.  No host synchronisation between steps; the sequence is
  * captured once as a HIP graph per (nsteps, buffers, cfl, t_end) and replayed.
+ * A 1-D grid of at most 960 cells takes the whole run in one launch instead, on
+ * the handle's stream (U_work is then not written).
  */
 int csh_run_cfl(csh_grid *h, int nsteps, double cfl, double t_end, void *U, void *U_work,
                 double *dt_log);
@@ -228,7 +230,7 @@ int csh_run_cfl(csh_grid *h, int nsteps, double cfl, double t_end, void *U, void
  * through.  For reverse passes that keep the whole trajectory in memory (a
  * 512 x 512 FP64 run of 200 steps is 2.5 GB).  The steps are launched on the
  * handle's stream directly (no graph: the state array is usually new at every
- * call); asynchronous.
+ * call; short 1-D grids in one launch); asynchronous.
  */
 int csh_run_cfl_states(csh_grid *h, int nsteps, double cfl, const void *U0, void *states, double *dt_log);
 

@@ -100,6 +100,30 @@ hipError_t launch_kt(const StepArgs<T>& a, bool final_stage, hipStream_t s);
 template <typename T>
 hipError_t launch_kt_fused(StepArgs<T> a, hipStream_t s);
 
+// Whole runs of a 1-D grid of at most kLineCells cells in one launch.  U: in
+// place (null: the input U0 is left); states: if set, step k's result goes to
+// states + 6 nx k; dts: if set, the given timesteps, else cfl / s, clipped at
+// t_end (<= 0: none).  The slots are left as after nsteps single steps.
+constexpr int kLineCells = 16 * kStrip;
+
+template <typename T>
+struct LineArgs {
+    const T* U0;
+    T *U, *states;
+    int nx, bcx, nsteps;
+    double dx, dy, cfl, t_end;
+    const double* dts;
+    double* dt_log;
+    Slot* slots;
+    int s_out;
+    int* flag;
+    double vc2, rc2, x0, y0;
+};
+
+// scheme: 0 characteristic with HLL, 1 with HLLC, 2 Kurganov-Tadmor
+template <typename T>
+hipError_t launch_line_run(const LineArgs<T>& a, int scheme, hipStream_t s);
+
 template <typename T>
 hipError_t launch_copy(const T* src, T* dst, int64_t n, hipStream_t s);
 
