@@ -37,9 +37,7 @@
  *                    was recorded with);
  *       CSH_PLANES   the most planes the 3-D sweep marches in one piece;
  *       CSH_WG3      workgroups of the 3-D sweep;
- *     the last two are read at every csh3_step and whenever csh3_run_cfl
- *     records its graph (a recorded graph keeps the values it was recorded
- *     with).
+ *     the last two are read at every step of csh3_step and csh3_run_cfl.
  */
 #ifndef CSHYDRO_H
 #define CSHYDRO_H
@@ -213,8 +211,9 @@ int csh_fluxes(csh_grid *h, double dt, const void *U, void *Fx, void *Fy);
  * the state unchanged).  U: device state, updated in place on return (the
  * steps alternate between U and U_work, a caller-owned device buffer of the
  * same size).  dt_log: device array of nsteps doubles receiving each step's
- * timestep, or NULL.  No host synchronisation between steps; the sequence is
- * captured once as a HIP graph per (nsteps, buffers, cfl, t_end) and replayed.
+ * timestep, or NULL.  No host synchronisation between steps; on small grids the
+ * sequence is captured once as a HIP graph per (nsteps, state buffers, cfl,
+ * t_end) and replayed, on larger ones the steps are launched one by one.
  * A 1-D grid of at most 960 cells takes the whole run in one launch instead, on
  * the handle's stream (U_work is then not written).
  */
@@ -237,8 +236,8 @@ int csh_run_cfl_states(csh_grid *h, int nsteps, double cfl, const void *U0, void
 /*
  * Advance nsteps steps with given timesteps: step k uses dts[k] (device array
  * of nsteps doubles, read when the step runs).  U is updated in place (U_work
- * as for csh_run_cfl); captured once as a HIP graph per (nsteps, buffers, dts)
- * and replayed.  Replays a recorded run exactly (the timesteps of csh_run_cfl's
+ * as for csh_run_cfl); launched as csh_run_cfl, a graph per (nsteps, buffers,
+ * dts).  Replays a recorded run exactly (the timesteps of csh_run_cfl's
  * dt_log reproduce its states bit for bit).
  */
 int csh_run_dts(csh_grid *h, int nsteps, const double *dts, void *U, void *U_work);
@@ -284,9 +283,8 @@ int csh_batch_init(csh_batch **b, int ntubes, const int64_t *offsets, int dtype,
 /*
  * Advance every tube nsteps steps, each with its own CFL timestep
  * dt = cfl / s_k recomputed on the device after every step, in one persistent
- * launch (workgroups take whole tubes, longest first, from a device queue;
- * replayed from a captured HIP graph).  U is updated in place (U_work: caller
- * buffer of the same size).  dt_out: device array [ntubes][nsteps] of the
+ * launch (workgroups take whole tubes, longest first, from a device queue).
+ * U is updated in place (U_work: caller buffer of the same size).  dt_out: device array [ntubes][nsteps] of the
  * timesteps taken, or NULL.  threads: workgroup size (64, 128, 256, 512 or
  * 1024), or 0 for the size chosen by csh_batch_autotune (256 if never tuned).
  */
@@ -358,7 +356,7 @@ int csh3_max_signal_speed(csh3_grid *h, const void *U, double *s);
 int csh3_last_signal_speed(csh3_grid *h, double *s);
 
 /* nsteps steps with dt = cfl / s chosen on the device from each step's input,
- * replayed from a captured HIP graph (recorded once per argument set).  U is
+ * launched one after the other with no host synchronisation between.  U is
  * advanced in place, U_work is scratch of the same size, dt_log (device,
  * nsteps doubles) receives the timesteps.  Synchronises. */
 int csh3_run_cfl(csh3_grid *h, int nsteps, double cfl, void *U, void *U_work, double *dt_log);

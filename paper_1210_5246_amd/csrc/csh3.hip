@@ -335,7 +335,7 @@ __global__ __launch_bounds__(256) void sweep3_kernel(SArgs q)
 
     smax = wave_max(smax);
     if (lane == 0) slot_add(p.slots[p.s_out], blockIdx.x, smax);
-    if (__any(bad) && lane == 0) atomicOr(p.flag, 1);
+    if (__any(bad) && lane == 0) raise_flag(p.flag);
 }
 
 __global__ __launch_bounds__(256) void init3_kernel(const double* __restrict__ W, double* __restrict__ U, int64_t n,
@@ -350,7 +350,7 @@ __global__ __launch_bounds__(256) void init3_kernel(const double* __restrict__ W
 #pragma unroll
         for (int m = 0; m < NV; ++m) U[m * n + c] = u.v[m];
     }
-    if (__any(bad) && (threadIdx.x & 63) == 0) atomicOr(flag, 1);
+    if (__any(bad) && (threadIdx.x & 63) == 0) raise_flag(flag);
 }
 
 __global__ __launch_bounds__(256) void maxspeed3_kernel(const double* __restrict__ U, int64_t n, double ih0,
@@ -367,7 +367,7 @@ __global__ __launch_bounds__(256) void maxspeed3_kernel(const double* __restrict
     }
     s = wave_max(s);
     if ((threadIdx.x & 63) == 0) slot_add(*slot, blockIdx.x, s);
-    if (__any(bad) && (threadIdx.x & 63) == 0) atomicOr(flag, 1);
+    if (__any(bad) && (threadIdx.x & 63) == 0) raise_flag(flag);
 }
 
 }  // namespace d3
@@ -380,15 +380,10 @@ struct csh3_grid {
     int n[3] = {0, 0, 0}, bc[3] = {0, 0, 0};
     double h[3] = {1, 1, 1};
     hipStream_t stream = nullptr;
-    hipStream_t capture = nullptr;
     Slot* slots = nullptr;
-    int* flag = nullptr;
+    csh::HostCell* cell = nullptr;  // pinned: rate and non-physical flag for the host
     int phase = 0;
     int ncu = 256;  // compute units of the device
-    hipGraphExec_t exec = nullptr;
-    int g_nsteps = -1;
-    double g_cfl = 0;  // arguments the cached graph of csh3_run_cfl was recorded with
-    const void *g_U = nullptr, *g_W = nullptr, *g_log = nullptr;
 };
 
 namespace {
@@ -432,7 +427,7 @@ d3::Args args(csh3_grid* h, const double* U, double* Un, int dev_dt, double dt, 
     a.s_out = (h->phase + 1) % 3;
     a.s_reset = (h->phase + 2) % 3;
     a.dt_log = log;
-    a.flag = h->flag;
+    a.flag = &h->cell->flag;
     return a;
 }
 
@@ -482,27 +477,17 @@ hipError_t enqueue_maxspeed3(csh3_grid* h, const double* U, hipStream_t s)
     const int64_t n = (int64_t)ncell(h);
     const int blocks = (int)std::min<int64_t>((n + 255) / 256, 4096);
     d3::maxspeed3_kernel<<<blocks, 256, 0, s>>>(U, n, 1.0 / h->h[0], 1.0 / h->h[1], 1.0 / h->h[2],
-                                                h->slots + h->phase, h->flag);
+                                                h->slots + h->phase, &h->cell->flag);
     return hipGetLastError();
 }
 
 int read_rate(csh3_grid* h, int slot, double* s)
 {
-    Slot sl;
-    int flag = 0;
-    CSH3_HIP(hipMemcpyAsync(&sl, h->slots + slot, sizeof(Slot), hipMemcpyDeviceToHost, h->stream));
-    CSH3_HIP(hipMemcpyAsync(&flag, h->flag, sizeof(int), hipMemcpyDeviceToHost, h->stream));
+    CSH3_HIP(csh::launch_publish(h->slots + slot, h->cell, h->stream));
     CSH3_HIP(hipStreamSynchronize(h->stream));
-    *s = csh::slot_rate_host(sl);
-    if (flag) return fail3(CSH_ERR_NONPHYSICAL, "a state was not physical");
+    *s = h->cell->rate;
+    if (h->cell->flag) return fail3(CSH_ERR_NONPHYSICAL, "a state was not physical");
     return CSH_OK;
-}
-
-void drop_graph3(csh3_grid* h)
-{
-    if (h->exec) (void)hipGraphExecDestroy(h->exec);
-    h->exec = nullptr;
-    h->g_nsteps = -1;
 }
 
 }  // namespace
@@ -546,24 +531,19 @@ extern "C" int csh3_init_state(csh3_grid** out, int nx, int ny, int nz, double d
         csh3_destroy(h);
         return code;
     };
-    if (hipMalloc(&h->slots, 3 * sizeof(Slot)) != hipSuccess || hipMalloc(&h->flag, sizeof(int)) != hipSuccess)
-        return cleanup(fail3(CSH_ERR_HIP, "hipMalloc of the handle's buffers failed"));
-    if (hipStreamCreateWithFlags(&h->capture, hipStreamNonBlocking) != hipSuccess)
-        return cleanup(fail3(CSH_ERR_HIP, "hipStreamCreate failed"));
+    if (hipMalloc(&h->slots, 3 * sizeof(Slot)) != hipSuccess || !(h->cell = csh::acquire_cell()))
+        return cleanup(fail3(CSH_ERR_HIP, "allocation of the handle's buffers failed"));
     const int64_t n = (int64_t)ncell(h);
     hipError_t e = csh::launch_reset(h->slots, 3, 0.0, h->stream);
-    if (e == hipSuccess) e = hipMemsetAsync(h->flag, 0, sizeof(int), h->stream);
     if (e == hipSuccess) {
         d3::init3_kernel<<<(unsigned)((n + 255) / 256), 256, 0, h->stream>>>(static_cast<const double*>(W),
-                                                                              static_cast<double*>(U), n, h->flag);
+                                                                              static_cast<double*>(U), n, &h->cell->flag);
         e = hipGetLastError();
     }
-    int flag = 0;
-    if (e == hipSuccess) e = hipMemcpyAsync(&flag, h->flag, sizeof(int), hipMemcpyDeviceToHost, h->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
     if (e != hipSuccess) return cleanup(fail3(CSH_ERR_HIP, std::string("init: ") + hipGetErrorString(e)));
     *out = h;
-    if (flag) return fail3(CSH_ERR_NONPHYSICAL, "initial state not physical");
+    if (h->cell->flag) return fail3(CSH_ERR_NONPHYSICAL, "initial state not physical");
     return CSH_OK;
 }
 
@@ -572,20 +552,18 @@ extern "C" int csh3_step(csh3_grid* h, double dt, const void* U, void* U_new)
     if (!h || !U || !U_new) return fail3(CSH_ERR_ARG, "NULL argument");
     if (U == U_new) return fail3(CSH_ERR_ARG, "U_new must not alias U");
     if (!(dt >= 0)) return fail3(CSH_ERR_ARG, "dt must be >= 0");
-    CSH3_HIP(hipMemsetAsync(h->flag, 0, sizeof(int), h->stream));
+    h->cell->flag = 0;  // every call of a handle ends synchronised
     CSH3_HIP(enqueue_step3(h, static_cast<const double*>(U), static_cast<double*>(U_new), 0, dt, 0, nullptr,
                            h->stream));
-    int flag = 0;
-    CSH3_HIP(hipMemcpyAsync(&flag, h->flag, sizeof(int), hipMemcpyDeviceToHost, h->stream));
     CSH3_HIP(hipStreamSynchronize(h->stream));
-    if (flag) return fail3(CSH_ERR_NONPHYSICAL, "the new state is not physical");
+    if (h->cell->flag) return fail3(CSH_ERR_NONPHYSICAL, "the new state is not physical");
     return CSH_OK;
 }
 
 extern "C" int csh3_max_signal_speed(csh3_grid* h, const void* U, double* s)
 {
     if (!h || !U || !s) return fail3(CSH_ERR_ARG, "NULL argument");
-    CSH3_HIP(hipMemsetAsync(h->flag, 0, sizeof(int), h->stream));
+    h->cell->flag = 0;
     CSH3_HIP(enqueue_maxspeed3(h, static_cast<const double*>(U), h->stream));
     return read_rate(h, h->phase, s);
 }
@@ -624,47 +602,20 @@ extern "C" int csh3_run_cfl(csh3_grid* h, int nsteps, double cfl, void* U, void*
     if (U == U_work) return fail3(CSH_ERR_ARG, "U and U_work must be distinct");
     if (nsteps < 0 || !(cfl > 0)) return fail3(CSH_ERR_ARG, "nsteps >= 0 and cfl > 0 required");
     if (nsteps == 0) return CSH_OK;
-    const bool same = h->exec && h->g_nsteps == nsteps && h->g_cfl == cfl && h->g_U == U && h->g_W == U_work &&
-                      h->g_log == dt_log;
-    if (!same) {
-        drop_graph3(h);
-        hipGraph_t graph = nullptr;
-        CSH3_HIP(hipStreamBeginCapture(h->capture, hipStreamCaptureModeThreadLocal));
-        hipError_t e = enqueue_run3(h, nsteps, cfl, U, U_work, dt_log, h->capture);
-        hipError_t e2 = hipStreamEndCapture(h->capture, &graph);
-        if (e != hipSuccess || e2 != hipSuccess) {
-            if (graph) (void)hipGraphDestroy(graph);
-            return fail3(CSH_ERR_HIP, std::string("capture: ") + hipGetErrorString(e != hipSuccess ? e : e2));
-        }
-        e = hipGraphInstantiate(&h->exec, graph, nullptr, nullptr, 0);
-        (void)hipGraphDestroy(graph);
-        if (e != hipSuccess) {
-            h->exec = nullptr;
-            return fail3(CSH_ERR_HIP, std::string("instantiate: ") + hipGetErrorString(e));
-        }
-        h->g_nsteps = nsteps;
-        h->g_cfl = cfl;
-        h->g_U = U;
-        h->g_W = U_work;
-        h->g_log = dt_log;
-    }
-    CSH3_HIP(hipMemsetAsync(h->flag, 0, sizeof(int), h->stream));
-    CSH3_HIP(hipGraphLaunch(h->exec, h->stream));
-    h->phase = nsteps % 3;
-    int flag = 0;
-    CSH3_HIP(hipMemcpyAsync(&flag, h->flag, sizeof(int), hipMemcpyDeviceToHost, h->stream));
+    // plain launches: a step takes far longer than its launch (38 us at 61 x 47 x 33
+    // against 3), so a recorded graph would save nothing and cost its recording
+    h->cell->flag = 0;
+    CSH3_HIP(enqueue_run3(h, nsteps, cfl, U, U_work, dt_log, h->stream));
     CSH3_HIP(hipStreamSynchronize(h->stream));
-    if (flag) return fail3(CSH_ERR_NONPHYSICAL, "a state was not physical");
+    if (h->cell->flag) return fail3(CSH_ERR_NONPHYSICAL, "a state was not physical");
     return CSH_OK;
 }
 
 extern "C" void csh3_destroy(csh3_grid* h)
 {
     if (!h) return;
-    if (h->stream) (void)hipStreamSynchronize(h->stream);
-    drop_graph3(h);
-    if (h->capture) (void)hipStreamDestroy(h->capture);
+    (void)hipStreamSynchronize(h->stream);
     if (h->slots) (void)hipFree(h->slots);
-    if (h->flag) (void)hipFree(h->flag);
+    csh::release_cell(h->cell);
     delete h;
 }

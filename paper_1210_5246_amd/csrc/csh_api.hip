@@ -2,7 +2,9 @@
 #include <cstdio>
 #include <cstdlib>
 #include <algorithm>
+#include <mutex>
 #include <string>
+#include <vector>
 
 #include "cshydro.h"
 #include "csh_api_util.h"
@@ -15,6 +17,52 @@ thread_local std::string csh_err_msg;
 
 extern "C" const char* csh_last_error(void) { return csh_err_msg.c_str(); }
 
+namespace csh {
+
+namespace {
+
+struct CellPage {
+    HostCell* cells;
+    uint64_t used;  // bit k: cell k is handed out
+};
+std::mutex cell_mutex;
+std::vector<CellPage>& cell_pages = *new std::vector<CellPage>;  // outlives every handle, also at process exit
+
+}  // namespace
+
+HostCell* acquire_cell()
+{
+    std::lock_guard<std::mutex> lock(cell_mutex);
+    auto page = std::find_if(cell_pages.begin(), cell_pages.end(), [](const CellPage& p) { return ~p.used != 0; });
+    if (page == cell_pages.end()) {
+        void* cells = nullptr;  // portable: a page serves the handles of every device
+        if (hipHostMalloc(&cells, 64 * sizeof(HostCell), hipHostMallocPortable) != hipSuccess) return nullptr;
+        cell_pages.push_back({static_cast<HostCell*>(cells), 0});
+        page = cell_pages.end() - 1;
+    }
+    const int k = __builtin_ctzll(~page->used);
+    page->used |= 1ull << k;
+    page->cells[k] = HostCell{0.0, 0};
+    return page->cells + k;
+}
+
+void release_cell(HostCell* cell)
+{
+    if (!cell) return;
+    std::lock_guard<std::mutex> lock(cell_mutex);
+    for (auto page = cell_pages.begin(); page != cell_pages.end(); ++page) {
+        if (cell < page->cells || cell >= page->cells + 64) continue;
+        page->used &= ~(1ull << (cell - page->cells));
+        if (page->used == 0 && cell_pages.size() > 1) {
+            (void)hipHostFree(page->cells);
+            cell_pages.erase(page);
+        }
+        return;
+    }
+}
+
+}  // namespace csh
+
 struct csh_grid {
     int nx = 0, ny = 0, bcx = 0, bcy = 0, dtype = CSH_F64;
     double dx = 1, dy = 1;
@@ -22,7 +70,7 @@ struct csh_grid {
     hipStream_t stream = nullptr;
     hipStream_t capture = nullptr;  // private stream used only to record graphs
     Slot* slots = nullptr;          // 3 device slots (see csh_internal.h)
-    int* flag = nullptr;            // device: 1 once a non-physical state was seen
+    csh::HostCell* cell = nullptr;  // pinned: rate and non-physical flag for the host
     int phase = 0;                  // slot holding the rate of the latest output
     int ty = 32;                    // rows per segment of the 2-D sweep
     int tw = 0;                     // rows per wavefront of a stacked segment (0: a wavefront per segment)
@@ -36,6 +84,8 @@ struct csh_grid {
     int g_mode = -1, g_nsteps = -1;
     double g_cfl = 0, g_tend = 0;
     const void *g_U = nullptr, *g_W = nullptr, *g_log = nullptr;
+    double* log = nullptr;          // the recorded run's timestep log, copied to the caller's
+    int log_n = 0;
 };
 
 namespace {
@@ -113,7 +163,7 @@ csh::StepArgs<T> base_args(const csh_grid* h)
     a.rc2 = h->rc * h->rc;
     a.x0 = h->x0;
     a.y0 = h->y0;
-    a.flag = h->flag;
+    a.flag = &h->cell->flag;
     return a;
 }
 
@@ -164,20 +214,17 @@ hipError_t enqueue_maxspeed(csh_grid* h, const void* U, hipStream_t s)
     if (e != hipSuccess) return e;
     if (h->dtype == CSH_F64)
         return csh::launch_maxspeed<double>(static_cast<const double*>(U), h->nx, h->ny, h->dx, h->dy,
-                                            h->slots + h->phase, h->flag, s);
+                                            h->slots + h->phase, &h->cell->flag, s);
     return csh::launch_maxspeed<float>(static_cast<const float*>(U), h->nx, h->ny, h->dx, h->dy,
-                                       h->slots + h->phase, h->flag, s);
+                                       h->slots + h->phase, &h->cell->flag, s);
 }
 
 int read_rate(csh_grid* h, double* s)
 {
-    Slot sl;
-    int flag = 0;
-    CSH_HIP(hipMemcpyAsync(&sl, h->slots + h->phase, sizeof(Slot), hipMemcpyDeviceToHost, h->stream));
-    CSH_HIP(hipMemcpyAsync(&flag, h->flag, sizeof(int), hipMemcpyDeviceToHost, h->stream));
+    CSH_HIP(csh::launch_publish(h->slots + h->phase, h->cell, h->stream));
     CSH_HIP(hipStreamSynchronize(h->stream));
-    *s = csh::slot_rate_host(sl);
-    if (flag) return csh_fail(CSH_ERR_NONPHYSICAL, "non-physical state (rho <= 0, stress not positive-definite or non-finite)");
+    *s = h->cell->rate;
+    if (h->cell->flag) return csh_fail(CSH_ERR_NONPHYSICAL, "non-physical state (rho <= 0, stress not positive-definite or non-finite)");
     return CSH_OK;
 }
 
@@ -224,22 +271,19 @@ extern "C" int csh_init_state(csh_grid** out, int nx, int ny, double dx, double 
         csh_destroy(h);
         return code;
     };
-    if (hipMalloc(&h->slots, 3 * sizeof(Slot)) != hipSuccess || hipMalloc(&h->flag, sizeof(int)) != hipSuccess)
-        return cleanup(csh_fail(CSH_ERR_HIP, "hipMalloc of the handle's scalars failed"));
+    if (hipMalloc(&h->slots, 3 * sizeof(Slot)) != hipSuccess || !(h->cell = csh::acquire_cell()))
+        return cleanup(csh_fail(CSH_ERR_HIP, "allocation of the handle's scalars failed"));
     if (hipStreamCreateWithFlags(&h->capture, hipStreamNonBlocking) != hipSuccess)
         return cleanup(csh_fail(CSH_ERR_HIP, "hipStreamCreate failed"));
     const int64_t n = (int64_t)nx * ny;
     hipError_t e = csh::launch_reset(h->slots, 3, 0.0, h->stream);
-    if (e == hipSuccess) e = hipMemsetAsync(h->flag, 0, sizeof(int), h->stream);
     if (e == hipSuccess)
-        e = dtype == CSH_F64 ? csh::launch_init<double>(static_cast<const double*>(W), static_cast<double*>(U), n, h->flag, h->stream)
-                             : csh::launch_init<float>(static_cast<const float*>(W), static_cast<float*>(U), n, h->flag, h->stream);
-    int flag = 0;
-    if (e == hipSuccess) e = hipMemcpyAsync(&flag, h->flag, sizeof(int), hipMemcpyDeviceToHost, h->stream);
+        e = dtype == CSH_F64 ? csh::launch_init<double>(static_cast<const double*>(W), static_cast<double*>(U), n, &h->cell->flag, h->stream)
+                             : csh::launch_init<float>(static_cast<const float*>(W), static_cast<float*>(U), n, &h->cell->flag, h->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
     if (e != hipSuccess) return cleanup(csh_fail(CSH_ERR_HIP, std::string("init: ") + hipGetErrorString(e)));
     *out = h;
-    if (flag) return csh_fail(CSH_ERR_NONPHYSICAL, "initial state not physical");
+    if (h->cell->flag) return csh_fail(CSH_ERR_NONPHYSICAL, "initial state not physical");
     return CSH_OK;
 }
 
@@ -247,15 +291,13 @@ extern "C" int csh_set_state(csh_grid* h, const void* W, void* U)
 {
     if (!h || !W || !U) return csh_fail(CSH_ERR_ARG, "NULL argument");
     const int64_t n = (int64_t)h->nx * h->ny;
-    hipError_t e = hipMemsetAsync(h->flag, 0, sizeof(int), h->stream);
+    hipError_t e = csh::launch_clear_flag(&h->cell->flag, h->stream);
     if (e == hipSuccess)
-        e = h->dtype == CSH_F64 ? csh::launch_init<double>(static_cast<const double*>(W), static_cast<double*>(U), n, h->flag, h->stream)
-                                : csh::launch_init<float>(static_cast<const float*>(W), static_cast<float*>(U), n, h->flag, h->stream);
-    int flag = 0;
-    if (e == hipSuccess) e = hipMemcpyAsync(&flag, h->flag, sizeof(int), hipMemcpyDeviceToHost, h->stream);
+        e = h->dtype == CSH_F64 ? csh::launch_init<double>(static_cast<const double*>(W), static_cast<double*>(U), n, &h->cell->flag, h->stream)
+                                : csh::launch_init<float>(static_cast<const float*>(W), static_cast<float*>(U), n, &h->cell->flag, h->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
     if (e != hipSuccess) return csh_fail(CSH_ERR_HIP, std::string("set_state: ") + hipGetErrorString(e));
-    if (flag) return csh_fail(CSH_ERR_NONPHYSICAL, "state not physical");
+    if (h->cell->flag) return csh_fail(CSH_ERR_NONPHYSICAL, "state not physical");
     return CSH_OK;
 }
 
@@ -453,7 +495,7 @@ hipError_t enqueue_line_run(csh_grid* h, int nsteps, double cfl, double t_end, c
     a.dt_log = dt_log;
     a.slots = h->slots;
     h->phase = a.s_out = nsteps % 3;
-    a.flag = h->flag;
+    a.flag = &h->cell->flag;
     a.vc2 = h->vc * h->vc;
     a.rc2 = h->rc * h->rc;
     a.x0 = h->x0;
@@ -471,19 +513,50 @@ int line_run(csh_grid* h, int nsteps, double cfl, double t_end, const void* U0, 
     return CSH_OK;
 }
 
-// record (once per distinct argument set) and replay the graph of a run
-// (mode 0: csh_run_cfl, 1: csh_run_dts)
-int run_graph(csh_grid* h, int mode, int nsteps, double cfl, double t_end, void* U, void* U_work,
-              const void* lg)
+// Whether a run's steps are replayed as a recorded graph.  The host enqueues a
+// launch in ~3 us and the device takes ~0.4 us longer between two of them than
+// between two nodes of a graph, but recording 100 steps takes 0.4-0.5 ms: from
+// 4 strip rows per SIMD (a step of 13 us, 512^2) the plain launches are as fast
+// (100 steps of 512^2: 1389 against 1396 us, 64^2: 549 against 509 us) and the
+// first run is spared the recording (1480 against 1750 us).
+bool worth_recording(const csh_grid* h)
 {
+    return (long)((h->nx + csh::kStrip - 1) / csh::kStrip) * h->ny <= 4L * 1024;
+}
+
+// All steps of csh_run_cfl (mode 0, lg: the log or null) or csh_run_dts (mode 1,
+// lg: the timesteps): launched one by one, or replayed from a graph recorded once
+// per argument set.  The graph logs into the handle's own buffer, so that it
+// serves every log the caller passes.
+int run_steps(csh_grid* h, int mode, int nsteps, double cfl, double t_end, void* U, void* U_work, const void* lg)
+{
+    auto enqueue = [&](const void* l, hipStream_t s) {
+        return mode == 0 ? enqueue_run(h, nsteps, cfl, t_end, U, U_work, (double*)l, nullptr, s)
+                         : enqueue_run(h, nsteps, 1.0, 0.0, U, U_work, nullptr, (const double*)l, s);
+    };
+    if (!worth_recording(h)) {
+        const hipError_t e = enqueue(lg, h->stream);
+        if (e != hipSuccess) return csh_fail(CSH_ERR_HIP, std::string("run: ") + hipGetErrorString(e));
+        return CSH_OK;
+    }
+    const bool log = mode == 0 && lg;
+    if (log && h->log_n < nsteps) {
+        CSH_HIP(hipStreamSynchronize(h->stream));
+        drop_graph(h);
+        if (h->log) (void)hipFree(h->log);
+        h->log = nullptr;
+        h->log_n = 0;
+        CSH_HIP(hipMalloc(&h->log, sizeof(double) * (size_t)nsteps));
+        h->log_n = nsteps;
+    }
+    const void* l = log ? h->log : lg;
     const bool same = h->exec && h->g_mode == mode && h->g_nsteps == nsteps && h->g_cfl == cfl &&
-                      h->g_tend == t_end && h->g_U == U && h->g_W == U_work && h->g_log == lg;
+                      h->g_tend == t_end && h->g_U == U && h->g_W == U_work && h->g_log == l;
     if (!same) {
         drop_graph(h);
         hipGraph_t g = nullptr;
         CSH_HIP(hipStreamBeginCapture(h->capture, hipStreamCaptureModeThreadLocal));
-        hipError_t e = mode == 0 ? enqueue_run(h, nsteps, cfl, t_end, U, U_work, (double*)lg, nullptr, h->capture)
-                                 : enqueue_run(h, nsteps, 1.0, 0.0, U, U_work, nullptr, (const double*)lg, h->capture);
+        hipError_t e = enqueue(l, h->capture);
         hipError_t e2 = hipStreamEndCapture(h->capture, &g);
         if (e != hipSuccess || e2 != hipSuccess) {
             if (g) (void)hipGraphDestroy(g);
@@ -501,10 +574,11 @@ int run_graph(csh_grid* h, int mode, int nsteps, double cfl, double t_end, void*
         h->g_tend = t_end;
         h->g_U = U;
         h->g_W = U_work;
-        h->g_log = lg;
+        h->g_log = l;
     }
     CSH_HIP(hipGraphLaunch(h->exec, h->stream));
     h->phase = nsteps % 3;
+    if (log) CSH_HIP(csh::launch_copy<double>(h->log, (double*)lg, nsteps, h->stream));
     return CSH_OK;
 }
 
@@ -518,7 +592,7 @@ extern "C" int csh_run_cfl(csh_grid* h, int nsteps, double cfl, double t_end, vo
     if (nsteps < 0 || !(cfl > 0)) return csh_fail(CSH_ERR_ARG, "nsteps >= 0 and cfl > 0 required");
     if (nsteps == 0) return CSH_OK;
     if (one_launch(h)) return line_run(h, nsteps, cfl, t_end, U, U, nullptr, dt_log, nullptr);
-    return run_graph(h, 0, nsteps, cfl, t_end, U, U_work, dt_log);
+    return run_steps(h, 0, nsteps, cfl, t_end, U, U_work, dt_log);
 }
 
 extern "C" int csh_run_cfl_states(csh_grid* h, int nsteps, double cfl, const void* U0, void* states,
@@ -543,7 +617,7 @@ extern "C" int csh_run_dts(csh_grid* h, int nsteps, const double* dts, void* U, 
     if (nsteps < 0) return csh_fail(CSH_ERR_ARG, "nsteps >= 0 required");
     if (nsteps == 0) return CSH_OK;
     if (one_launch(h)) return line_run(h, nsteps, 1.0, 0.0, U, U, nullptr, nullptr, dts);
-    return run_graph(h, 1, nsteps, 0.0, 0.0, U, U_work, dts);
+    return run_steps(h, 1, nsteps, 0.0, 0.0, U, U_work, dts);
 }
 
 extern "C" int csh_destroy(csh_grid* h)
@@ -553,8 +627,9 @@ extern "C" int csh_destroy(csh_grid* h)
     drop_graph(h);
     if (h->capture) (void)hipStreamDestroy(h->capture);
     if (h->slots) (void)hipFree(h->slots);
-    if (h->flag) (void)hipFree(h->flag);
+    csh::release_cell(h->cell);
     if (h->adj_ws) (void)hipFree(h->adj_ws);
+    if (h->log) (void)hipFree(h->log);
     if (h->kt_buf) (void)hipFree(h->kt_buf);
     if (h->fourier_ws) (void)hipFree(h->fourier_ws);
     delete h;

@@ -118,7 +118,7 @@ __global__ __launch_bounds__(NT) void batch_kernel(BatchArgs a)
                 store_cons(a.U + off, plane, (size_t)i, load_cons<double>(A, plane, (size_t)i));
             __syncthreads();
         }
-        if (__any(bad) && lane == 0) atomicOr(a.flag, 1);
+        if (__any(bad) && lane == 0) raise_flag(a.flag);
     }
 }
 
@@ -160,17 +160,14 @@ int resident_blocks(int threads)
 struct csh_batch {
     int ntubes = 0;
     int64_t N = 0;
-    hipStream_t stream = nullptr, capture = nullptr;
+    hipStream_t stream = nullptr;
     int64_t* offsets = nullptr;
     int* order = nullptr;
     int* counter = nullptr;
-    int* flag = nullptr;
+    csh::HostCell* cell = nullptr;  // pinned: the non-physical flag
     int best_threads = 256;
     int max_len = 0;
-    hipGraphExec_t exec = nullptr;
-    int g_nsteps = -1, g_threads = 0;
-    double g_cfl = 0;
-    const void *g_U = nullptr, *g_W = nullptr, *g_dt = nullptr;
+    int blocks = 0, blocks_threads = 0;  // launch size of the last workgroup size used
 };
 
 namespace {
@@ -190,15 +187,8 @@ csh::BatchArgs batch_args(csh_batch* b, int nsteps, double cfl, void* U, void* U
     a.ntubes = b->ntubes;
     a.nsteps = nsteps;
     a.cfl = cfl;
-    a.flag = b->flag;
+    a.flag = &b->cell->flag;
     return a;
-}
-
-void drop_graph(csh_batch* b)
-{
-    if (b->exec) (void)hipGraphExecDestroy(b->exec);
-    b->exec = nullptr;
-    b->g_nsteps = -1;
 }
 
 }  // namespace
@@ -233,21 +223,16 @@ extern "C" int csh_batch_init(csh_batch** out, int ntubes, const int64_t* offset
     };
     if (hipMalloc(&b->offsets, sizeof(int64_t) * (ntubes + 1)) != hipSuccess ||
         hipMalloc(&b->order, sizeof(int) * ntubes) != hipSuccess || hipMalloc(&b->counter, sizeof(int)) != hipSuccess ||
-        hipMalloc(&b->flag, sizeof(int)) != hipSuccess)
-        return cleanup(csh_fail(CSH_ERR_HIP, "hipMalloc of the batch tables failed"));
-    if (hipStreamCreateWithFlags(&b->capture, hipStreamNonBlocking) != hipSuccess)
-        return cleanup(csh_fail(CSH_ERR_HIP, "hipStreamCreate failed"));
+        !(b->cell = csh::acquire_cell()))
+        return cleanup(csh_fail(CSH_ERR_HIP, "allocation of the batch tables failed"));
     hipError_t e = hipMemcpyAsync(b->offsets, offsets, sizeof(int64_t) * (ntubes + 1), hipMemcpyHostToDevice, b->stream);
     if (e == hipSuccess) e = hipMemcpyAsync(b->order, order.data(), sizeof(int) * ntubes, hipMemcpyHostToDevice, b->stream);
-    if (e == hipSuccess) e = hipMemsetAsync(b->flag, 0, sizeof(int), b->stream);
     if (e == hipSuccess)
-        e = csh::launch_init<double>(static_cast<const double*>(W), static_cast<double*>(U), b->N, b->flag, b->stream);
-    int flag = 0;
-    if (e == hipSuccess) e = hipMemcpyAsync(&flag, b->flag, sizeof(int), hipMemcpyDeviceToHost, b->stream);
+        e = csh::launch_init<double>(static_cast<const double*>(W), static_cast<double*>(U), b->N, &b->cell->flag, b->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(b->stream);
     if (e != hipSuccess) return cleanup(csh_fail(CSH_ERR_HIP, std::string("batch init: ") + hipGetErrorString(e)));
     *out = b;
-    if (flag) return csh_fail(CSH_ERR_NONPHYSICAL, "initial state not physical");
+    if (b->cell->flag) return csh_fail(CSH_ERR_NONPHYSICAL, "initial state not physical");
     return CSH_OK;
 }
 
@@ -259,44 +244,19 @@ extern "C" int csh_batch_run(csh_batch* b, int nsteps, double cfl, void* U, void
     if (threads == 0) threads = b->best_threads;
     if (!valid_threads(threads)) return csh_fail(CSH_ERR_ARG, "threads must be 64, 128, 256, 512 or 1024");
     if (nsteps == 0) return CSH_OK;
-    const bool same = b->exec && b->g_nsteps == nsteps && b->g_threads == threads && b->g_cfl == cfl &&
-                      b->g_U == U && b->g_W == U_work && b->g_dt == dt_out;
-    if (!same) {
-        drop_graph(b);
-        const int blocks = std::min(b->ntubes, csh::resident_blocks(threads));
-        const auto a = batch_args(b, nsteps, cfl, U, U_work, dt_out);
-        hipGraph_t g = nullptr;
-        CSH_HIP(hipStreamBeginCapture(b->capture, hipStreamCaptureModeThreadLocal));
-        hipError_t e = csh::launch_batch(a, threads, blocks, b->capture);
-        hipError_t e2 = hipStreamEndCapture(b->capture, &g);
-        if (e != hipSuccess || e2 != hipSuccess) {
-            if (g) (void)hipGraphDestroy(g);
-            return csh_fail(CSH_ERR_HIP, std::string("batch capture: ") + hipGetErrorString(e != hipSuccess ? e : e2));
-        }
-        e = hipGraphInstantiate(&b->exec, g, nullptr, nullptr, 0);
-        (void)hipGraphDestroy(g);
-        if (e != hipSuccess) {
-            b->exec = nullptr;
-            return csh_fail(CSH_ERR_HIP, std::string("batch instantiate: ") + hipGetErrorString(e));
-        }
-        b->g_nsteps = nsteps;
-        b->g_threads = threads;
-        b->g_cfl = cfl;
-        b->g_U = U;
-        b->g_W = U_work;
-        b->g_dt = dt_out;
+    if (b->blocks_threads != threads) {
+        b->blocks = std::min(b->ntubes, csh::resident_blocks(threads));
+        b->blocks_threads = threads;
     }
-    CSH_HIP(hipGraphLaunch(b->exec, b->stream));
+    CSH_HIP(csh::launch_batch(batch_args(b, nsteps, cfl, U, U_work, dt_out), threads, b->blocks, b->stream));
     return CSH_OK;
 }
 
 extern "C" int csh_batch_status(csh_batch* b)
 {
     if (!b) return csh_fail(CSH_ERR_ARG, "NULL argument");
-    int flag = 0;
-    CSH_HIP(hipMemcpyAsync(&flag, b->flag, sizeof(int), hipMemcpyDeviceToHost, b->stream));
     CSH_HIP(hipStreamSynchronize(b->stream));
-    if (flag) return csh_fail(CSH_ERR_NONPHYSICAL, "a tube's state was not physical");
+    if (b->cell->flag) return csh_fail(CSH_ERR_NONPHYSICAL, "a tube's state was not physical");
     return CSH_OK;
 }
 
@@ -415,12 +375,10 @@ extern "C" int csh_batch_destroy(csh_batch* b)
 {
     if (!b) return CSH_OK;
     (void)hipStreamSynchronize(b->stream);
-    drop_graph(b);
-    if (b->capture) (void)hipStreamDestroy(b->capture);
     if (b->offsets) (void)hipFree(b->offsets);
     if (b->order) (void)hipFree(b->order);
     if (b->counter) (void)hipFree(b->counter);
-    if (b->flag) (void)hipFree(b->flag);
+    csh::release_cell(b->cell);
     delete b;
     return CSH_OK;
 }

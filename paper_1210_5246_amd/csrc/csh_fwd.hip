@@ -55,7 +55,7 @@ __device__ __forceinline__ void close_step(const StepArgs<T>& p, int lane, doubl
 {
     smax = wave_max(smax);
     if (lane == 0) slot_add(p.slots[p.s_out], blockIdx.x, smax);
-    if (__any(bad) && lane == 0) atomicOr(p.flag, 1);
+    if (__any(bad) && lane == 0) raise_flag(p.flag);
 }
 
 // One-dimensional grids: a lane per cell, 60 cells per wavefront (two halo
@@ -313,7 +313,7 @@ __global__ __launch_bounds__(256) void init_kernel(const T* __restrict__ W, T* _
         bad = !physical(w);
         store_cons(U, (size_t)n, (size_t)c, to_cons(w));
     }
-    if (__any(bad) && (threadIdx.x & 63) == 0) atomicOr(flag, 1);
+    if (__any(bad) && (threadIdx.x & 63) == 0) raise_flag(flag);
 }
 
 template <typename T>
@@ -348,7 +348,7 @@ __global__ __launch_bounds__(256) void maxspeed_kernel(const T* __restrict__ U, 
     __shared__ double red[4];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     if (lane == 0) red[wv] = s;
-    if (__any(bad) && lane == 0) atomicOr(flag, 1);
+    if (__any(bad) && lane == 0) raise_flag(flag);
     __syncthreads();
     if (threadIdx.x == 0) slot_add(*slot, blockIdx.x, fmax(fmax(red[0], red[1]), fmax(red[2], red[3])));
 }
@@ -374,6 +374,26 @@ __global__ void reset_kernel(Slot* slots, int nslots, double t0)
 hipError_t launch_reset(Slot* slots, int nslots, double t0, hipStream_t s)
 {
     reset_kernel<<<1, 64, 0, s>>>(slots, nslots, t0);
+    return hipGetLastError();
+}
+
+__global__ void publish_kernel(const Slot* slot, HostCell* cell)
+{
+    const double s = slot_rate(*slot);
+    if (threadIdx.x == 0) cell->rate = s;
+}
+
+hipError_t launch_publish(const Slot* slot, HostCell* cell, hipStream_t s)
+{
+    publish_kernel<<<1, 64, 0, s>>>(slot, cell);
+    return hipGetLastError();
+}
+
+__global__ void clear_flag_kernel(int* flag) { *flag = 0; }
+
+hipError_t launch_clear_flag(int* flag, hipStream_t s)
+{
+    clear_flag_kernel<<<1, 1, 0, s>>>(flag);
     return hipGetLastError();
 }
 

@@ -27,15 +27,26 @@ struct Slot {
     } part[kRateParts];
 };
 
-// The rate of a host copy of a slot: the maximum over its parts.
-inline double slot_rate_host(const Slot& sl)
+// What a handle's kernels tell the host, in pinned memory the kernels write
+// directly: the host reads it after a stream synchronisation, with no copy (two
+// small copies to pageable memory had cost ~25 us of a 47 us host-stepped step
+// at 251 x 187).  The flag is written only when a non-physical state is met.
+struct alignas(64) HostCell {
+    double rate;  // written by launch_publish
+    int flag;     // 1 once a non-physical state was seen
+};
+
+// A cell for one handle (null if out of memory), flag 0, and its return once
+// the handle's stream is idle.  Thread-safe; pages of 64 cells, each freed with
+// its last cell, but for one page kept for the next handle (a pinned allocation
+// takes ~0.3 ms, more than the rest of making a handle).
+HostCell* acquire_cell();
+void release_cell(HostCell* cell);
+
+// Sets the flag (any lane, any number of times).
+__device__ __forceinline__ void raise_flag(int* flag)
 {
-    double s = 0.0;
-    for (int k = 0; k < kRateParts; ++k) {
-        const double v = __builtin_bit_cast(double, sl.part[k].bits);
-        s = v > s ? v : s;
-    }
-    return s;
+    __hip_atomic_store(flag, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // Clears a slot's rate: threads 0 .. kRateParts - 1 of one workgroup.
@@ -72,7 +83,7 @@ struct StepArgs {
     double* dt_log;          // if set, receives the timestep used
     const double* dt_in;     // if set (and dev_dt == 0), the timestep is read from here
     double vc2, rc2, x0, y0; // external flat-rotation-curve potential (vc2 == 0: none)
-    int* flag;               // set to 1 if an output cell is not physical
+    int* flag;               // raised if an output cell is not physical
     const T* Ubase;          // two-stage schemes: state the stage update starts from (null: U)
 };
 
@@ -88,6 +99,10 @@ hipError_t launch_maxspeed(const T* U, int nx, int ny, double dx, double dy, Slo
                            hipStream_t s);
 
 hipError_t launch_reset(Slot* slots, int nslots, double t0, hipStream_t s);
+
+// In stream order: the slot's rate to the host's cell; the flag cleared.
+hipError_t launch_publish(const Slot* slot, HostCell* cell, hipStream_t s);
+hipError_t launch_clear_flag(int* flag, hipStream_t s);
 
 // Kurganov-Tadmor stage on a 1-D grid: first (half step into the stage
 // buffer, records dt in slots[s_in].dt) or final (full step from Ubase with

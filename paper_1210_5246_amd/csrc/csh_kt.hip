@@ -85,7 +85,7 @@ __global__ __launch_bounds__(64 * kWaves) void kt_kernel(StepArgs<T> p)
     if (FINAL) {
         smax = wave_max(smax);
         if (lane == 0) slot_add(p.slots[p.s_out], blockIdx.x, smax);
-        if (__any(bad) && lane == 0) atomicOr(p.flag, 1);
+        if (__any(bad) && lane == 0) raise_flag(p.flag);
     }
 }
 
@@ -282,7 +282,7 @@ __global__ __launch_bounds__(64 * kWaves) void kt_fused_kernel(StepArgs<T> p)
 
     smax = wave_max(smax);
     if (lane == 0) slot_add(p.slots[p.s_out], blockIdx.x, smax);
-    if (__any(bad) && lane == 0) atomicOr(p.flag, 1);
+    if (__any(bad) && lane == 0) raise_flag(p.flag);
 }
 
 template <typename T>

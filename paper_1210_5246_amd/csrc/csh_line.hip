@@ -127,7 +127,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) void line_run_kernel(LineArgs<T> p)
         p.slots[p.s_out].t = t;
         p.slots[p.s_out].part[0].bits = (unsigned long long)__double_as_longlong(s);
     }
-    if (__any(bad) && lane == 0) atomicOr(p.flag, 1);
+    if (__any(bad) && lane == 0) raise_flag(p.flag);
 }
 
 }  // namespace

@@ -55,3 +55,49 @@ def test_hot_cell_3d():
         assert abs(g.max_signal_speed() - s) <= 1e-13 * s, cell
         g.step(0.0)
         assert abs(g.last_signal_speed() - s) <= 1e-13 * s, cell
+
+
+def test_many_handles_keep_their_own_rate_and_flag():
+    """More handles than a page of host cells holds, some freed in between."""
+    W = torch.from_numpy(_uniform(4, 70)).cuda()
+    grids = []
+    for k in range(150):
+        Wk = W.clone()
+        Wk[1, 2, 3] = 2.0 + k
+        grids.append((k, csh.Grid(Wk, 1.0 / 70, 0.25, (0, 0))))
+        if k % 3 == 2:
+            grids.pop(0)
+    U = grids[5][1].U.clone()
+    U[0, 1, 1] = -1.0
+    grids[5][1].step(1e-5, U)
+    s0 = None
+    for n, (k, g) in enumerate(grids):
+        if n == 5:
+            with pytest.raises(csh.NonPhysicalState):
+                g.last_signal_speed()
+            continue
+        s = g.max_signal_speed()
+        s0 = s - 70.0 * k if s0 is None else s0
+        assert abs(s - (s0 + 70.0 * k)) <= 1e-12 * s, k
+
+
+@pytest.mark.parametrize("nx,ny", [(40, 30), (1200, 700)])
+def test_log_buffer_and_replay(nx, ny):
+    """A run repeated with other log buffers and lengths gives the same state and log
+    (recorded steps on the small grid, plain launches on the large one)."""
+    Wd = torch.from_numpy(_uniform(ny, nx)).cuda()
+    Wd[1] += 0.1 * torch.sin(torch.arange(nx, device="cuda") * 0.1)
+    g = csh.Grid(Wd, 1.0 / nx, 1.0 / ny, (0, 0))
+    first = None
+    for n in (7, 7, 3, 7, 12, 7):
+        U = g.set_state(Wd)
+        log = torch.full((n + 2,), -1.0, dtype=torch.float64, device="cuda")
+        g.run_cfl(n, 0.8, dt_log=log)
+        torch.cuda.synchronize()
+        assert (log[:n] > 0).all() and (log[n:] == -1.0).all()
+        if n == 7:
+            if first is None:
+                first = (U.clone(), log.clone())
+            assert torch.equal(U, first[0]) and torch.equal(log, first[1])
+        else:
+            assert torch.equal(log[:3], first[1][:3])
