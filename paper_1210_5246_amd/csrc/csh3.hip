@@ -226,31 +226,25 @@ __global__ __launch_bounds__(256) void sweep3_kernel(SArgs q)
                     chi = 1.0 + k2 * fmin(uk + ak, 0.0);
                     clo = 1.0 - k2 * fmax(uk - ak, 0.0);
                 };
-                V10 base = W0, dz, dy, dx;  // half slopes
+                V10 base, dz, dy, dx;  // half slopes
                 {
                     const Eig<0> e = eig<0>(W0, ir);
                     a3[0] = e.a;
                     dx = half_slope<0>(W0, ir, e, shift<-1>(W0), shift<+1>(W0));
-                    const V10 Ad = jac<0>(W0, ir, dx);
-#pragma unroll
-                    for (int m = 0; m < NV; ++m) base.v[m] -= kx2 * Ad.v[m];
+                    base = sub_jac<0>(W0, kx2, W0, ir, dx);
                 }
                 {
                     const Eig<1> e = eig<1>(W0, ir);
                     a3[1] = e.a;
                     dy = half_slope<1>(W0, ir, e, get10(R, ys, col), get10(R, ys + 2, col));
-                    const V10 Ad = jac<1>(W0, ir, dy);
-#pragma unroll
-                    for (int m = 0; m < NV; ++m) base.v[m] -= ky2 * Ad.v[m];
+                    base = sub_jac<1>(base, ky2, W0, ir, dy);
                 }
                 const V10 Wp = prim(Cz);
                 {
                     const Eig<2> e = eig<2>(W0, ir);
                     a3[2] = e.a;
                     dz = half_slope<2>(W0, ir, e, Wm, Wp);
-                    const V10 Ad = jac<2>(W0, ir, dz);
-#pragma unroll
-                    for (int m = 0; m < NV; ++m) base.v[m] -= kz2 * Ad.v[m];
+                    base = sub_jac<2>(base, kz2, W0, ir, dz);
                 }
                 V10 ylo;
                 {
@@ -278,9 +272,7 @@ __global__ __launch_bounds__(256) void sweep3_kernel(SArgs q)
                             for (int m = 0; m < NV; ++m) Un.v[m] = acc.v[m] - cz * Gz.v[m];
                             if (own) {
                                 store32(q.b, ((unsigned)(r - 1) * ny + j) * nx + c, Un);
-                                const V10 wn = to_prim(Un, rcp(Un.v[0]));
-                                smax = fmax(smax, signal_rate(wn, ih));
-                                bad |= !physical(wn);
+                                smax = fmax(smax, checked_rate(to_prim(Un, rcp(Un.v[0])), ih, bad));
                             }
                         }
                         if (r < z1) {

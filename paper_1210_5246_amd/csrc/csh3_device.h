@@ -66,27 +66,35 @@ CSH_HD V10 to_cons(const V10& w)
     return U;
 }
 
-// A d with A the primitive Jacobian along N
+// base - k A d with A the primitive Jacobian along N:
+//   A d = (u_n d_rho + rho d_un, u_n d_ui + d_Pin / rho,
+//          u_n d_Pij + P_ij d_un + P_in d_uj + P_jn d_ui),
+// k folded into the factors the components share.
 template <int N>
-CSH_HD V10 jac(const V10& w, double ir, const V10& d)
+CSH_HD V10 sub_jac(const V10& base, double k, const V10& w, double ir, const V10& d)
 {
+    constexpr int t1 = Axes<N>::t1, t2 = Axes<N>::t2;
+    constexpr int nn = P(N, N), n1 = P(N, t1), n2 = P(N, t2), s11 = P(t1, t1), s12 = P(t1, t2), s22 = P(t2, t2);
+    const double un = w.v[1 + N], ku = k * un, kir = k * ir;
+    const double dn = k * d.v[1 + N], d1 = k * d.v[1 + t1], d2 = k * d.v[1 + t2];
+    const double p1 = 2.0 * w.v[n1], p2 = 2.0 * w.v[n2];
     V10 o;
-    const double un = w.v[1 + N];
-    o.v[0] = un * d.v[0] + w.v[0] * d.v[1 + N];
-#pragma unroll
-    for (int i = 0; i < 3; ++i) o.v[1 + i] = un * d.v[1 + i] + ir * d.v[P(i, N)];
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-        for (int j = i; j < 3; ++j)
-            o.v[P(i, j)] = un * d.v[P(i, j)] + w.v[P(i, j)] * d.v[1 + N] + w.v[P(i, N)] * d.v[1 + j] +
-                           w.v[P(j, N)] * d.v[1 + i];
+    o.v[0] = base.v[0] - ku * d.v[0] - w.v[0] * dn;
+    o.v[1 + N] = base.v[1 + N] - un * dn - kir * d.v[nn];
+    o.v[1 + t1] = base.v[1 + t1] - un * d1 - kir * d.v[n1];
+    o.v[1 + t2] = base.v[1 + t2] - un * d2 - kir * d.v[n2];
+    o.v[nn] = base.v[nn] - ku * d.v[nn] - (3.0 * w.v[nn]) * dn;
+    o.v[n1] = base.v[n1] - ku * d.v[n1] - p1 * dn - w.v[nn] * d1;
+    o.v[n2] = base.v[n2] - ku * d.v[n2] - p2 * dn - w.v[nn] * d2;
+    o.v[s11] = base.v[s11] - ku * d.v[s11] - w.v[s11] * dn - p1 * d1;
+    o.v[s12] = base.v[s12] - ku * d.v[s12] - w.v[s12] * dn - w.v[n1] * d2 - w.v[n2] * d1;
+    o.v[s22] = base.v[s22] - ku * d.v[s22] - w.v[s22] * dn - p2 * d2;
     return o;
 }
 
 template <int N>
 struct Eig {
-    double a, c, h2c, ip, q1, q2;  // a = sqrt(3 Pnn / rho), c = sqrt(Pnn / rho), h2c = 1/(2c), ip = 1/Pnn
+    double a, ic, ip, q1, q2;  // a = sqrt(3 Pnn / rho), ic = sqrt(rho / Pnn) = 1/c, ip = 1/Pnn
 };
 
 template <int N>
@@ -97,9 +105,8 @@ CSH_HD Eig<N> eig(const V10& w, double ir)
     const double pnn = w.v[P(N, N)];
     const double t = pnn * ir;
     const double y = rsqrt(t);  // 1 / c
-    e.c = t * y;
-    e.a = 1.7320508075688772935 * e.c;
-    e.h2c = 0.5 * y;
+    e.a = 1.7320508075688772935 * (t * y);
+    e.ic = y;
     e.ip = y * y * ir;          // (rho / Pnn) / rho
     e.q1 = w.v[P(N, t1)] * e.ip;
     e.q2 = w.v[P(N, t2)] * e.ip;
@@ -123,18 +130,21 @@ CSH_HD double mc_half(double dl, double dr)
 //   u -+ c (t):      (dPnt - q_t dPnn) -+ rho c (q_t du_n - du_t)  (2 Pnn times)
 //   u (4 waves):     drho - rho dPnn / (3 Pnn) and the three transverse-stress
 //                    combinations, unscaled;
-// the back-projection divides the scales out.
+// the back-projection divides the scales out.  The coefficients come from 1/c
+// and 1/Pnn as in two dimensions: rho c = Pnn / c, c / Pnn = 1 / (rho c), and
+// with h = S / 2 the S terms of the density and the transverse stresses are
+// kr h and (P_tt' / Pnn + 2 q_t q_t') h / 3.
 template <int N>
 CSH_HD V10 half_slope(const V10& w, double ir, const Eig<N>& e, const V10& wm, const V10& wp)
 {
     constexpr int t1 = Axes<N>::t1, t2 = Axes<N>::t2;
     constexpr int nn = P(N, N), n1 = P(N, t1), n2 = P(N, t2), s11 = P(t1, t1), s12 = P(t1, t2), s22 = P(t2, t2);
-    const double rho = w.v[0];
-    const double ra = rho * e.a, rc = rho * e.c, rip = rho * e.ip;
-    const double kr = rip * (1.0 / 3.0);
-    const double k11 = (4.0 * e.q1 * e.q1 - w.v[s11] * e.ip) * (1.0 / 3.0);
-    const double k12 = (4.0 * e.q1 * e.q2 - w.v[s12] * e.ip) * (1.0 / 3.0);
-    const double k22 = (4.0 * e.q2 * e.q2 - w.v[s22] * e.ip) * (1.0 / 3.0);
+    const double rc = w.v[nn] * e.ic, ra = 1.7320508075688772935 * rc;
+    const double ip3 = e.ip * (1.0 / 3.0), kr = w.v[0] * ip3;
+    const double g11 = w.v[s11] * ip3, g12 = w.v[s12] * ip3, g22 = w.v[s22] * ip3;
+    const double r1 = w.v[n1] * ip3, r2 = w.v[n2] * ip3;
+    const double qq11 = e.q1 * r1, qq12 = e.q1 * r2, qq22 = e.q2 * r2;
+    const double k11 = 4.0 * qq11 - g11, k12 = 4.0 * qq12 - g12, k22 = 4.0 * qq22 - g22;
     const double q1x2 = e.q1 + e.q1, q2x2 = e.q2 + e.q2;
     auto project = [&](const V10& d, double (&al)[NV]) {
         const double dnn = d.v[nn], dun = d.v[1 + N];
@@ -167,40 +177,52 @@ CSH_HD V10 half_slope(const V10& w, double ir, const Eig<N>& e, const V10& wm, c
     const double S = m[0] + m[9], D = m[9] - m[0];
     const double S1 = m[1] + m[7], D1 = m[7] - m[1];
     const double S2 = m[2] + m[8], D2 = m[8] - m[2];
-    const double i6 = e.ip * (1.0 / 6.0), bu = e.a * i6, bc = e.h2c * ir;  // a / (6 Pnn), c / (2 Pnn)
-    const double pn1 = w.v[n1], pn2 = w.v[n2];
+    const double z = e.ic * ir, bu = 0.28867513459481288225 * z, bc = 0.5 * z;  // a / (6 Pnn), c / (2 Pnn)
+    const double h = 0.5 * S, h1 = 0.5 * S1, h2 = 0.5 * S2;
     V10 d;
-    d.v[0] = (rip * (1.0 / 6.0)) * S + m[3];
+    d.v[0] = kr * h + m[3];
     d.v[1 + N] = bu * D;
-    d.v[1 + t1] = (bu * e.q1) * D + bc * D1;
-    d.v[1 + t2] = (bu * e.q2) * D + bc * D2;
-    d.v[nn] = 0.5 * S;
-    d.v[n1] = 0.5 * (e.q1 * S + S1);
-    d.v[n2] = 0.5 * (e.q2 * S + S2);
-    d.v[s11] = ((w.v[s11] + q1x2 * pn1) * i6) * S + e.q1 * S1 + m[4];
-    d.v[s12] = ((w.v[s12] + pn1 * e.q2 + pn2 * e.q1) * i6) * S + 0.5 * (e.q2 * S1 + e.q1 * S2) + m[5];
-    d.v[s22] = ((w.v[s22] + q2x2 * pn2) * i6) * S + e.q2 * S2 + m[6];
+    d.v[1 + t1] = e.q1 * d.v[1 + N] + bc * D1;
+    d.v[1 + t2] = e.q2 * d.v[1 + N] + bc * D2;
+    d.v[nn] = h;
+    d.v[n1] = e.q1 * h + h1;
+    d.v[n2] = e.q2 * h + h2;
+    d.v[s11] = (2.0 * qq11 + g11) * h + (q1x2 * h1 + m[4]);
+    d.v[s12] = (2.0 * qq12 + g12) * h + (e.q2 * h1 + (e.q1 * h2 + m[5]));
+    d.v[s22] = (2.0 * qq22 + g22) * h + (q2x2 * h2 + m[6]);
     return d;
 }
 
-// F - s U along N, formed from the primitive state: with s' = u_n - s and
-// m = rho s', X_rho = m, X_i = m u_i + P_in, X_ij = u_j X_i + s' P_ij + P_nj u_i,
-// which for i = n is u_j X_n + P_nj (s' + u_n).
-template <int N>
-CSH_HD V10 moving_flux(const V10& w, double s)
+// One side of the HLL flux along N: w (F - s U), formed from the primitive state:
+// with s' = u_n - s and m = rho s', F - s U is X_rho = m, X_i = m u_i + P_in,
+// X_ij = u_j X_i + s' P_ij + P_nj u_i (for i = n: u_j X_n + P_nj (s' + u_n)), linear
+// in (s', P_in) at fixed velocities, so the weight scales those alone.  The
+// stresses accumulate onto `add` (the other side, of opposite weight).
+template <int N, bool ADD>
+CSH_HD V10 weighted_flux(const V10& w, double s, double weight, const V10& add)
 {
-    const double un = w.v[1 + N], sp = un - s, m = w.v[0] * sp, g = sp + un;
-    V10 X;
-    X.v[0] = m;
+    const double un = w.v[1 + N], sp = un - s, g = sp + un, ws = weight * sp, m = w.v[0] * ws;
+    double pn[3];
 #pragma unroll
-    for (int i = 0; i < 3; ++i) X.v[1 + i] = m * w.v[1 + i] + w.v[P(i, N)];
+    for (int i = 0; i < 3; ++i) pn[i] = weight * w.v[P(i, N)];
+    V10 X;
+    X.v[0] = ADD ? add.v[0] + m : m;
+    double xi[3];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        xi[i] = m * w.v[1 + i] + pn[i];
+        X.v[1 + i] = ADD ? add.v[1 + i] + xi[i] : xi[i];
+    }
 #pragma unroll
     for (int i = 0; i < 3; ++i)
 #pragma unroll
         for (int j = i; j < 3; ++j) {
-            if (i == N) X.v[P(i, j)] = w.v[1 + j] * X.v[1 + N] + w.v[P(N, j)] * g;
-            else if (j == N) X.v[P(i, j)] = w.v[1 + i] * X.v[1 + N] + w.v[P(N, i)] * g;
-            else X.v[P(i, j)] = w.v[1 + j] * X.v[1 + i] + sp * w.v[P(i, j)] + w.v[P(N, j)] * w.v[1 + i];
+            const double a = ADD ? add.v[P(i, j)] : 0.0;
+            if (i == N) X.v[P(i, j)] = ADD ? a + w.v[1 + j] * xi[N] + pn[j] * g : w.v[1 + j] * xi[N] + pn[j] * g;
+            else if (j == N) X.v[P(i, j)] = ADD ? a + w.v[1 + i] * xi[N] + pn[i] * g : w.v[1 + i] * xi[N] + pn[i] * g;
+            else
+                X.v[P(i, j)] = ADD ? a + w.v[1 + j] * xi[i] + ws * w.v[P(i, j)] + pn[j] * w.v[1 + i]
+                                   : w.v[1 + j] * xi[i] + ws * w.v[P(i, j)] + pn[j] * w.v[1 + i];
         }
     return X;
 }
@@ -211,17 +233,13 @@ CSH_HD V10 moving_flux(const V10& w, double s)
 template <int N>
 CSH_HD V10 hll(const V10& wl, const V10& wr)
 {
-    const double tl = 3.0 * wl.v[P(N, N)], tr = 3.0 * wr.v[P(N, N)];
-    const double al = tl * rsqrt(tl * wl.v[0]), ar = tr * rsqrt(tr * wr.v[0]);
-    const double sl = fmin(fmin(wl.v[1 + N] - al, wr.v[1 + N] - ar), 0.0);
-    const double sr = fmax(fmax(wl.v[1 + N] + al, wr.v[1 + N] + ar), 0.0);
+    constexpr double s3 = 1.7320508075688772935;
+    const double pl = wl.v[P(N, N)], pr = wr.v[P(N, N)];
+    const double cl = pl * rsqrt(pl * wl.v[0]), cr = pr * rsqrt(pr * wr.v[0]);
+    const double sl = fmin(fmin(wl.v[1 + N] - s3 * cl, wr.v[1 + N] - s3 * cr), 0.0);
+    const double sr = fmax(fmax(wl.v[1 + N] + s3 * cl, wr.v[1 + N] + s3 * cr), 0.0);
     const double inv = rcp(sr - sl);
-    const double a = sr * inv, b = sl * inv;
-    const V10 XL = moving_flux<N>(wl, sl), XR = moving_flux<N>(wr, sr);
-    V10 F;
-#pragma unroll
-    for (int m = 0; m < NV; ++m) F.v[m] = a * XL.v[m] - b * XR.v[m];
-    return F;
+    return weighted_flux<N, true>(wr, sr, -sl * inv, weighted_flux<N, false>(wl, sl, sr * inv, V10{}));
 }
 
 // CFL rate: sum over the axes of (|u_k| + sqrt(3 P_kk / rho)) / h_k
@@ -231,9 +249,22 @@ CSH_HD double signal_rate(const V10& w, const double ih[3])
     double s = 0.0;
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
-        const double t = 3.0 * w.v[P(k, k)] * ir;
-        s += (fabs(w.v[1 + k]) + t * rsqrt(t)) * ih[k];
+        const double c = sqrt_pos(w.v[P(k, k)] * ir);
+        s = s + fabs(w.v[1 + k]) * ih[k] + c * (1.7320508075688772935 * ih[k]);
     }
+    return s;
+}
+
+// CFL rate of a new state together with the test of physical(): a finite rate
+// means finite velocities and P_kk >= 0 with rho > 0 (each under a square root,
+// NaN at <= 0); an infinite or NaN P_ij, i != j, fails one of the minors.
+CSH_HD double checked_rate(const V10& w, const double ih[3], bool& bad)
+{
+    const double pxx = w.v[4], pxy = w.v[5], pxz = w.v[6], pyy = w.v[7], pyz = w.v[8], pzz = w.v[9];
+    const double m2 = pxx * pyy - pxy * pxy;
+    const double det = pxx * (pyy * pzz - pyz * pyz) - pxy * (pxy * pzz - pyz * pxz) + pxz * (pxy * pyz - pyy * pxz);
+    const double s = signal_rate(w, ih);
+    bad |= !((w.v[0] > 0.0) & (m2 > 0.0) & (det > 0.0) & __builtin_isfinite(s + w.v[0]));
     return s;
 }
 
@@ -245,7 +276,7 @@ CSH_HD bool physical(const V10& w)
     double sum = 0.0;
 #pragma unroll
     for (int m = 0; m < NV; ++m) sum += w.v[m];
-    return (w.v[0] > 0.0) & (pxx > 0.0) & (m2 > 0.0) & (det > 0.0) & isfinite(sum);
+    return (w.v[0] > 0.0) & (pxx > 0.0) & (m2 > 0.0) & (det > 0.0) & __builtin_isfinite(sum);
 }
 
 }  // namespace d3

@@ -103,9 +103,7 @@ __global__ __launch_bounds__(NT) void batch_kernel(BatchArgs a)
                 const Cons<double> Un = update(U0, cx, F, lane_shift<-1>(F));
                 if (lane >= 2 && lane < 2 + kStrip && c < n) {
                     store_cons(B, plane, (size_t)c, Un);
-                    const Prim<double> wn = to_prim(Un);
-                    smax = fmax(smax, signal_rate<double, false>(wn, idx, 0.0));
-                    bad |= !physical(wn);
+                    smax = fmax(smax, checked_rate<double, false>(Un, idx, 0.0, bad));
                 }
             }
             s = block_max<NT>(smax, red, (step + 1) & 1);  // its barrier also orders this step's stores before the next step's loads

@@ -174,6 +174,7 @@ CSH_HD Cons<T> flux_x(const Prim<T>& w, const Cons<T>& U)
 template <typename T>
 struct Eig {
     T a, c, h2a, h2c, ip, q;  // h2a = 1/(2a), h2c = 1/(2c), ip = 1/Pxx
+    T ic;                     // 1/c
 };
 
 template <typename T>
@@ -184,6 +185,7 @@ CSH_HD Eig<T> eig_x(const Prim<T>& w, T ir)
     const T y = rsqrt(t);                 // 1 / c
     e.c = t * y;
     e.a = T(1.7320508075688772935) * e.c;  // sqrt(3) c
+    e.ic = y;
     e.h2c = T(0.5) * y;
     e.h2a = T(0.28867513459481288225) * y;  // 1 / (2 sqrt(3) c)
     e.ip = y * y * ir;                      // 1 / Pxx = (rho / Pxx) / rho
@@ -279,13 +281,16 @@ CSH_HD T mc_half(T dl, T dr)
 // u -+ c pair, the slope is
 //   (rho S / (6 Pxx) + m_rho, a D / (6 Pxx), a q D / (6 Pxx) + c D' / (2 Pxx),
 //    S / 2, (q S + S') / 2, (Pyy + 2 Pxy q) S / (6 Pxx) + q S' + m_Pyy).
+// The coefficients come from 1/c and 1/Pxx: rho c = Pxx / c, c / Pxx = 1 / (rho c),
+// and with h = S / 2 the S terms are kr h and (Pyy / Pxx + 2 q^2) h / 3, whose
+// factors the projection needs too (92 operations against 100 with each
+// coefficient formed from its own quotient).
 template <typename T>
 CSH_HD Prim<T> half_slope(const Prim<T>& w, T ir, const Eig<T>& e, const Prim<T>& dl, const Prim<T>& dr)
 {
-    const T ra = w.r * e.a, rc = w.r * e.c, q2 = e.q + e.q;
-    const T rip = w.r * e.ip;  // rho / Pxx
-    const T kr = rip * T(1.0 / 3.0);
-    const T k4 = (T(4) * e.q * e.q - w.pyy * e.ip) * T(1.0 / 3.0);
+    const T rc = w.pxx * e.ic, ra = T(1.7320508075688772935) * rc, q2 = e.q + e.q;
+    const T ip3 = e.ip * T(1.0 / 3.0), kr = w.r * ip3, g3 = w.pyy * ip3, qq3 = e.q * (w.pxy * ip3);
+    const T k4 = T(4) * qq3 - g3;
     auto project = [&](const Prim<T>& d, T (&al)[6]) {
         al[0] = d.pxx - ra * d.u;
         al[5] = d.pxx + ra * d.u;
@@ -300,16 +305,15 @@ CSH_HD Prim<T> half_slope(const Prim<T>& w, T ir, const Eig<T>& e, const Prim<T>
     project(dr, r);
 #pragma unroll
     for (int k = 0; k < 6; ++k) m[k] = mc_half(l[k], r[k]);
-    const T i6 = e.ip * T(1.0 / 6.0);
     const T S = m[0] + m[5], D = m[5] - m[0], S2 = m[1] + m[4], D2 = m[4] - m[1];
-    const T bu = e.a * i6;
+    const T z = e.ic * ir;  // 1 / (rho c) = c / Pxx
     Prim<T> d;
-    d.r = (rip * T(1.0 / 6.0)) * S + m[2];
-    d.u = bu * D;
-    d.v = (bu * e.q) * D + (e.h2c * ir) * D2;  // c / (2 Pxx) = 1 / (2 c rho)
     d.pxx = T(0.5) * S;
-    d.pxy = T(0.5) * (e.q * S + S2);
-    d.pyy = ((w.pyy + q2 * w.pxy) * i6) * S + e.q * S2 + m[3];
+    d.r = kr * d.pxx + m[2];
+    d.u = (T(0.28867513459481288225) * z) * D;  // a / (6 Pxx)
+    d.v = e.q * d.u + (T(0.5) * z) * D2;
+    d.pxy = e.q * d.pxx + T(0.5) * S2;
+    d.pyy = (T(2) * qq3 + g3) * d.pxx + (e.q * S2 + m[3]);
     return d;
 }
 
@@ -329,6 +333,22 @@ CSH_HD Prim<T> jac_x(const Prim<T>& w, T ir, const Prim<T>& d)
     return o;
 }
 
+// base - k A d with A the primitive x Jacobian (rows of A d: u d_rho + rho d_u,
+// u d_u + d_Pxx/rho, u d_v + d_Pxy/rho, u d_Pxx + 3 Pxx d_u,
+// u d_Pxy + 2 Pxy d_u + Pxx d_v, u d_Pyy + Pyy d_u + 2 Pxy d_v), k folded into
+// the factors the components share (20 operations against 22).
+template <typename T>
+CSH_HD Prim<T> sub_jac_x(const Prim<T>& base, T k, const Prim<T>& w, T ir, const Prim<T>& d)
+{
+    const T ku = k * w.u, kir = k * ir, du = k * d.u, dv = k * d.v, p2 = T(2) * w.pxy, p3 = T(3) * w.pxx;
+    return {base.r - ku * d.r - w.r * du,
+            base.u - w.u * du - kir * d.pxx,
+            base.v - w.u * dv - kir * d.pxy,
+            base.pxx - ku * d.pxx - p3 * du,
+            base.pxy - ku * d.pxy - p2 * du - w.pxx * dv,
+            base.pyy - ku * d.pyy - w.pyy * du - p2 * dv};
+}
+
 template <typename T>
 CSH_HD Prim<T> axpy(T a, const Prim<T>& x, const Prim<T>& y)
 {
@@ -342,6 +362,7 @@ struct Face {
     Prim<T> w;
     Cons<T> U;
     T a;  // normal fast speed sqrt(3 Pnn / rho)
+    T c;  // sqrt(Pnn / rho)
 };
 
 // x-face state from a primitive state (normal direction x)
@@ -351,8 +372,8 @@ CSH_HD Face<T> make_face_x(const Prim<T>& w)
     Face<T> f;
     f.w = w;
     f.U = to_cons(w);
-    const T t = T(3) * w.pxx;
-    f.a = t * rsqrt(t * w.r);  // sqrt(3 Pxx / rho)
+    f.c = w.pxx * rsqrt(w.pxx * w.r);
+    f.a = T(1.7320508075688772935) * f.c;
     return f;
 }
 
@@ -375,17 +396,31 @@ CSH_HD Cons<T> moving_flux_x(const Prim<T>& w, T s)
 // HLL flux in x (Davis speed estimates), branch-free form: with the outer
 // speeds clamped, S_L' = min(S_L, 0) and S_R' = max(S_R, 0), the three-case
 // flux is (S_R' F_L - S_L' F_R + S_L' S_R' (U_R - U_L)) / (S_R' - S_L'), which
-// is (S_R' X_L - S_L' X_R) / (S_R' - S_L') with X_K = F_K - S_K' U_K.
+// is (S_R' X_L - S_L' X_R) / (S_R' - S_L') with X_K = F_K - S_K' U_K.  Every
+// component of X is linear in (s', Pxx, Pxy) at fixed velocities (moving_flux_x),
+// so the two weights scale those three instead of the six components, and the
+// right side accumulates onto the left.
 template <typename T>
 CSH_HD Cons<T> hll_x(const Face<T>& L, const Face<T>& R)
 {
-    const T sl = fmin(fmin(L.w.u - L.a, R.w.u - R.a), T(0));
-    const T sr = fmax(fmax(L.w.u + L.a, R.w.u + R.a), T(0));
+    constexpr T s3 = T(1.7320508075688772935);
+    const T sl = fmin(fmin(L.w.u - s3 * L.c, R.w.u - s3 * R.c), T(0));
+    const T sr = fmax(fmax(L.w.u + s3 * L.c, R.w.u + s3 * R.c), T(0));
     const T inv = rcp(sr - sl);
     const T a = sr * inv, b = sl * inv;
-    const Cons<T> XL = moving_flux_x(L.w, sl), XR = moving_flux_x(R.w, sr);
-    return {a * XL.r - b * XR.r,     a * XL.mx - b * XR.mx,   a * XL.my - b * XR.my,
-            a * XL.exx - b * XR.exx, a * XL.exy - b * XR.exy, a * XL.eyy - b * XR.eyy};
+    const T pl = L.w.u - sl, pr = R.w.u - sr;              // s' of each side
+    const T al = a * pl, ar = b * pr;                      // weighted
+    const T gl = pl + L.w.u, gr = pr + R.w.u;
+    const T pxl = a * L.w.pxx, pxr = b * R.w.pxx, qxl = a * L.w.pxy, qxr = b * R.w.pxy;
+    const T ml = L.w.r * al, mr = R.w.r * ar;
+    const T xl = ml * L.w.u + pxl, xr = mr * R.w.u + pxr;  // X_mx
+    const T yl = ml * L.w.v + qxl, yr = mr * R.w.v + qxr;  // X_my
+    return {ml - mr,
+            xl - xr,
+            yl - yr,
+            L.w.u * xl + pxl * gl - R.w.u * xr - pxr * gr,
+            L.w.v * xl + qxl * gl - R.w.v * xr - qxr * gr,
+            L.w.v * (yl + qxl) + L.w.pyy * al - R.w.v * (yr + qxr) - R.w.pyy * ar};
 }
 
 // HLLC flux in x for the moment equations: outer speeds as for HLL, one
@@ -437,7 +472,7 @@ CSH_HD Cons<T> riemann_x(const Face<T>& L, const Face<T>& R)
 template <typename T>
 CSH_HD Face<T> swap(const Face<T>& f)
 {
-    return {swap(f.w), swap(f.U), f.a};
+    return {swap(f.w), swap(f.U), f.a, f.c};
 }
 
 // The four time-centred face states of a cell (primitive, axes not exchanged)
@@ -462,7 +497,7 @@ CSH_HD Faces<T> face_states_d(const Prim<T>& W0, T ir, const Prim<T>& dlx, const
     const T kx2 = kx + kx;
     const Eig<T> ex = eig_x(W0, ir);
     const Prim<T> hx = half_slope(W0, ir, ex, dlx, drx);
-    Prim<T> base = axpy(-kx2, jac_x(W0, ir, hx), W0);
+    Prim<T> base = sub_jac_x(W0, kx2, W0, ir, hx);
     Faces<T> f;
     const T chix = T(1) + kx2 * fmin(W0.u + ex.a, T(0));
     const T clox = T(1) - kx2 * fmax(W0.u - ex.a, T(0));
@@ -471,7 +506,7 @@ CSH_HD Faces<T> face_states_d(const Prim<T>& W0, T ir, const Prim<T>& dlx, const
         const Prim<T> W0s = swap(W0);
         const Eig<T> ey = eig_x(W0s, ir);
         const Prim<T> hys = half_slope(W0s, ir, ey, swap(dly), swap(dry));
-        base = axpy(-ky2, swap(jac_x(W0s, ir, hys)), base);
+        base = swap(sub_jac_x(swap(base), ky2, W0s, ir, hys));
         const Prim<T> hy = swap(hys);
         const T chiy = T(1) + ky2 * fmin(W0.v + ey.a, T(0));
         const T cloy = T(1) - ky2 * fmax(W0.v - ey.a, T(0));
@@ -546,28 +581,25 @@ __device__ __forceinline__ void kick(Cons<T>& U, const P& p, double dt, int i, i
 template <typename T, bool TWOD>
 CSH_HD double signal_rate(const Prim<T>& w, double idx, double idy)
 {
-    const T ir = rcp(w.r);
-    const T tx = T(3) * w.pxx * ir;
-    T s = (fabs(w.u) + sqrt_pos(tx)) * T(idx);
-    if (TWOD) {
-        const T ty = T(3) * w.pyy * ir;
-        s += (fabs(w.v) + sqrt_pos(ty)) * T(idy);
-    }
+    const T ir = rcp(w.r), s3 = T(1.7320508075688772935);
+    T s = fabs(w.u) * T(idx) + sqrt_pos(w.pxx * ir) * (s3 * T(idx));
+    if (TWOD) s = s + fabs(w.v) * T(idy) + sqrt_pos(w.pyy * ir) * (s3 * T(idy));
     return double(s);
 }
 
-// CFL rate of a new 2-D state together with the test of physical() (rho > 0,
+// CFL rate of a new state together with the test of physical() (rho > 0,
 // positive-definite stress, everything finite), sharing the work: a NaN or an
-// infinity in u, v, Pxx or Pyy makes the rate NaN or infinite, one in Pxy
-// fails det > 0, one in rho fails rho > 0 or makes rate + rho infinite.
-template <typename T>
+// infinity in u, v, Pxx or Pyy makes the rate NaN or infinite (1-D: v and Pyy
+// are added to it for the test), one in Pxy fails det > 0, one in rho fails
+// rho > 0 or makes rate + rho infinite.  With rho > 0 a Pxx <= 0 makes its
+// square root NaN, and so the rate; with Pxx > 0, det > 0 needs Pyy > 0.
+template <typename T, bool TWOD = true>
 CSH_HD double checked_rate(const Cons<T>& U, double idx, double idy, bool& bad)
 {
     const Prim<T> w = to_prim(U);
-    const double s = signal_rate<T, true>(w, idx, idy);
-    const bool ok = (w.r > T(0)) & (w.pxx > T(0)) & (w.pyy > T(0)) & (w.pxx * w.pyy - w.pxy * w.pxy > T(0)) &
-                    isfinite(s + double(w.r));
-    bad |= !ok;
+    const double s = signal_rate<T, TWOD>(w, idx, idy);
+    const double t = TWOD ? s + double(w.r) : s + double(w.r + w.v + w.pyy);
+    bad |= !((w.r > T(0)) & (w.pxx * w.pyy - w.pxy * w.pxy > T(0)) & __builtin_isfinite(t));
     return s;
 }
 
@@ -578,7 +610,7 @@ CSH_HD bool physical(const Prim<T>& w)
     // every test evaluated (no short-circuit: no lane-divergent branches)
     const bool pd = (w.r > T(0)) & (w.pxx > T(0)) & (w.pyy > T(0)) & (w.pxx * w.pyy - w.pxy * w.pxy > T(0));
     // a NaN or infinity in any component makes the sum NaN or infinite
-    return pd & isfinite(w.r + w.u + w.v + w.pxx + w.pxy + w.pyy);
+    return pd & __builtin_isfinite(w.r + w.u + w.v + w.pxx + w.pxy + w.pyy);
 }
 
 // ---- wavefront primitives --------------------------------------------------------------------

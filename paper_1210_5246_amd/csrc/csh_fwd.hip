@@ -84,9 +84,7 @@ __global__ __launch_bounds__(64 * kWaves) void sweep1d_kernel(StepArgs<T> p)
     kick(Un, p, dt, c, 0, false);
     if (lane >= 2 && lane < 2 + kStrip && c < p.nx) {
         store_cons(p.Unew, (size_t)p.nx, (size_t)c, Un);
-        const Prim<T> wn = to_prim(Un);
-        smax = signal_rate<T, false>(wn, 1.0 / p.dx, 0.0);
-        bad = !physical(wn);
+        smax = checked_rate<T, false>(Un, 1.0 / p.dx, 0.0, bad);
     }
     close_step(p, lane, smax, bad);
 }

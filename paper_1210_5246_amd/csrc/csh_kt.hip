@@ -77,9 +77,7 @@ __global__ __launch_bounds__(64 * kWaves) void kt_kernel(StepArgs<T> p)
     if (own) {
         out.store((unsigned)c, Un);
         if (FINAL) {
-            const Prim<T> wn = to_prim(Un);
-            smax = fmax(smax, signal_rate<T, false>(wn, 1.0 / p.dx, 0.0));
-            bad |= !physical(wn);
+            smax = fmax(smax, checked_rate<T, false>(Un, 1.0 / p.dx, 0.0, bad));
         }
     }
     if (FINAL) {

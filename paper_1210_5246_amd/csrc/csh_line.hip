@@ -71,9 +71,10 @@ __global__ __launch_bounds__(64 * kMaxWaves) void line_run_kernel(LineArgs<T> p)
                 state[b][3][gc], state[b][4][gc], state[b][5][gc]};
     };
     auto rate = [&](const Cons<T>& U) -> double {
-        const Prim<T> W = to_prim(U);
-        bad |= own && !physical(W);
-        return own ? signal_rate<T, false>(W, idx, 0.0) : 0.0;
+        bool b = false;
+        const double s = checked_rate<T, false>(U, idx, 0.0, b);
+        bad |= own && b;
+        return own ? s : 0.0;
     };
 
     Cons<T> U = load_cons(p.U0, (size_t)p.nx, (size_t)gc);
