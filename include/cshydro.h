@@ -79,8 +79,8 @@ const char *csh_last_error(void);
  * hipStream_t (NULL: the null stream).  Synchronises; returns
  * CSH_ERR_NONPHYSICAL (handle still created) if some cell of W has rho <= 0,
  * Pxx <= 0, Pyy <= 0, Pxx Pyy - Pxy^2 <= 0 or a non-finite value.
- * The handle owns small device scalars (and, once csh_adjoint_step is used,
- * the adjoint workspace); free it with csh_destroy.
+ * The handle owns small device scalars (and, once csh_adjoint_step is used on a
+ * 1-D grid, its workspace); free it with csh_destroy.
  */
 int csh_init_state(csh_grid **h, int nx, int ny, double dx, double dy, int bc_x, int bc_y,
                    int dtype, const void *W, void *U, void *stream);
@@ -249,9 +249,9 @@ int csh_run_dts(csh_grid *h, int nsteps, const double *dts, void *U, void *U_wor
  * HLL branches fixed at U; at ties the subgradient of the first minimal
  * argument), external kick included.  U, lam_next: device, read only;
  * lam: device output; all [6][ny][nx] of the handle's dtype (CSH_F64 only).
- * Does not touch the handle's CFL state.  The first call allocates a workspace
- * of 66 (nx + 2)(ny + 2) + 6 (nx + 4)(ny + 2) doubles (1-D: 66 (nx + 2) +
- * 6 (nx + 4)) that the handle keeps until csh_destroy.  Asynchronous.
+ * Does not touch the handle's CFL state.  On a 1-D grid the first call allocates
+ * a workspace of 66 (nx + 2) + 6 (nx + 4) doubles that the handle keeps until
+ * csh_destroy; a 2-D grid needs none.  Asynchronous.
  */
 int csh_adjoint_step(csh_grid *h, double dt, const void *U, const void *lam_next, void *lam);
 

@@ -19,8 +19,6 @@ namespace csh {
 
 using P = Prim<double>;
 using C = Cons<double>;
-using A6 = Char<double>;
-using E = Eig<double>;
 
 CSH_HD void acc(P& a, const P& b)
 {
@@ -34,148 +32,21 @@ CSH_HD double dot(const P& a, const P& b)
 CSH_HD P zero_p() { return {0, 0, 0, 0, 0, 0}; }
 CSH_HD C zero_c() { return {0, 0, 0, 0, 0, 0}; }
 
-// eig_x(w, ir): c = sqrt(pxx ir), a = sqrt3 c, h2c = 0.5/c, h2a = k/c, ip = 1/pxx, q = pxy ip
-CSH_HD void eig_vjp(const P& w, double ir, const E& e, const E& eb, P& wb, double& irb)
+// The limiter m = mc_half(dl, dr) with the weights of its two arguments in the
+// branch it takes: 1/4 and 1/4 centred, 1 and 0 or 0 and 1 one-sided, 0 and 0
+// off.  m is one of (dl + dr) / 4, dl, dr and 0 itself, so comparing it tells the
+// branch (the centred one first); written without branches, so the adjoints stay
+// in registers.
+struct McVjp {
+    double m, wl, wr;
+};
+CSH_HD McVjp mc_half_vjp(double dl, double dr)
 {
-    double cb = eb.c;
-    double ipb = eb.ip;
-    // q = pxy * ip
-    wb.pxy += e.ip * eb.q;
-    ipb += w.pxy * eb.q;
-    // ip = 1 / pxx
-    wb.pxx += -e.ip * e.ip * ipb;
-    // h2a = k / c ; h2c = 0.5 / c ; a = sqrt3 c  (1 / c = 2 h2c)
-    const double ic = 2.0 * e.h2c;
-    cb += -e.h2a * ic * eb.h2a;
-    cb += -e.h2c * ic * eb.h2c;
-    cb += 1.7320508075688772935 * eb.a;
-    // c = sqrt(pxx ir)
-    const double tb = cb * e.h2c;
-    wb.pxx += ir * tb;
-    irb += w.pxx * tb;
-}
-
-// project(w, e, d) -> alpha
-CSH_HD void project_vjp(const P& w, const E& e, const P& d, const A6& ab, P& wb, E& eb, P& db)
-{
-    const double t1b = ab.a1 + ab.a6, t2b = ab.a6 - ab.a1;
-    const double hb = ab.a2 - ab.a5, sb = ab.a2 + ab.a5;
-    // a3 = d.r - w.r d.pxx ip / 3
-    db.r += ab.a3;
-    constexpr double third = 1.0 / 3.0, sixth = 1.0 / 6.0;
-    wb.r += -d.pxx * e.ip * third * ab.a3;
-    db.pxx += -w.r * e.ip * third * ab.a3;
-    eb.ip += -w.r * d.pxx * third * ab.a3;
-    // a4 = d.pyy - 2 q d.pxy + (4 q^2 - pyy ip) d.pxx / 3
-    db.pyy += ab.a4;
-    eb.q += (-2.0 * d.pxy + 8.0 * e.q * d.pxx * third) * ab.a4;
-    db.pxy += -2.0 * e.q * ab.a4;
-    wb.pyy += -e.ip * d.pxx * third * ab.a4;
-    eb.ip += -w.pyy * d.pxx * third * ab.a4;
-    db.pxx += (4.0 * e.q * e.q - w.pyy * e.ip) * third * ab.a4;
-    // h = (q d.u - d.v) h2c
-    const double X = e.q * d.u - d.v;
-    const double Xb = e.h2c * hb;
-    eb.h2c += X * hb;
-    eb.q += d.u * Xb;
-    db.u += e.q * Xb;
-    db.v -= Xb;
-    // s = (d.pxy - q d.pxx) (ip / 2)
-    const double Y = d.pxy - e.q * d.pxx;
-    const double Yb = 0.5 * e.ip * sb;
-    eb.ip += 0.5 * Y * sb;
-    db.pxy += Yb;
-    eb.q -= d.pxx * Yb;
-    db.pxx -= e.q * Yb;
-    // t2 = d.u h2a
-    db.u += e.h2a * t2b;
-    eb.h2a += d.u * t2b;
-    // t1 = d.pxx ip / 6
-    db.pxx += e.ip * sixth * t1b;
-    eb.ip += d.pxx * sixth * t1b;
-}
-
-// backproject(w, e, alpha) -> d
-CSH_HD void backproject_vjp(const P& w, const E& e, const A6& al, const P& db, P& wb, E& eb, A6& ab)
-{
-    const double S = al.a1 + al.a6, D = al.a6 - al.a1;
-    const double S25 = al.a2 + al.a5, D25 = al.a5 - al.a2;
-    const double Sb = w.r * db.r + 3.0 * w.pxx * db.pxx + 3.0 * w.pxy * db.pxy + (w.pyy + 2.0 * w.pxy * e.q) * db.pyy;
-    const double Db = e.a * db.u + e.a * e.q * db.v;
-    const double S25b = w.pxx * db.pxy + 2.0 * w.pxy * db.pyy;
-    const double D25b = e.c * db.v;
-    ab.a3 += db.r;
-    ab.a4 += db.pyy;
-    wb.r += S * db.r;
-    eb.a += D * db.u + e.q * D * db.v;
-    eb.q += e.a * D * db.v + 2.0 * w.pxy * S * db.pyy;
-    eb.c += D25 * db.v;
-    wb.pxx += 3.0 * S * db.pxx + S25 * db.pxy;
-    wb.pxy += 3.0 * S * db.pxy + 2.0 * e.q * S * db.pyy + 2.0 * S25 * db.pyy;
-    wb.pyy += S * db.pyy;
-    ab.a1 += Sb - Db;
-    ab.a6 += Sb + Db;
-    ab.a2 += S25b - D25b;
-    ab.a5 += S25b + D25b;
-}
-
-// MC: m = sgn(dc) min(2|dl|, |dc|, 2|dr|) if dl and dr are nonzero with one
-// sign, else 0 (the forward form tests the signs, not the product).  The
-// branch taken sets the weights of the two inputs (0.5 / 0.5 centred, 2 / 0
-// or 0 / 2 one-sided, 0 / 0 off); written without branches so the two
-// adjoints stay in registers.
-CSH_HD void mc_vjp(double dl, double dr, double mb, double& dlb, double& drb)
-{
-    const bool on = dl != 0.0 && dr != 0.0 && (dl < 0.0) == (dr < 0.0);
-    const double adc = fabs(0.5 * (dl + dr)), al2 = 2.0 * fabs(dl), ar2 = 2.0 * fabs(dr);
-    const bool cen = adc <= al2 && adc <= ar2;  // centred difference
-    const bool left = al2 <= ar2;               // else 2 dl (same sign as dc), else 2 dr
-    const double wl = on ? (cen ? 0.5 : (left ? 2.0 : 0.0)) : 0.0;
-    const double wr = on ? (cen ? 0.5 : (left ? 0.0 : 2.0)) : 0.0;
-    dlb += wl * mb;
-    drb += wr * mb;
-}
-
-// limited_slope(w, e, dl, dr) -> dm
-CSH_HD void limited_slope_vjp(const P& w, const E& e, const P& dl, const P& dr, const P& dmb, P& wb, E& eb,
-                              P& dlb, P& drb)
-{
-    const A6 l = project(w, e, dl), r = project(w, e, dr);
-    A6 m;
-    m.a1 = mc(l.a1, r.a1);
-    m.a2 = mc(l.a2, r.a2);
-    m.a3 = mc(l.a3, r.a3);
-    m.a4 = mc(l.a4, r.a4);
-    m.a5 = mc(l.a5, r.a5);
-    m.a6 = mc(l.a6, r.a6);
-    A6 mb{0, 0, 0, 0, 0, 0};
-    backproject_vjp(w, e, m, dmb, wb, eb, mb);
-    A6 lb{0, 0, 0, 0, 0, 0}, rb{0, 0, 0, 0, 0, 0};
-    mc_vjp(l.a1, r.a1, mb.a1, lb.a1, rb.a1);
-    mc_vjp(l.a2, r.a2, mb.a2, lb.a2, rb.a2);
-    mc_vjp(l.a3, r.a3, mb.a3, lb.a3, rb.a3);
-    mc_vjp(l.a4, r.a4, mb.a4, lb.a4, rb.a4);
-    mc_vjp(l.a5, r.a5, mb.a5, lb.a5, rb.a5);
-    mc_vjp(l.a6, r.a6, mb.a6, lb.a6, rb.a6);
-    project_vjp(w, e, dl, lb, wb, eb, dlb);
-    project_vjp(w, e, dr, rb, wb, eb, drb);
-}
-
-// jac_x(w, ir, d) -> o
-CSH_HD void jac_vjp(const P& w, double ir, const P& d, const P& ob, P& wb, double& irb, P& db)
-{
-    wb.u += d.r * ob.r + d.u * ob.u + d.v * ob.v + d.pxx * ob.pxx + d.pxy * ob.pxy + d.pyy * ob.pyy;
-    wb.r += d.u * ob.r;
-    irb += d.pxx * ob.u + d.pxy * ob.v;
-    wb.pxx += 3.0 * d.u * ob.pxx + d.v * ob.pxy;
-    wb.pxy += 2.0 * d.u * ob.pxy + 2.0 * d.v * ob.pyy;
-    wb.pyy += d.u * ob.pyy;
-    db.r += w.u * ob.r;
-    db.u += w.r * ob.r + w.u * ob.u + 3.0 * w.pxx * ob.pxx + 2.0 * w.pxy * ob.pxy + w.pyy * ob.pyy;
-    db.v += w.u * ob.v + w.pxx * ob.pxy + 2.0 * w.pxy * ob.pyy;
-    db.pxx += ir * ob.u + w.u * ob.pxx;
-    db.pxy += ir * ob.v + w.u * ob.pxy;
-    db.pyy += w.u * ob.pyy;
+    const double q = 0.25 * (dl + dr);
+    const double A = fmin(fmin(dl, dr), q), B = fmax(fmax(dl, dr), q);
+    const double m = fmax(A, fmin(B, 0.0));
+    const bool on = m != 0.0, cen = on & (m == q), left = on & !cen & (m == dl), right = on & !cen & !left;
+    return {m, cen ? 0.25 : (left ? 1.0 : 0.0), cen ? 0.25 : (right ? 1.0 : 0.0)};
 }
 
 CSH_HD P swapb(const P& a) { return swap(a); }  // the adjoint of a permutation that is its own inverse
@@ -200,94 +71,134 @@ CSH_HD P base_adjoint(const Faces<double>& fb, bool twod)
     return baseb;
 }
 
+// The reverse pass of one direction of face_states (normal direction x): from
+// the adjoints of the high and low face states (fhi, flo) and of their common
+// centre (baseb), with the slope's differences dl, dr and k2 = dt / dx; adds to
+// wb and irb what goes to the cell's state and 1/rho other than through the
+// differences and the identity part of the centre, and returns the adjoints of
+// dl and dr.  The forward part is half_slope's scaled form, whose coefficients
+// are differentiated as they are formed there.
+CSH_HD void direction_vjp(const P& w, double ir, const P& dl, const P& dr, double k2, const P& fhi, const P& flo,
+                          const P& baseb, P& wb, double& irb, P& dlb, P& drb)
+{
+    constexpr double s3 = 1.7320508075688772935, ka = 0.28867513459481288225, third = 1.0 / 3.0;
+    // ---- forward: half_slope and the tracing coefficients ----
+    const double t = w.pxx * ir, y = rsqrt(t), c = t * y, a = s3 * c;  // y = 1 / c
+    const double ip = y * y * ir, q = w.pxy * ip, rc = w.pxx * y, ra = s3 * rc, q2 = q + q;
+    const double ip3 = ip * third, kr = w.r * ip3, g3 = w.pyy * ip3, p3 = w.pxy * ip3, qq3 = q * p3;
+    const double k4 = 4.0 * qq3 - g3, cp = 2.0 * qq3 + g3;
+    const double z = y * ir, bu = ka * z, hz = 0.5 * z;
+    auto project = [&](const P& d, double (&al)[6]) {
+        const double s = d.pxy - q * d.pxx, h = q * d.u - d.v;
+        al[0] = d.pxx - ra * d.u;
+        al[5] = d.pxx + ra * d.u;
+        al[1] = s + rc * h;
+        al[4] = s - rc * h;
+        al[2] = d.r - kr * d.pxx;
+        al[3] = d.pyy - q2 * d.pxy + k4 * d.pxx;
+    };
+    double l[6], r[6], m[6], wl[6], wr[6];
+    project(dl, l);
+    project(dr, r);
+    for (int n = 0; n < 6; ++n) {
+        const McVjp v = mc_half_vjp(l[n], r[n]);
+        m[n] = v.m;
+        wl[n] = v.wl;
+        wr[n] = v.wr;
+    }
+    const double S = m[0] + m[5], D = m[5] - m[0], S2 = m[1] + m[4], D2 = m[4] - m[1];
+    P h;
+    h.pxx = 0.5 * S;
+    h.r = kr * h.pxx + m[2];
+    h.u = bu * D;
+    h.v = q * h.u + hz * D2;
+    h.pxy = q * h.pxx + 0.5 * S2;
+    h.pyy = cp * h.pxx + (q * S2 + m[3]);
+    const double up = w.u + a, um = w.u - a;
+    const double chi = 1.0 + k2 * fmin(up, 0.0), clo = 1.0 - k2 * fmax(um, 0.0);
+    // ---- reverse: hi = base + chi h, lo = base - clo h, base -= k2 A h ----
+    const double chib = up < 0.0 ? k2 * dot(h, fhi) : 0.0, clob = um > 0.0 ? k2 * dot(h, flo) : 0.0;
+    wb.u += chib + clob;
+    double ab = chib - clob;
+    const P o = scale(-k2, baseb);
+    wb.u += dot(h, o);
+    wb.r += h.u * o.r;
+    wb.pxx += 3.0 * h.u * o.pxx + h.v * o.pxy;
+    wb.pxy += 2.0 * (h.u * o.pxy + h.v * o.pyy);
+    wb.pyy += h.u * o.pyy;
+    irb += h.pxx * o.u + h.pxy * o.v;
+    P hb = axpy(w.u, o, axpy(chi, fhi, scale(-clo, flo)));
+    hb.u += w.r * o.r + 3.0 * w.pxx * o.pxx + 2.0 * w.pxy * o.pxy + w.pyy * o.pyy;
+    hb.v += w.pxx * o.pxy + 2.0 * w.pxy * o.pyy;
+    hb.pxx += ir * o.u;
+    hb.pxy += ir * o.v;
+    // the back-projection
+    const double hub = hb.u + q * hb.v;
+    const double hpb = hb.pxx + cp * hb.pyy + q * hb.pxy + kr * hb.r;
+    double qb = S2 * hb.pyy + h.pxx * hb.pxy + h.u * hb.v;
+    double krb = h.pxx * hb.r;
+    const double cpb = h.pxx * hb.pyy;
+    const double Sb = 0.5 * hpb, Db = bu * hub, S2b = q * hb.pyy + 0.5 * hb.pxy, D2b = hz * hb.v;
+    const double zb = ka * (D * hub) + 0.5 * (D2 * hb.v);
+    const double mb[6] = {Sb - Db, S2b - D2b, hb.r, hb.pyy, S2b + D2b, Sb + Db};
+    // the limiter and the two projections
+    double rcb = 0.0, rab = 0.0, k4b = 0.0;
+    auto project_vjp = [&](const P& d, const double (&wk)[6], P& db) {
+        const double a0 = wk[0] * mb[0], a1 = wk[1] * mb[1], a2 = wk[2] * mb[2], a3 = wk[3] * mb[3];
+        const double a4 = wk[4] * mb[4], a5 = wk[5] * mb[5];
+        const double sb = a1 + a4, eb = a1 - a4, fb = a5 - a0, hh = rc * eb;
+        rcb += (q * d.u - d.v) * eb;
+        rab += d.u * fb;
+        qb += d.u * hh - d.pxx * sb - 2.0 * d.pxy * a3;
+        krb -= d.pxx * a2;
+        k4b += d.pxx * a3;
+        db = {a2, q * hh + ra * fb, -hh, a0 + a5 - q * sb - kr * a2 + k4 * a3, sb - q2 * a3, a3};
+    };
+    project_vjp(dl, wl, dlb);
+    project_vjp(dr, wr, drb);
+    // the coefficients
+    const double qq3b = 2.0 * cpb + 4.0 * k4b, g3b = cpb - k4b, p3b = q * qq3b;
+    qb += p3 * qq3b;
+    wb.pyy += ip3 * g3b;
+    wb.r += ip3 * krb;
+    wb.pxy += ip3 * p3b + ip * qb;
+    const double ipb = third * (w.pxy * p3b + w.pyy * g3b + w.r * krb) + w.pxy * qb;
+    rcb += s3 * rab;
+    const double yb = w.pxx * rcb + ir * zb - (s3 * ab) * (c * c);  // a = s3 / y
+    const double tb = -0.5 * (y * (y * y)) * yb;                    // y = t^(-1/2)
+    wb.pxx += y * rcb - ip * ip * ipb + ir * tb;
+    irb += y * zb + w.pxx * tb;
+}
+
 CSH_HD void face_states_vjp_y(const P& W0, const P& Wm, const P& Wp, double ky, const Faces<double>& fb, P& W0b,
                               P& Wmb, P& Wpb)
 {
-    // ---- forward recompute ----
     const double ir = rcp(W0.r);
-    const P W0s = swap(W0);
-    const E ey = eig_x(W0s, ir);
-    const P dlys = swap(sub(W0, Wm)), drys = swap(sub(Wp, W0));
-    const P dyms = limited_slope(W0s, ey, dlys, drys);
-    const P dym = swap(dyms);
-    const double chiy = 0.5 + ky * fmin(W0.v + ey.a, 0.0);
-    const double cloy = 0.5 - ky * fmax(W0.v - ey.a, 0.0);
-    // ---- reverse ----
-    const P baseb = base_adjoint(fb, true);
+    P wb = zero_p(), dlb, drb;
     double irb = 0.0;
-    E eyb{0, 0, 0, 0, 0, 0};
-    P dymb = zero_p();
-    acc(dymb, scale(chiy, fb.yhi));
-    acc(dymb, scale(-cloy, fb.ylo));
-    const double chiyb = dot(dym, fb.yhi), cloyb = -dot(dym, fb.ylo);
-    // chiy = 1/2 + ky min(v + ay, 0) ; cloy = 1/2 - ky max(v - ay, 0)
-    if (W0.v + ey.a < 0.0) {
-        W0b.v += ky * chiyb;
-        eyb.a += ky * chiyb;
-    }
-    if (W0.v - ey.a > 0.0) {
-        W0b.v -= ky * cloyb;
-        eyb.a += ky * cloyb;
-    }
-    // base -= ky swap(jac_x(W0s, ir, dyms))
-    P W0sb = zero_p(), dymsb = swapb(dymb);
-    jac_vjp(W0s, ir, dyms, scale(-ky, swapb(baseb)), W0sb, irb, dymsb);
-    // dyms = limited_slope(W0s, ey, dlys, drys)
-    P dlysb = zero_p(), drysb = zero_p();
-    limited_slope_vjp(W0s, ey, dlys, drys, dymsb, W0sb, eyb, dlysb, drysb);
-    eig_vjp(W0s, ir, ey, eyb, W0sb, irb);
-    acc(W0b, swapb(W0sb));
-    // dlys = swap(W0 - Wm), drys = swap(Wp - W0)
-    const P dlyb = swapb(dlysb), dryb = swapb(drysb);
-    acc(W0b, dlyb);
-    acc(Wmb, scale(-1.0, dlyb));
-    acc(Wpb, dryb);
-    acc(W0b, scale(-1.0, dryb));
-    // ir = 1 / W0.r
-    W0b.r += -ir * ir * irb;
+    direction_vjp(swap(W0), ir, swap(sub(W0, Wm)), swap(sub(Wp, W0)), ky + ky, swapb(fb.yhi), swapb(fb.ylo),
+                  swapb(base_adjoint(fb, true)), wb, irb, dlb, drb);
+    // dl = W0 - Wm, dr = Wp - W0, ir = 1 / W0.r
+    wb.r -= ir * ir * irb;
+    acc(W0b, swapb(sub(axpy(1.0, wb, dlb), drb)));
+    acc(Wmb, swapb(scale(-1.0, dlb)));
+    acc(Wpb, swapb(drb));
 }
 
 template <bool TWOD>
 CSH_HD void face_states_vjp_x(const P& W0, const P& Wl, const P& Wr, double kx, const Faces<double>& fb, P& W0b,
                               P& Wlb, P& Wrb)
 {
-    // ---- forward recompute ----
     const double ir = rcp(W0.r);
-    const E ex = eig_x(W0, ir);
-    const P dlx = sub(W0, Wl), drx = sub(Wr, W0);
-    const P dxm = limited_slope(W0, ex, dlx, drx);
-    const double chix = 0.5 + kx * fmin(W0.u + ex.a, 0.0);
-    const double clox = 0.5 - kx * fmax(W0.u - ex.a, 0.0);
-    // ---- reverse ----
     const P baseb = base_adjoint(fb, TWOD);
+    P wb = baseb, dlb, drb;  // base = W0 + ...
     double irb = 0.0;
-    E exb{0, 0, 0, 0, 0, 0};
-    P dxmb = zero_p();
-    acc(dxmb, scale(chix, fb.xhi));
-    acc(dxmb, scale(-clox, fb.xlo));
-    const double chixb = dot(dxm, fb.xhi), cloxb = -dot(dxm, fb.xlo);
-    // chix = 1/2 + kx min(u + ax, 0) ; clox = 1/2 - kx max(u - ax, 0)
-    if (W0.u + ex.a < 0.0) {
-        W0b.u += kx * chixb;
-        exb.a += kx * chixb;
-    }
-    if (W0.u - ex.a > 0.0) {
-        W0b.u -= kx * cloxb;
-        exb.a += kx * cloxb;
-    }
-    // base = W0 - kx jac_x(W0, ir, dxm) (- the transverse term, in the y part)
-    acc(W0b, baseb);
-    jac_vjp(W0, ir, dxm, scale(-kx, baseb), W0b, irb, dxmb);
-    P dlxb = zero_p(), drxb = zero_p();
-    limited_slope_vjp(W0, ex, dlx, drx, dxmb, W0b, exb, dlxb, drxb);
-    eig_vjp(W0, ir, ex, exb, W0b, irb);
-    // dlx = W0 - Wl, drx = Wr - W0
-    acc(W0b, dlxb);
-    acc(Wlb, scale(-1.0, dlxb));
-    acc(Wrb, drxb);
-    acc(W0b, scale(-1.0, drxb));
-    // ir = 1 / W0.r
-    W0b.r += -ir * ir * irb;
+    direction_vjp(W0, ir, sub(W0, Wl), sub(Wr, W0), kx + kx, fb.xhi, fb.xlo, baseb, wb, irb, dlb, drb);
+    // dl = W0 - Wl, dr = Wr - W0, ir = 1 / W0.r
+    wb.r -= ir * ir * irb;
+    acc(W0b, sub(axpy(1.0, wb, dlb), drb));
+    acc(Wlb, scale(-1.0, dlb));
+    acc(Wrb, drb);
 }
 
 // reverse of face_states<double, TWOD>(W0, ir, Wl, Wr, Wm, Wp, kx, ky)
@@ -329,79 +240,60 @@ CSH_HD void to_prim_vjp(const C& U, const P& wb, C& Ub)
     Ub.r += wb.r - ir * ir * irb;
 }
 
-// flux_x(w, U)
-CSH_HD void flux_vjp(const P& w, const C& U, const C& Fb, P& wb, C& Ub)
+// w (F - s U) of one side (moving_flux_x), reversed: from the adjoint Xb of
+// F - s U, adds to the state's adjoint and returns that of s.  X1, X2: its
+// momentum components.
+CSH_HD double moving_flux_vjp(const P& w, double s, double X1, double X2, const C& Xb, P& wb)
 {
-    Ub.mx += Fb.r + w.u * Fb.mx;
-    Ub.my += w.u * Fb.my;
-    Ub.exx += w.u * Fb.exx;
-    Ub.exy += w.u * Fb.exy;
-    Ub.eyy += w.u * Fb.eyy;
-    wb.u += U.mx * Fb.mx + U.my * Fb.my + (U.exx + 2.0 * w.pxx) * Fb.exx + (U.exy + w.pxy) * Fb.exy + U.eyy * Fb.eyy;
-    wb.v += w.pxx * Fb.exy + 2.0 * w.pxy * Fb.eyy;
-    wb.pxx += Fb.mx + 2.0 * w.u * Fb.exx + w.v * Fb.exy;
-    wb.pxy += Fb.my + w.u * Fb.exy + 2.0 * w.v * Fb.eyy;
+    const double sp = w.u - s, m = w.r * sp, g = sp + w.u;
+    const double X2b = Xb.my + w.v * Xb.eyy, X1b = Xb.mx + w.u * Xb.exx + w.v * Xb.exy;
+    const double gb = w.pxx * Xb.exx + w.pxy * Xb.exy;
+    const double mb = Xb.r + w.v * X2b + w.u * X1b;
+    const double spb = w.pyy * Xb.eyy + w.r * mb + gb;
+    wb.r += sp * mb;
+    wb.u += X1 * Xb.exx + m * X1b + gb + spb;
+    wb.v += (X2 + w.pxy) * Xb.eyy + X1 * Xb.exy + m * X2b;
+    wb.pxx += g * Xb.exx + X1b;
+    wb.pxy += w.v * Xb.eyy + g * Xb.exy + X2b;
+    wb.pyy += sp * Xb.eyy;
+    return -spb;
 }
 
-// hll_x(make_face_x(wl), make_face_x(wr)): adjoints of the two primitive face states
+// hll_x(make_face_x(wl), make_face_x(wr)): adjoints of the two primitive face
+// states.  F = a X_L - b X_R with a = S_R' / (S_R' - S_L'), b = S_L' / (S_R' - S_L')
+// (a - b = 1) and X_K = F_K - S_K' U_K, whose dependence on S_K' is reversed with
+// the rest of X_K.
 CSH_HD void hll_vjp(const P& wl, const P& wr, const C& Fb, P& wlb, P& wrb)
 {
-    const Face<double> L = make_face_x(wl), R = make_face_x(wr);
-    const double A1 = L.w.u - L.a, B1 = R.w.u - R.a;
-    const double C1 = L.w.u + L.a, D1 = R.w.u + R.a;
+    constexpr double s3 = 1.7320508075688772935;
+    const double yl = rsqrt(wl.pxx * wl.r), yr = rsqrt(wr.pxx * wr.r);
+    const double cl = wl.pxx * yl, cr = wr.pxx * yr;  // sqrt(Pxx / rho)
+    const double A1 = wl.u - s3 * cl, B1 = wr.u - s3 * cr;
+    const double C1 = wl.u + s3 * cl, D1 = wr.u + s3 * cr;
     const double sl = fmin(fmin(A1, B1), 0.0);
     const double sr = fmax(fmax(C1, D1), 0.0);
     const double inv = rcp(sr - sl);
-    const double slr = sl * sr;
-    const C FL = flux_x(L.w, L.U), FR = flux_x(R.w, R.U);
-    const double fl[6] = {FL.r, FL.mx, FL.my, FL.exx, FL.exy, FL.eyy};
-    const double fr[6] = {FR.r, FR.mx, FR.my, FR.exx, FR.exy, FR.eyy};
-    const double ul[6] = {L.U.r, L.U.mx, L.U.my, L.U.exx, L.U.exy, L.U.eyy};
-    const double ur[6] = {R.U.r, R.U.mx, R.U.my, R.U.exx, R.U.exy, R.U.eyy};
-    const double fb[6] = {Fb.r, Fb.mx, Fb.my, Fb.exx, Fb.exy, Fb.eyy};
-    double flb[6], frb[6], ulb[6], urb[6];
-    double srb = 0, slb = 0, invb = 0, slrb = 0;
-    for (int k = 0; k < 6; ++k) {
-        const double du = ur[k] - ul[k];
-        const double N = sr * fl[k] - sl * fr[k] + slr * du;
-        const double Nb = inv * fb[k];
-        invb += N * fb[k];
-        flb[k] = sr * Nb;
-        frb[k] = -sl * Nb;
-        srb += fl[k] * Nb;
-        slb -= fr[k] * Nb;
-        slrb += du * Nb;
-        urb[k] = slr * Nb;
-        ulb[k] = -slr * Nb;
-    }
-    srb += sl * slrb;
-    slb += sr * slrb;
-    // inv = 1 / (sr - sl)
-    srb += -inv * inv * invb;
-    slb += inv * inv * invb;
-    double ulwb = 0, urwb = 0, alb = 0, arb = 0;  // adjoints of u_L, u_R, a_L, a_R
-    if (fmin(A1, B1) < 0.0) {
-        if (A1 <= B1) { ulwb += slb; alb -= slb; }
-        else { urwb += slb; arb -= slb; }
-    }
-    if (fmax(C1, D1) > 0.0) {
-        if (C1 >= D1) { ulwb += srb; alb += srb; }
-        else { urwb += srb; arb += srb; }
-    }
-    C ULb = {ulb[0], ulb[1], ulb[2], ulb[3], ulb[4], ulb[5]};
-    C URb = {urb[0], urb[1], urb[2], urb[3], urb[4], urb[5]};
-    flux_vjp(L.w, L.U, C{flb[0], flb[1], flb[2], flb[3], flb[4], flb[5]}, wlb, ULb);
-    flux_vjp(R.w, R.U, C{frb[0], frb[1], frb[2], frb[3], frb[4], frb[5]}, wrb, URb);
-    to_cons_vjp(L.w, ULb, wlb);
-    to_cons_vjp(R.w, URb, wrb);
-    wlb.u += ulwb;
-    wrb.u += urwb;
-    // a = sqrt(3 pxx / r): da/dpxx = a / (2 pxx), da/dr = -a / (2 r)
-    const double hl = 0.5 * L.a * alb, hr = 0.5 * R.a * arb;
-    wlb.pxx += hl * rcp(L.w.pxx);
-    wlb.r -= hl * rcp(L.w.r);
-    wrb.pxx += hr * rcp(R.w.pxx);
-    wrb.r -= hr * rcp(R.w.r);
+    const double a = sr * inv, b = sl * inv;
+    const C XL = moving_flux_x(wl, sl), XR = moving_flux_x(wr, sr);
+    const double t = inv * ((XL.r - XR.r) * Fb.r + (XL.mx - XR.mx) * Fb.mx + (XL.my - XR.my) * Fb.my +
+                            (XL.exx - XR.exx) * Fb.exx + (XL.exy - XR.exy) * Fb.exy + (XL.eyy - XR.eyy) * Fb.eyy);
+    auto weighted = [&](double k) -> C {
+        return {k * Fb.r, k * Fb.mx, k * Fb.my, k * Fb.exx, k * Fb.exy, k * Fb.eyy};
+    };
+    const double slb = a * t + moving_flux_vjp(wl, sl, XL.mx, XL.my, weighted(a), wlb);
+    const double srb = moving_flux_vjp(wr, sr, XR.mx, XR.my, weighted(-b), wrb) - b * t;
+    // the speed estimates: the first argument on ties, no slope where clipped at 0
+    const bool ll = A1 <= B1, rl = C1 >= D1;
+    const double sbl = fmin(A1, B1) < 0.0 ? slb : 0.0, sbr = fmax(C1, D1) > 0.0 ? srb : 0.0;
+    const double l1 = ll ? sbl : 0.0, l2 = ll ? 0.0 : sbl, r1 = rl ? sbr : 0.0, r2 = rl ? 0.0 : sbr;
+    wlb.u += l1 + r1;
+    wrb.u += l2 + r2;
+    // a = s3 sqrt(Pxx / rho): da/dPxx = s3 y / 2, da/drho = -s3 y (Pxx / rho) / 2
+    const double hl = 0.5 * s3 * yl * (r1 - l1), hr = 0.5 * s3 * yr * (r2 - l2);
+    wlb.pxx += hl;
+    wlb.r -= hl * (cl * cl);
+    wrb.pxx += hr;
+    wrb.r -= hr * (cr * cr);
 }
 
 // the fixed-field kick is affine in U with a constant Jacobian K; lam' = K^T lam
@@ -656,13 +548,13 @@ CSH_HD void gather_cell(const AdjArgs& a, int i, int j)
     store_cons(a.lam0, plane, c, out);
 }
 
-// ---- the tiled two-kernel reverse pass (2-D) ----------------------------------------------
+// ---- the reverse pass by tiles, on the CPU (2-D) -----------------------------------------
 //
-// Kernel A (faces and fluxes) and kernel B (face states and gather) replace the
-// five one-thread-per-cell stages on 2-D grids.  Each works on a tile held in
-// LDS, so the face states, the shares of the face-state reverse pass and
-// their sums never travel through device memory; only the face-state
-// adjoints (FSb) pass from A to B.
+// The phases of a tiled reverse pass in two kernels, A (faces and fluxes) and B
+// (face states and gather), as bodies a CPU loop over tiles, phases and threads
+// runs (tests/host).  The device runs both phases in one kernel with the same
+// treatment of the boundaries; these bodies show it equal to the per-cell
+// reference above.  Only the face-state adjoints (FSb) pass from A to B.
 //
 // Periodic axes are treated as a pure wrap: a virtual cell outside [0, n) is
 // the wrapped cell (its state, its lam' and its face-state adjoints), every
@@ -673,10 +565,6 @@ CSH_HD void gather_cell(const AdjArgs& a, int i, int j)
 // same forward step; they differ from the five-stage pass only in the order
 // of the sums.
 //
-// The bodies below are the per-thread work of each phase between the
-// workgroup barriers, written so a CPU loop over tiles, phases and threads
-// runs them unchanged (tests/host).
-
 // kernel A: a tile of kA_TX x kA_TY extended cells, one thread per cell
 constexpr int kA_TX = 32, kA_TY = 8, kA_THREADS = kA_TX * kA_TY;
 constexpr int kA_WX = kA_TX + 3, kA_WY = kA_TY + 3;  // states: cells [X0 - 1, X0 + TX + 2)
@@ -685,10 +573,7 @@ constexpr int kA_NW = kA_WX * kA_WY, kA_NF = kA_FX * kA_FY;
 constexpr int kA_LDS = 6 * kA_NW + 12 * kA_NF;       // doubles of LDS: states, low x and y face states
 
 // kernel B: a tile of kB_W x kB_H virtual cells (four rows per wavefront),
-// the outputs its inner (kB_W - 2) x (kB_H - 2) cells.  16 x 16 rather than
-// 64 x 8: 77 KB of LDS, so two workgroups share a CU and one's barriers
-// overlap the other's work, and at 512^2 1369 tiles fill three rounds of 512
-// (64 x 8: 774 tiles, four rounds of one workgroup per CU)
+// the outputs its inner (kB_W - 2) x (kB_H - 2) cells
 constexpr int kB_W = 16, kB_H = 16, kB_THREADS = kB_W * kB_H;
 constexpr int kB_OX = kB_W - 2, kB_OY = kB_H - 2;
 enum { SH_LEFT = 0, SH_RIGHT = 1, SH_DOWN = 2, SH_UP = 3, SH_TOT = 4 };

@@ -1,10 +1,7 @@
 // Adjoint of one sweep at frozen timestep (FP64): lam^n = (d S_dt / d U^n)^T lam^{n+1}.
 //
-// 2-D grids: two LDS-tiled kernels (adjoint_tileA_kernel, adjoint_tileB_kernel,
-// the phase bodies in csh_adjoint.h): A recomputes the face states of a tile
-// and takes the flux adjoints of its faces through HLL into the face-state
-// adjoints, B takes those through the face-state reverse pass, sums the shares
-// that land on each cell and folds the ghost positions of outflow axes.
+// 2-D grids: one kernel, adjoint_fused_kernel: blocks of cells whose face states,
+// flux adjoints, face-state reverse pass and sums stay in registers and LDS.
 //
 // 1-D grids: the forward step reads primitive states at "extended" cells
 // e = i, i in [-1, nx], whose values come from the mapped cells map(e) of the
@@ -24,12 +21,11 @@
 //   4. gather: per interior cell, sum the XS of the padded positions that the
 //              boundary mapping sends to this cell, chain through W(U) and add
 //              lam' itself.
-// (The 2-D grids ran this scheme with a y part as five kernels before the
-// tiled pass replaced it; its per-cell bodies remain the reference the tiled
-// pass is tested against on the CPU.)
+// (The per-cell bodies of that scheme with a y part, csh_adjoint.h, are the CPU
+// reference the 2-D kernel is tested against.)
 //
-// The kernels take their workgroup numbers XCD-aware (xcd_block), so tiles or
-// rows that share halo cells sit in the same L2.
+// The kernels take their workgroup numbers XCD-aware (xcd_block), so blocks that
+// share halo cells sit in the same L2.
 #include <string>
 
 #include "csh_adjoint.h"
@@ -83,48 +79,145 @@ __global__ __launch_bounds__(256) void adjoint_xsum_kernel(AdjArgs a)
         store_p(a.XS, (size_t)(a.nx + 4) * a.ey, 0, xs_index(a, i, j), sum);
 }
 
-// The tiled reverse pass of 2-D grids.  Kernel A: a workgroup per tile of
-// 32 x 8 extended cells (one thread each): the states of the tile and a
-// ring into LDS, the face states of each cell (its high ones kept in
-// registers, its low ones shared through LDS, plus the low ones of the column
-// to the right and the row above), then per cell the flux adjoints of its
-// high x and y faces through HLL into the face-state adjoints (FSb, device
-// memory).  47 KB of LDS: three workgroups per CU.
-__global__ __launch_bounds__(kA_THREADS) void adjoint_tileA_kernel(AdjArgs a, int tiles_x)
-{
-    __shared__ double L[kA_LDS];
-    const unsigned b = xcd_block(blockIdx.x, gridDim.x);
-    const int X0 = -1 + (int)(b % (unsigned)tiles_x) * kA_TX, Y0 = -1 + (int)(b / (unsigned)tiles_x) * kA_TY;
-    const int t = threadIdx.x;
-    tileA_states(a, X0, Y0, t, L);
-    __syncthreads();
-    P xhi, yhi;
-    tileA_faces(a, t, L, xhi, yhi);
-    __syncthreads();
-    tileA_fluxes(a, X0, Y0, t, L, xhi, yhi);
-}
+// The reverse pass of 2-D grids, one launch.  A workgroup holds a block of
+// BX x 16 cells (a thread each; a cell outside the grid is a virtual one: the
+// wrapped cell on a periodic axis, else the ghost cell, with lam' = 0) and outputs
+// its inner (BX - 4) x 12.  Per cell: the face states (states of the block and a
+// ring in LDS); the flux adjoints of its high x and y faces through HLL into the
+// adjoints of the face states on both sides; the face-state reverse pass; the sum
+// of what lands on each position, on outflow axes folded onto the boundary cells;
+// W(U) reverse and lam'.  x neighbours exchange by lane shifts (a shift that
+// crosses from one row of the block to the next lands on a cell whose value is not
+// used or is zero), y neighbours through LDS, where a slot read by one thread only
+// is overwritten by it: three barriers.
+//
+// Two launches with the face-state adjoints in between (192 B per cell written and
+// read with a ring) moved 663 B per cell-step, 49 us at 512^2 whatever their
+// instruction count; here the state, lam^{n+1} and lam^n are all that is moved
+// (131 x 93 16.9 -> 8.5 us, 300 x 200 21.1 -> 12.8, 512^2 51.2 -> 38.8).  Bound by
+// FP64 issue (~1900 instructions a thread, 256 threads for 144 outputs) and by the
+// latency of its phases at two wavefronts per SIMD (256 registers).
+constexpr int kF_Y = 16, kF_OY = kF_Y - 4;
 
-// Kernel B: a workgroup per tile of 16 x 16 virtual cells (four rows per
-// wavefront), outputs its inner 14 x 14: the states of the tile and a ring
-// into LDS, per cell the face-state reverse pass from its FSb (its own share
-// in registers, the four to its neighbours in LDS), then per position
-// everything that lands on it, then per output the folded sum through W(U)
-// plus lam'.  77 KB of LDS, two workgroups per CU.
-__global__ __launch_bounds__(kB_THREADS) void adjoint_tileB_kernel(AdjArgs a, int tiles_x)
+template <int BX>
+__global__ __launch_bounds__(BX * kF_Y, 2) void adjoint_fused_kernel(AdjArgs a, int tiles_x)
 {
-    __shared__ double L[kB_LDS];
+    constexpr int SX = BX + 2, OX = BX - 4;
+    __shared__ double S[(kF_Y + 2) * 6 * SX];  // states; later the totals of the positions
+    __shared__ double Y[kF_Y * 6 * BX];        // low y-face states, their adjoints, the shares downwards
+    __shared__ double M[kF_Y * 6 * BX];        // lam', then the shares upwards
     const unsigned b = xcd_block(blockIdx.x, gridDim.x);
-    const int X0 = (int)(b % (unsigned)tiles_x) * kB_OX, Y0 = (int)(b / (unsigned)tiles_x) * kB_OY;
-    const int t = threadIdx.x;
-    tileB_states(a, X0, Y0, t, L);
+    const int X0 = (int)(b % (unsigned)tiles_x) * OX, Y0 = (int)(b / (unsigned)tiles_x) * kF_OY;
+    const int lx = threadIdx.x % BX, ly = threadIdx.x / BX;
+    const int i = X0 - 2 + lx, j = Y0 - 2 + ly;
+    // cells past [-3, n + 2] feed nothing that is used
+    auto map = [](int k, int n, int bc) { return map_index(min(max(k, -3), n + 2), n, bc); };
+    const int gi = map(i, a.nx, a.bcx), gj = map(j, a.ny, a.bcy);
+    const Planes<double> Up(a.U, (size_t)a.nx * a.ny), Lp(a.lam1, (size_t)a.nx * a.ny);
+    const unsigned cell = (unsigned)(gj * a.nx + gi);
+
+    // rows and columns of S are those of the block, shifted by one
+    auto put_state = [&](int col, int row, const P& v) { lds_put(S + (row + 1) * 6 * SX, SX, 0, col + 1, v); };
+    auto state = [&](int col, int row) -> P { return lds_get(S + (row + 1) * 6 * SX, SX, 0, col + 1); };
+    double* const Yrow = Y + ly * 6 * BX;
+    double* const Mrow = M + ly * 6 * BX;
+
+    // lam' of the mapped cell: the kick's transpose applied to lam^{n+1}
+    auto lam_prime_here = [&]() -> C {
+        C l = Lp.load(cell);
+        if (a.vc2 != 0.0) {
+            const double x = a.x0 + (gi + 0.5) * a.dx, y = a.y0 + (gj + 0.5) * a.dy;
+            const double f = -a.vc2 * rcp(x * x + y * y + a.rc2);
+            l = kick_vjp(l, a.dt, f * x, f * y);
+        }
+        return l;
+    };
+
+    // states of the cell and of the ring, lam' of the cell
+    C lam = zero_c();
+    if ((a.bcx == 0 || (i >= 0 && i < a.nx)) && (a.bcy == 0 || (j >= 0 && j < a.ny))) lam = lam_prime_here();
+    const P W0 = to_prim(Up.load(cell));
+    const double ir = rcp(W0.r);
+    put_state(lx, ly, W0);
+    if (lx == 0 || lx == BX - 1) {
+        const int d = lx == 0 ? -1 : 1;
+        put_state(lx + d, ly, to_prim(Up.load((unsigned)(gj * a.nx + map(i + d, a.nx, a.bcx)))));
+    }
+    if (ly == 0 || ly == kF_Y - 1) {
+        const int d = ly == 0 ? -1 : 1;
+        put_state(lx, ly + d, to_prim(Up.load((unsigned)(map(j + d, a.ny, a.bcy) * a.nx + gi))));
+    }
+    lds_put(Mrow, BX, 0, lx, {lam.r, lam.mx, lam.my, lam.exx, lam.exy, lam.eyy});
     __syncthreads();
-    // (loading the face-state adjoints before the staging above, or between it
-    // and the barrier, measured slower)
-    const P self = tileB_shares(a, X0, Y0, t, L, tileB_face_adjoints(a, X0, Y0, t));
+
+    // face states; the adjoints of those at the cell's high x face, and of its low x
+    // face from the thread to the left
+    const P dlx = sub(W0, state(lx - 1, ly)), drx = sub(state(lx + 1, ly), W0);
+    Faces<double> f = face_states_d<double, true>(W0, ir, dlx, drx, sub(W0, state(lx, ly - 1)),
+                                                  sub(state(lx, ly + 1), W0), a.kx, a.ky);
+    lds_put(Yrow, BX, 0, lx, f.ylo);
+    Faces<double> fb{zero_p(), zero_p(), zero_p(), zero_p()};
+    {
+        P right = zero_p();
+        hll_vjp(f.xhi, lane_shift<+1>(f.xlo), csub(lane_shift<+1>(lam), lam, a.cx), fb.xhi, right);
+        fb.xlo = lane_shift<-1>(right);
+    }
     __syncthreads();
-    tileB_put_total(t, tileB_total(t, self, L), L);  // the totals go to a slot no thread reads here
+    // the same for the y faces, through the row above's slots
+    if (ly < kF_Y - 1) {
+        const P l = lds_get(Mrow + 6 * BX, BX, 0, lx);
+        const C above = {l.r, l.u, l.v, l.pxx, l.pxy, l.pyy};
+        P low = zero_p(), high = zero_p();
+        hll_vjp(swap(f.yhi), swap(lds_get(Yrow + 6 * BX, BX, 0, lx)), swap(csub(above, lam, a.cy)), low, high);
+        fb.yhi = swapb(low);
+        lds_put(Yrow + 6 * BX, BX, 0, lx, swapb(high));
+    }
     __syncthreads();
-    tileB_gather(a, X0, Y0, t, L);
+    if (ly > 0) fb.ylo = lds_get(Yrow, BX, 0, lx);
+
+    // the face-state reverse pass of the cells next to an output, inside the extended ring
+    P self = zero_p(), left = zero_p(), right = zero_p(), down = zero_p(), up = zero_p();
+    if (lx >= 1 && lx <= BX - 2 && ly >= 1 && ly <= kF_Y - 2 && i >= -1 && i <= a.nx && j >= -1 && j <= a.ny) {
+        face_states_vjp_y(W0, state(lx, ly - 1), state(lx, ly + 1), a.ky, fb, self, down, up);
+        face_states_vjp_x<true>(W0, state(lx - 1, ly), state(lx + 1, ly), a.kx, fb, self, left, right);
+    }
+    lds_put(Yrow, BX, 0, lx, down);
+    lds_put(Mrow, BX, 0, lx, up);
+    acc(self, lane_shift<+1>(left));
+    acc(self, lane_shift<-1>(right));
+    __syncthreads();
+    // what lands on this position
+    if (ly < kF_Y - 1) acc(self, lds_get(Yrow + 6 * BX, BX, 0, lx));
+    if (ly > 0) acc(self, lds_get(Mrow - 6 * BX, BX, 0, lx));
+    // outflow axes: the two ghost positions on either side belong to the boundary cell
+    // (the branches are uniform in the workgroup)
+    if (a.bcx != 0 && (X0 == 0 || X0 + OX >= a.nx)) {
+        const P l1 = lane_shift<-1>(self), l2 = lane_shift<-1>(l1), r1 = lane_shift<+1>(self), r2 = lane_shift<+1>(r1);
+        const double first = i == 0 ? 1.0 : 0.0, last = i == a.nx - 1 ? 1.0 : 0.0;
+        if (first + last != 0.0) {
+            acc(self, scale(first, l1));
+            acc(self, scale(first, l2));
+            acc(self, scale(last, r1));
+            acc(self, scale(last, r2));
+        }
+    }
+    if (a.bcy != 0 && (Y0 == 0 || Y0 + kF_OY >= a.ny)) {
+        put_state(lx, ly, self);  // the states were last read before the barrier above
+        __syncthreads();
+        if (j == 0 && ly >= 2) {
+            acc(self, state(lx, ly - 1));
+            acc(self, state(lx, ly - 2));
+        }
+        if (j == a.ny - 1 && ly <= kF_Y - 3) {
+            acc(self, state(lx, ly + 1));
+            acc(self, state(lx, ly + 2));
+        }
+    }
+    if (lx < 2 || lx >= BX - 2 || ly < 2 || ly >= kF_Y - 2 || i >= a.nx || j >= a.ny) return;
+    // the state and lam' again from the caches: kept in registers they would spill
+    C out = lam_prime_here();
+    to_prim_vjp(Up.load(cell), self, out);
+    OutPlanes<double>(a.lam0, (size_t)a.nx * a.ny).store(cell, out);
 }
 
 __global__ __launch_bounds__(256) void init_adjoint_kernel(const double* W, const double* lamU, double* lamW, int64_t n)
@@ -147,7 +240,7 @@ __global__ __launch_bounds__(256) void init_adjoint_kernel(const double* W, cons
 size_t csh_adjoint_workspace_doubles(int nx, int ny)
 {
     const size_t ey = ny > 1 ? ny + 2 : 1, ne = (size_t)(nx + 2) * ey;
-    if (ny > 1) return ne * 6 * 4;  // the tiled pass: the face-state adjoints only
+    if (ny > 1) return 0;
     return ne * 6 * (4 + 4 + 3) + (size_t)(nx + 4) * ey * 6;
 }
 
@@ -176,11 +269,18 @@ int csh_adjoint_impl(csh_grid_view v, double dt, const void* U, const void* lam_
     a.lam0 = static_cast<double*>(lam);
     const size_t ne = (size_t)a.ex * a.ey;
     if (twod) {
-        a.FSb = ws;
-        const int tax = (a.ex + kA_TX - 1) / kA_TX, tay = (a.ey + kA_TY - 1) / kA_TY;
-        const int tbx = (a.nx + kB_OX - 1) / kB_OX, tby = (a.ny + kB_OY - 1) / kB_OY;
-        adjoint_tileA_kernel<<<(unsigned)(tax * tay), kA_THREADS, 0, s>>>(a, tax);
-        adjoint_tileB_kernel<<<(unsigned)(tbx * tby), kB_THREADS, 0, s>>>(a, tbx);
+        // Blocks of 16 columns, two on a CU at a time, or of 32, one on a CU: the wider
+        // ones trace fewer cells twice (28 x 12 outputs of 32 x 16 cells against
+        // 12 x 12 of 16 x 16), the narrower ones overlap two blocks' barriers.  A round
+        // of them takes 8.5 and 11 us; the launch takes the fewer (us, 16 / 32 columns:
+        // 131 x 93 8.6 / 11.6, 300 x 200 13.1 / 13.0, 400^2 25.8 / 23.3, 512^2
+        // 39.4 / 43.5, 1024^2 126 / 138).
+        auto tiles = [&](int n, int o) { return (long)((n + o - 1) / o); };
+        const long n16 = tiles(v.nx, 12) * tiles(v.ny, kF_OY), n32 = tiles(v.nx, 28) * tiles(v.ny, kF_OY);
+        if (10 * ((n16 + 511) / 512) <= 13 * ((n32 + 255) / 256))
+            adjoint_fused_kernel<16><<<(unsigned)n16, 16 * kF_Y, 0, s>>>(a, (int)tiles(v.nx, 12));
+        else
+            adjoint_fused_kernel<32><<<(unsigned)n32, 32 * kF_Y, 0, s>>>(a, (int)tiles(v.nx, 28));
     } else {
         a.FS = ws;
         a.FSb = ws + 24 * ne;

@@ -109,12 +109,6 @@ struct Cons {
     T r, mx, my, exx, exy, eyy;
 };
 
-// characteristic amplitudes of the waves (u-a, u-c, u[rho], u[Pyy], u+c, u+a)
-template <typename T>
-struct Char {
-    T a1, a2, a3, a4, a5, a6;
-};
-
 template <typename T>
 CSH_HD Prim<T> swap(const Prim<T>& w)
 {
@@ -173,8 +167,7 @@ CSH_HD Cons<T> flux_x(const Prim<T>& w, const Cons<T>& U)
 // shear speed c = sqrt(Pxx / rho), q = Pxy / Pxx.
 template <typename T>
 struct Eig {
-    T a, c, h2a, h2c, ip, q;  // h2a = 1/(2a), h2c = 1/(2c), ip = 1/Pxx
-    T ic;                     // 1/c
+    T a, ic, ip, q;  // ic = 1/c, ip = 1/Pxx
 };
 
 template <typename T>
@@ -183,77 +176,11 @@ CSH_HD Eig<T> eig_x(const Prim<T>& w, T ir)
     Eig<T> e;
     const T t = w.pxx * ir;
     const T y = rsqrt(t);                 // 1 / c
-    e.c = t * y;
-    e.a = T(1.7320508075688772935) * e.c;  // sqrt(3) c
     e.ic = y;
-    e.h2c = T(0.5) * y;
-    e.h2a = T(0.28867513459481288225) * y;  // 1 / (2 sqrt(3) c)
+    e.a = T(1.7320508075688772935) * (t * y);  // sqrt(3) c
     e.ip = y * y * ir;                      // 1 / Pxx = (rho / Pxx) / rho
     e.q = w.pxy * e.ip;
     return e;
-}
-
-// alpha = L d: amplitudes of a primitive difference on the six waves.
-template <typename T>
-CSH_HD Char<T> project(const Prim<T>& w, const Eig<T>& e, const Prim<T>& d)
-{
-    const T t1 = d.pxx * e.ip * T(1.0 / 6.0);
-    const T t2 = d.u * e.h2a;
-    const T s = (d.pxy - e.q * d.pxx) * (T(0.5) * e.ip);
-    const T h = (e.q * d.u - d.v) * e.h2c;
-    Char<T> al;
-    al.a1 = t1 - t2;
-    al.a6 = t1 + t2;
-    al.a2 = h + s;
-    al.a5 = s - h;
-    al.a3 = d.r - w.r * d.pxx * e.ip * T(1.0 / 3.0);
-    al.a4 = d.pyy - T(2) * e.q * d.pxy + (T(4) * e.q * e.q - w.pyy * e.ip) * d.pxx * T(1.0 / 3.0);
-    return al;
-}
-
-// d = R alpha: back-projection on the right eigenvectors.
-template <typename T>
-CSH_HD Prim<T> backproject(const Prim<T>& w, const Eig<T>& e, const Char<T>& al)
-{
-    const T S = al.a1 + al.a6, D = al.a6 - al.a1;
-    const T S25 = al.a2 + al.a5, D25 = al.a5 - al.a2;
-    Prim<T> d;
-    d.r = w.r * S + al.a3;
-    d.u = e.a * D;
-    d.v = e.a * e.q * D + e.c * D25;
-    d.pxx = T(3) * w.pxx * S;
-    d.pxy = T(3) * w.pxy * S + w.pxx * S25;
-    d.pyy = (w.pyy + T(2) * w.pxy * e.q) * S + T(2) * w.pxy * S25 + al.a4;
-    return d;
-}
-
-// Monotonised-central limiter, eq. (25), zero at extrema (the TVD clause).
-// With dl * dr > 0 the centred difference has the sign of both.
-template <typename T>
-CSH_HD T mc(T dl, T dr)
-{
-    // dr with dl's sign taken off is positive iff the two agree in sign; the
-    // clamp at zero then covers the extremum case
-    const T a = fmin(fabs(dl), copysign(T(1), dl) * dr);
-    const T m = fmax(fmin(a + a, T(0.5) * fabs(dl + dr)), T(0));
-    return copysign(m, dl);
-}
-
-// Limited primitive slope along x: eqs. (19)-(26) with dl = w_i - w_{i-1},
-// dr = w_{i+1} - w_i; the centred amplitudes are the mean of the one-sided ones.
-template <typename T>
-CSH_HD Prim<T> limited_slope(const Prim<T>& w, const Eig<T>& e, const Prim<T>& dl,
-                                                 const Prim<T>& dr)
-{
-    const Char<T> l = project(w, e, dl), r = project(w, e, dr);
-    Char<T> m;
-    m.a1 = mc(l.a1, r.a1);
-    m.a2 = mc(l.a2, r.a2);
-    m.a3 = mc(l.a3, r.a3);
-    m.a4 = mc(l.a4, r.a4);
-    m.a5 = mc(l.a5, r.a5);
-    m.a6 = mc(l.a6, r.a6);
-    return backproject(w, e, m);
 }
 
 // Half the MC limiter, mc(dl, dr) / 2, from order statistics: with
@@ -315,22 +242,6 @@ CSH_HD Prim<T> half_slope(const Prim<T>& w, T ir, const Eig<T>& e, const Prim<T>
     d.pxy = e.q * d.pxx + T(0.5) * S2;
     d.pyy = (T(2) * qq3 + g3) * d.pxx + (e.q * S2 + m[3]);
     return d;
-}
-
-// A d with A the primitive x Jacobian (rows: u d_rho + rho d_u, u d_u + d_Pxx/rho,
-// u d_v + d_Pxy/rho, u d_Pxx + 3 Pxx d_u, u d_Pxy + 2 Pxy d_u + Pxx d_v,
-// u d_Pyy + Pyy d_u + 2 Pxy d_v).
-template <typename T>
-CSH_HD Prim<T> jac_x(const Prim<T>& w, T ir, const Prim<T>& d)
-{
-    Prim<T> o;
-    o.r = w.u * d.r + w.r * d.u;
-    o.u = w.u * d.u + ir * d.pxx;
-    o.v = w.u * d.v + ir * d.pxy;
-    o.pxx = w.u * d.pxx + T(3) * w.pxx * d.u;
-    o.pxy = w.u * d.pxy + T(2) * w.pxy * d.u + w.pxx * d.v;
-    o.pyy = w.u * d.pyy + w.pyy * d.u + T(2) * w.pxy * d.v;
-    return o;
 }
 
 // base - k A d with A the primitive x Jacobian (rows of A d: u d_rho + rho d_u,
