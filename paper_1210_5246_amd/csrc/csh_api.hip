@@ -77,6 +77,7 @@ struct csh_grid {
     double* adj_ws = nullptr;       // adjoint workspace, allocated on first use
     size_t adj_ws_n = 0;
     int scheme = CSH_SCHEME_MUSCL_HLL;
+    csh::KtPlan kt_plan{};          // work decomposition of the 2-D Kurganov-Tadmor step
     void* kt_buf = nullptr;         // stage state of the 1-D Kurganov-Tadmor scheme
     double* fourier_ws = nullptr;   // partial sums + amplitudes of csh_fourier_amplitudes
     // cached graph of csh_run_cfl / csh_run_dts
@@ -185,7 +186,7 @@ hipError_t enqueue_step(csh_grid* h, const void* U, void* Un, int dev_dt, double
     a.s_reset = (h->phase + 2) % 3;
     if (h->scheme == CSH_SCHEME_KT && h->ny > 1) {
         h->phase = a.s_out;
-        return csh::launch_kt_fused<T>(a, s);
+        return csh::launch_kt_fused<T>(a, h->kt_plan, s);
     }
     if (h->scheme == CSH_SCHEME_KT) {
         // 1-D: stage 1: U -> stage buffer over dt/2; records dt in slot s_in
@@ -311,6 +312,7 @@ extern "C" int csh_set_scheme(csh_grid* h, int scheme)
         CSH_HIP(hipStreamSynchronize(h->stream));
         CSH_HIP(hipMalloc(&h->kt_buf, bytes));
     }
+    if (scheme == CSH_SCHEME_KT && h->ny > 1) h->kt_plan = csh::kt_plan(h->nx, h->ny, h->dtype == CSH_F64);
     h->scheme = scheme;
     drop_graph(h);
     return CSH_OK;

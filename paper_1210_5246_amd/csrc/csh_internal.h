@@ -110,10 +110,16 @@ hipError_t launch_clear_flag(int* flag, hipStream_t s);
 template <typename T>
 hipError_t launch_kt(const StepArgs<T>& a, bool final_stage, hipStream_t s);
 
-// Kurganov-Tadmor step on a 2-D grid, both stages in one launch (its own
-// strips and row segments; the arguments' decomposition fields are ignored)
+// Kurganov-Tadmor step on a 2-D grid, both stages in one launch: its kernel (a
+// workgroup or a wavefront per segment) and its rows per segment, chosen once for a
+// grid; the arguments' own decomposition fields are ignored
+struct KtPlan {
+    bool block;
+    int rows;
+};
+KtPlan kt_plan(int nx, int ny, bool f64);
 template <typename T>
-hipError_t launch_kt_fused(StepArgs<T> a, hipStream_t s);
+hipError_t launch_kt_fused(StepArgs<T> a, KtPlan plan, hipStream_t s);
 
 // Whole runs of a 1-D grid of at most kLineCells cells in one launch.  U: in
 // place (null: the input U0 is left); states: if set, step k's result goes to

@@ -5,15 +5,16 @@
 // L = -(dH_x/dx + dH_y/dy) with the local-speed flux of eq. (6) at faces
 // reconstructed by component-wise MC-limited linear primitive profiles.  On a
 // 2-D grid both stages run in one launch with the work decomposition of the
-// characteristic sweep (a wavefront per column strip marching up a row
-// segment, x neighbours by DPP lane shifts, y neighbours from row register
-// sets), U* living in registers only; a 1-D grid takes one launch per stage.
+// characteristic sweep (a wavefront per column strip marching up rows, x
+// neighbours by DPP lane shifts, y neighbours from row register sets), U* living
+// in registers (large grids) or in LDS; a 1-D grid takes one launch per stage.
 // The kernels carry half slopes (face states w -+ h) and twice the flux (the
 // update coefficients take the 1/2).
 #include <cstdlib>
 
 #include "csh_device.h"
 #include "csh_internal.h"
+#include "csh_xcd.h"
 
 namespace csh {
 
@@ -106,30 +107,6 @@ __global__ __launch_bounds__(64 * kWaves) void kt_kernel(StepArgs<T> p)
 // read, and the ghost rows a copy of the edge row.
 
 constexpr int kFusedStrip = 56;  // owned columns per wavefront of the fused step
-
-// Rows per segment of the fused step: the critical-path rule of the sweep,
-// with the fused wavefront's halo (stage 1 re-traces 6 rows, stage 2 2, an
-// average of 4 per row of the segment) and its 56-column strips.
-int kt_fused_rows(int nx, int ny)
-{
-    if (const char* e = std::getenv("CSH_KT_ROWS")) {
-        const int v = std::atoi(e);
-        if (v >= 1) return v;
-    }
-    const long strips = (nx + kFusedStrip - 1) / kFusedStrip;
-    auto waves = [&](int t) { return strips * ((ny + t - 1) / t); };
-    const int lo = waves(8) >= 256 ? 8 : 4;
-    int best = lo;
-    long best_cost = -1;
-    for (int t = lo; t <= 96; ++t) {
-        const long cost = ((waves(t) + 1023) / 1024) * (t + 4);
-        if (best_cost < 0 || cost < best_cost) {
-            best_cost = cost;
-            best = t;
-        }
-    }
-    return best;
-}
 
 template <typename T>
 __global__ __launch_bounds__(64 * kWaves) void kt_fused_kernel(StepArgs<T> p)
@@ -283,19 +260,202 @@ __global__ __launch_bounds__(64 * kWaves) void kt_fused_kernel(StepArgs<T> p)
     if (__any(bad) && lane == 0) raise_flag(p.flag);
 }
 
+// ---- both stages in one launch, grids of up to a few workgroups per CU ---------------------------
+//
+// A workgroup of eight wavefronts holds a strip of 56 columns and a segment of up
+// to kBlockRows - 4 rows: the wavefronts first form a share each of the segment's
+// U* rows (and two more on either side) into LDS, in primitive form, then, after a
+// barrier, a share each of the output rows, whose U^n they read again.  In the march
+// above every wavefront forms four U* rows of its neighbours' and runs the two stages
+// one after the other on one wavefront per SIMD; here that is four rows per eight
+// wavefronts, and the eight share the rows of both stages: 100^2 15.5 -> 9.4 us per
+// step, 512^2 24.5 -> 18.9, 1000 x 700 33.0 -> 30.8 (FP32 13.3 -> 7.4, 21.4 -> 14.4,
+// 26.4 -> 22.2).  Bound by the latency of a wavefront's few rows on small grids, by FP64
+// issue (0.9 of it) on the larger.  One workgroup on a CU in FP64 (LDS), two in FP32;
+// twelve wavefronts measured 5% slower (each adds a face per stage), sixteen spill.
+constexpr int kBlockWaves = 8;
+constexpr int kBlockCols = 60;  // U* columns kept: lanes 2..61
+constexpr int kBlockRows = 56;  // U* rows: 157.5 KB in FP64
+
+// half slopes from the differences below and above
 template <typename T>
-hipError_t launch_kt_fused(StepArgs<T> a, hipStream_t s)
+__device__ __forceinline__ Prim<T> mc_half_diff(const Prim<T>& a, const Prim<T>& b)
 {
+    return {mc_half(a.r, b.r),     mc_half(a.u, b.u),     mc_half(a.v, b.v),
+            mc_half(a.pxx, b.pxx), mc_half(a.pxy, b.pxy), mc_half(a.pyy, b.pyy)};
+}
+
+// One stage of a wavefront on the rows [ra, rb) of its columns.  fetch(r): row r of
+// U^n; state(r, C): the primitive row r the stage acts on, given that row; rows
+// ra - 2 .. rb + 1.  emit(r, U) takes the results.
+template <typename T, class Fetch, class State, class Emit>
+__device__ __forceinline__ void kt_march(int ra, int rb, T cx, T cy, Fetch fetch, State state, Emit emit)
+{
+    if (ra >= rb) return;
+    Cons<T> Ca = fetch(ra + 1), Cb = fetch(ra - 1), Cc = fetch(ra);
+    const Prim<T> below = state(ra - 2, fetch(ra - 2));
+    Prim<T> Wa = state(ra + 1, Ca), Wb = state(ra - 1, Cb), Wc = state(ra, Cc);
+    Prim<T> high = plus(Wb, mc_half_slope(below, Wb, Wc));  // high y-face state of the row below
+    Cons<T> acc{};
+    // (W0, C0) row r, Wm and Wp the rows below and above; (Wm, Cm) take row r + 2
+    auto row = [&](int r, Prim<T>& Wm, Cons<T>& Cm, const Prim<T>& W0, const Cons<T>& C0, const Prim<T>& Wp) {
+        const Cons<T> next = fetch(min(r + 2, rb + 1));  // past the end: a row already read
+        const Prim<T> sy = mc_half_slope(Wm, W0, Wp);
+        const Cons<T> G = swap(kt_flux2_x(swap(high), swap(sub(W0, sy))));  // face r - 1/2
+        if (r > ra)
+            emit(r - 1, Cons<T>{acc.r - cy * G.r, acc.mx - cy * G.mx, acc.my - cy * G.my, acc.exx - cy * G.exx,
+                                acc.exy - cy * G.exy, acc.eyy - cy * G.eyy});
+        if (r < rb) {
+            const Prim<T> drx = sub(lane_shift<+1>(W0), W0);
+            const Prim<T> sx = mc_half_diff(lane_shift<-1>(drx), drx);
+            const Cons<T> F = kt_flux2_x(plus(W0, sx), lane_shift<+1>(sub(W0, sx)));
+            const Cons<T> Fm = lane_shift<-1>(F);
+            acc = {C0.r - cx * (F.r - Fm.r) + cy * G.r,         C0.mx - cx * (F.mx - Fm.mx) + cy * G.mx,
+                   C0.my - cx * (F.my - Fm.my) + cy * G.my,     C0.exx - cx * (F.exx - Fm.exx) + cy * G.exx,
+                   C0.exy - cx * (F.exy - Fm.exy) + cy * G.exy, C0.eyy - cx * (F.eyy - Fm.eyy) + cy * G.eyy};
+        }
+        high = plus(W0, sy);
+        Wm = state(min(r + 2, rb + 1), next);
+        Cm = next;
+    };
+    for (int r = ra; r <= rb; r += 3) {
+        row(r, Wb, Cb, Wc, Cc, Wa);
+        if (r + 1 > rb) break;
+        row(r + 1, Wc, Cc, Wa, Ca, Wb);
+        if (r + 2 > rb) break;
+        row(r + 2, Wa, Ca, Wb, Cb, Wc);
+    }
+}
+
+template <typename T>
+__global__ __launch_bounds__(64 * kBlockWaves, 2) void kt_block_kernel(StepArgs<T> p)
+{
+    __shared__ T star[kBlockRows][6][kBlockCols];
+    double t_now;
+    const double dt = kt_dt(p, &t_now);
+    if (blockIdx.x == 0) {
+        slot_clear(p.slots[p.s_reset], threadIdx.x);
+        if (threadIdx.x == 0) {
+            p.slots[p.s_out].t = t_now + dt;
+            if (p.dt_log) *p.dt_log = dt;
+        }
+    }
+    const int lane = threadIdx.x & 63, w = wave_in_block();
+    const unsigned unit = xcd_block(blockIdx.x, gridDim.x);
+    const int sx = unit % p.nstrips, sy = unit / p.nstrips;
+    const int c0 = sx * kFusedStrip - 4, c = c0 + lane;  // columns of lane 0, of this lane
+    const int gc = map_index(c, p.nx, p.bcx);
+    const bool own = lane >= 4 && lane < 4 + kFusedStrip && c < p.nx;
+    const int y0 = sy * p.ty, y1 = min(y0 + p.ty, p.ny);
+    const Planes<T> in(p.U, (size_t)p.nx * p.ny);
+    const OutPlanes<T> out(p.Unew, (size_t)p.nx * p.ny);
+    auto fetch = [&](int r) -> Cons<T> { return in.load((unsigned)(map_near(map_near(r, p.ny, p.bcy), p.ny, p.bcy) * p.nx + gc)); };
+    // rows [a, b) shared out: this wavefront's first row
+    auto share = [&](int a, int b, int i) { return a + (b - a) * i / kBlockWaves; };
+
+    const T h1 = T(0.25 * dt / p.dx), h2 = T(0.25 * dt / p.dy);  // half the stage's length, of 2H
+    kt_march<T>(
+        share(y0 - 2, y1 + 2, w), share(y0 - 2, y1 + 2, w + 1), h1, h2, fetch,
+        [](int, const Cons<T>& C) { return to_prim(C); },
+        [&](int r, const Cons<T>& U) {
+            if (lane < 2 || lane >= 2 + kBlockCols) return;
+            T(*const q)[kBlockCols] = star[r - (y0 - 2)];
+            const Prim<T> s = to_prim(U);
+            q[0][lane - 2] = s.r;
+            q[1][lane - 2] = s.u;
+            q[2][lane - 2] = s.v;
+            q[3][lane - 2] = s.pxx;
+            q[4][lane - 2] = s.pxy;
+            q[5][lane - 2] = s.pyy;
+        });
+    __syncthreads();
+
+    // the column of U* this lane reads: its own (a torus window on a periodic axis), the
+    // edge column's on outflow; lanes outside 2..61 feed nothing that is used
+    const int src = p.bcx != 0 ? min(max(c, 0), p.nx - 1) - c0 : lane;
+    const int col = min(max(src - 2, 0), kBlockCols - 1);
+    double smax = 0.0;
+    bool bad = false;
+    const double idx = 1.0 / p.dx, idy = 1.0 / p.dy;
+    kt_march<T>(
+        share(y0, y1, w), share(y0, y1, w + 1), h1 + h1, h2 + h2, fetch,
+        [&](int r, const Cons<T>&) -> Prim<T> {
+            const int e = p.bcy != 0 ? min(max(r, 0), p.ny - 1) : r;  // outflow: the edge row
+            const T(*const q)[kBlockCols] = star[e - (y0 - 2)];
+            return {q[0][col], q[1][col], q[2][col], q[3][col], q[4][col], q[5][col]};
+        },
+        [&](int r, Cons<T> Un) {
+            kick(Un, p, dt, c, r, true);
+            if (own) {
+                out.store((unsigned)(r * p.nx + c), Un);
+                smax = fmax(smax, checked_rate(Un, idx, idy, bad));
+            }
+        });
+    smax = wave_max(smax);
+    if (lane == 0) slot_add(p.slots[p.s_out], blockIdx.x, smax);
+    if (__any(bad) && lane == 0) raise_flag(p.flag);
+}
+
+// Which kernel, and how many rows per segment: the least of the times (ns) below.
+//
+// March: the critical-path rule of the sweep, with its halo (stage 1 forms six rows
+// more than the segment's, stage 2 two, an average of four per row) and rounds of
+// 1024 wavefronts.  A row takes 1.74 us (FP32 1.3), the launch 3 (4).
+// Block: the longest share of either stage; a round is 256 workgroups (FP32: 512,
+// two on a CU, or a single one each).  A row of one stage takes 1.75 us with two
+// wavefronts on the SIMD (FP32 1.17, with four 1.5), the launch, the barrier and the
+// faces of a share 6.5 (5, 8).
+// Measured, march / block, us: FP64 100^2 15.5 / 9.4, 512^2 24.5 / 18.9, 700^2
+// 26.5 / 24.6, 1000 x 700 33.0 / 30.8; two rounds 1024^2 44 / 51.5, four 1500^2
+// 80 / 111.  FP32 1400^2 (two rounds) 53 / 46, 2048^2 (three) 104 / 87, 3000^2 (seven)
+// 171 / 195: past three rounds the march, whose wavefronts then overlap, is taken.
+KtPlan kt_plan(int nx, int ny, bool f64)
+{
+    const long strips = (nx + kFusedStrip - 1) / kFusedStrip;
+    auto segs = [&](int t) { return strips * ((ny + t - 1) / t); };
+    KtPlan best{false, 0};
+    long best_ns = -1;
+    auto offer = [&](bool block, int t, long ns) {
+        if (best_ns < 0 || ns < best_ns) {
+            best_ns = ns;
+            best = {block, t};
+        }
+    };
+    for (int t = segs(8) >= 256 ? 8 : 4; t <= 96; ++t) {
+        const long rows = ((segs(t) + 1023) / 1024) * (t + 4);
+        offer(false, t, f64 ? 3000 + 1740 * rows : 4000 + 1300 * rows);
+    }
+    auto share = [](int n) { return (n + kBlockWaves - 1) / kBlockWaves; };
+    for (int t = kBlockRows - 4; t >= 1; --t) {
+        const long n = segs(t), rows = share(t + 4) + share(t);
+        if (f64) offer(true, t, 6500 + 1750 * rows * ((n + 255) / 256));
+        else if (n <= 256) offer(true, t, 5000 + 1170 * rows);
+        else if (n <= 3 * 512) offer(true, t, (8000 + 1500 * rows) * ((n + 511) / 512));
+    }
+    return best;
+}
+
+template <typename T>
+hipError_t launch_kt_fused(StepArgs<T> a, KtPlan plan, hipStream_t s)
+{
+    if (const char* e = std::getenv("CSH_KT_ROWS")) {
+        const int v = std::atoi(e);
+        if (v >= 1) plan = {false, v};
+    }
     a.nstrips = (a.nx + kFusedStrip - 1) / kFusedStrip;
-    a.ty = kt_fused_rows(a.nx, a.ny);
+    a.ty = plan.rows;
     a.nsegs = (a.ny + a.ty - 1) / a.ty;
+    if (plan.block) {
+        kt_block_kernel<T><<<dim3(a.nstrips * a.nsegs), dim3(64 * kBlockWaves), 0, s>>>(a);
+        return hipGetLastError();
+    }
     const int nwaves = a.nstrips * a.nsegs;
     kt_fused_kernel<T><<<dim3((nwaves + kWaves - 1) / kWaves), dim3(64 * kWaves), 0, s>>>(a);
     return hipGetLastError();
 }
 
-template hipError_t launch_kt_fused<double>(StepArgs<double>, hipStream_t);
-template hipError_t launch_kt_fused<float>(StepArgs<float>, hipStream_t);
+template hipError_t launch_kt_fused<double>(StepArgs<double>, KtPlan, hipStream_t);
+template hipError_t launch_kt_fused<float>(StepArgs<float>, KtPlan, hipStream_t);
 
 template <typename T>
 hipError_t launch_kt(const StepArgs<T>& a, bool final_stage, hipStream_t s)
