@@ -193,12 +193,13 @@ __global__ __launch_bounds__(BX * kF_Y, 2) void adjoint_fused_kernel(AdjArgs a, 
     // (the branches are uniform in the workgroup)
     if (a.bcx != 0 && (X0 == 0 || X0 + OX >= a.nx)) {
         const P l1 = lane_shift<-1>(self), l2 = lane_shift<-1>(l1), r1 = lane_shift<+1>(self), r2 = lane_shift<+1>(r1);
-        const double first = i == 0 ? 1.0 : 0.0, last = i == a.nx - 1 ? 1.0 : 0.0;
-        if (first + last != 0.0) {
-            acc(self, scale(first, l1));
-            acc(self, scale(first, l2));
-            acc(self, scale(last, r1));
-            acc(self, scale(last, r2));
+        if (i == 0) {
+            acc(self, l1);
+            acc(self, l2);
+        }
+        if (i == a.nx - 1) {
+            acc(self, r1);
+            acc(self, r2);
         }
     }
     if (a.bcy != 0 && (Y0 == 0 || Y0 + kF_OY >= a.ny)) {

@@ -38,3 +38,21 @@ def test_blocks(shape, bc):
         G.set_potential(g.vc, g.rc, g.x0, g.y0)
     got = G.adjoint_step(dt, torch.from_numpy(U).cuda(), torch.from_numpy(lam).cuda()).cpu().numpy()
     assert np.abs(got - ref).max() / np.abs(ref).max() < 1e-12
+
+
+def test_a_nan_reaches_only_the_cells_of_its_stencil():
+    """NaN adjoints three cells from each boundary of an outflow grid: the same cells
+    are NaN as in the CPU pass, the boundary cells not among them."""
+    nx, ny = 24, 20
+    W = np.ascontiguousarray(wl.periodic(64, 72).W[:, :ny, :nx])
+    g = oracle.Grid(nx, ny, 1.0 / nx, 1.2 / ny, 1, 1, 0.0, 0.0, 0.0, 0.0)
+    U = oracle.cons_field(W)
+    dt = 0.8 / oracle.max_signal_speed(g, U)
+    for j, i in ((10, 3), (10, nx - 4), (3, 12), (ny - 4, 12)):
+        lam = np.random.default_rng(i).standard_normal(U.shape)
+        lam[:, j, i] = np.nan
+        ref = th.host_adjoint(g, dt, U, lam)
+        G = csh.Grid(torch.from_numpy(W).cuda(), g.dx, g.dy, (1, 1))
+        got = G.adjoint_step(dt, torch.from_numpy(U).cuda(), torch.from_numpy(lam).cuda()).cpu().numpy()
+        assert np.isfinite(ref[:, 10, [0, nx - 1]]).all() and np.isfinite(ref[:, [0, ny - 1], 12]).all()
+        np.testing.assert_array_equal(np.isnan(got), np.isnan(ref))
