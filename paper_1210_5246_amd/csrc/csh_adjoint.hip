@@ -35,48 +35,42 @@ namespace csh {
 
 // ---- kernels ----------------------------------------------------------------------------------------
 
-template <bool TWOD, int STAGE>
+// Stages 1, 2 and 4 of 1-D grids, a thread per cell.
+template <int STAGE>
 __global__ __launch_bounds__(256) void adjoint_kernel(AdjArgs a)
 {
     // cell counts stay below 2^31 (a plane is smaller than 4 GiB): 32-bit index arithmetic
     const unsigned t = xcd_block(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
     if (STAGE == 4) {  // interior cells
-        if (t >= (unsigned)a.nx * (unsigned)a.ny) return;
-        gather_cell<TWOD>(a, (int)(t % (unsigned)a.nx), (int)(t / (unsigned)a.nx));
+        if (t < (unsigned)a.nx) gather_cell<false>(a, (int)t, 0);
         return;
     }
-    if (t >= (unsigned)a.ex * (unsigned)a.ey) return;  // extended cells
-    const int i = (int)(t % (unsigned)a.ex) - 1;
-    const int j = TWOD ? (int)(t / (unsigned)a.ex) - 1 : 0;
-    if (STAGE == 1) faces_cell<TWOD>(a, i, j);
-    if (STAGE == 2) hll_cell<TWOD>(a, i, j);
-    if constexpr (STAGE == 3 && TWOD) cells_cell_y(a, i, j);
+    if (t >= (unsigned)a.ex) return;  // extended cells
+    if (STAGE == 1) faces_cell<false>(a, (int)t - 1, 0);
+    if (STAGE == 2) hll_cell<false>(a, (int)t - 1, 0);
 }
 
-// Stage 5, the x part, summed per padded position: a wavefront covers the
-// extended columns base .. base + 63 of one extended row (base = 62 w - 3) and
+// Stage 3, summed per padded position: a wavefront covers the extended cells
+// base .. base + 63 (base = 62 w - 3) and
 // writes the padded positions of its lanes 1..62; lanes outside the extended
 // range contribute zero.  The summation order is that of a per-position sum of
 // slots: self, then the left share of the cell to the right, then the right
 // share of the cell to the left.
 constexpr int kXsOwned = 62;
 
-template <bool TWOD>
 __global__ __launch_bounds__(256) void adjoint_xsum_kernel(AdjArgs a)
 {
     const int lane = threadIdx.x & 63;
     const long w = (long)xcd_block(blockIdx.x, gridDim.x) * 4 + wave_in_block();
-    const int wpr = (a.nx + 4 + kXsOwned - 1) / kXsOwned;  // wavefronts per extended row
-    if (w >= (long)wpr * a.ey) return;                     // uniform per wavefront
-    const int j = TWOD ? (int)(w / wpr) - 1 : 0;
-    const int i = (int)(w % wpr) * kXsOwned - 3 + lane;
+    if (w >= (a.nx + 4 + kXsOwned - 1) / kXsOwned) return;  // uniform per wavefront
+    const int i = (int)w * kXsOwned - 3 + lane;
     P b0 = zero_p(), bl = zero_p(), br = zero_p();
-    if (i >= -1 && i <= a.nx) cells_x_vjp<TWOD>(a, i, j, b0, bl, br);
+    if (i >= -1 && i <= a.nx) cells_x_vjp<false>(a, i, 0, b0, bl, br);
     const P l = lane_shift<+1>(bl), r = lane_shift<-1>(br);  // from the cells at i + 1, i - 1
     const P sum = {b0.r + l.r + r.r,       b0.u + l.u + r.u,       b0.v + l.v + r.v,
                    b0.pxx + l.pxx + r.pxx, b0.pxy + l.pxy + r.pxy, b0.pyy + l.pyy + r.pyy};
     if (lane >= 1 && lane <= kXsOwned && i >= -2 && i <= a.nx + 1)
-        store_p(a.XS, (size_t)(a.nx + 4) * a.ey, 0, xs_index(a, i, j), sum);
+        store_p(a.XS, (size_t)(a.nx + 4), 0, xs_index(a, i, 0), sum);
 }
 
 // The reverse pass of 2-D grids, one launch.  A workgroup holds a block of
@@ -240,9 +234,8 @@ __global__ __launch_bounds__(256) void init_adjoint_kernel(const double* W, cons
 
 size_t csh_adjoint_workspace_doubles(int nx, int ny)
 {
-    const size_t ey = ny > 1 ? ny + 2 : 1, ne = (size_t)(nx + 2) * ey;
     if (ny > 1) return 0;
-    return ne * 6 * (4 + 4 + 3) + (size_t)(nx + 4) * ey * 6;
+    return (size_t)(nx + 2) * 6 * (4 + 4 + 3) + (size_t)(nx + 4) * 6;
 }
 
 int csh_adjoint_impl(csh_grid_view v, double dt, const void* U, const void* lam_next, void* lam, double* ws,
@@ -287,13 +280,12 @@ int csh_adjoint_impl(csh_grid_view v, double dt, const void* U, const void* lam_
         a.FSb = ws + 24 * ne;
         a.Cs = ws + 48 * ne;
         a.XS = ws + 66 * ne;
-        const unsigned be = (unsigned)((ne + 255) / 256), bi = (unsigned)(((size_t)v.nx * v.ny + 255) / 256);
-        const long xs_waves = (long)((a.nx + 4 + kXsOwned - 1) / kXsOwned) * a.ey;
-        const unsigned bx = (unsigned)((xs_waves + 3) / 4);
-        adjoint_kernel<false, 1><<<be, 256, 0, s>>>(a);
-        adjoint_kernel<false, 2><<<be, 256, 0, s>>>(a);
-        adjoint_xsum_kernel<false><<<bx, 256, 0, s>>>(a);
-        adjoint_kernel<false, 4><<<bi, 256, 0, s>>>(a);
+        const unsigned be = (unsigned)((ne + 255) / 256), bi = (unsigned)(((size_t)v.nx + 255) / 256);
+        const unsigned bx = (unsigned)(((a.nx + 4 + kXsOwned - 1) / kXsOwned + 3) / 4);
+        adjoint_kernel<1><<<be, 256, 0, s>>>(a);
+        adjoint_kernel<2><<<be, 256, 0, s>>>(a);
+        adjoint_xsum_kernel<<<bx, 256, 0, s>>>(a);
+        adjoint_kernel<4><<<bi, 256, 0, s>>>(a);
     }
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return csh_fail(CSH_ERR_HIP, std::string("adjoint_step: ") + hipGetErrorString(e));
