@@ -88,9 +88,12 @@ __global__ __launch_bounds__(256) void adjoint_xsum_kernel(AdjArgs a)
 // Two launches with the face-state adjoints in between (192 B per cell written and
 // read with a ring) moved 663 B per cell-step, 49 us at 512^2 whatever their
 // instruction count; here the state, lam^{n+1} and lam^n are all that is moved
-// (131 x 93 16.9 -> 8.5 us, 300 x 200 21.1 -> 12.8, 512^2 51.2 -> 38.8).  Bound by
-// FP64 issue (~1900 instructions a thread, 256 threads for 144 outputs) and by the
-// latency of its phases at two wavefronts per SIMD (256 registers).
+// (131 x 93 16.9 -> 7.9 us, 300 x 200 21.1 -> 11.7, 512^2 51.2 -> 38.6).  Bound by
+// FP64 issue (VALU busy 0.49: ~1800 instructions a thread, 256 threads for 144
+// outputs) and by the latency of its phases at two wavefronts per SIMD (230
+// registers: values are put into LDS as soon as they are known and read again after
+// the fluxes; kept through the reverse pass they spilled 44 B a thread, 131 x 93
+// 8.5 us, 400^2 23.2 against 21.3).
 constexpr int kF_Y = 16, kF_OY = kF_Y - 4;
 
 template <int BX>
@@ -116,9 +119,8 @@ __global__ __launch_bounds__(BX * kF_Y, 2) void adjoint_fused_kernel(AdjArgs a, 
     double* const Yrow = Y + ly * 6 * BX;
     double* const Mrow = M + ly * 6 * BX;
 
-    // lam' of the mapped cell: the kick's transpose applied to lam^{n+1}
-    auto lam_prime_here = [&]() -> C {
-        C l = Lp.load(cell);
+    // lam' of the mapped cell from its lam^{n+1}: the kick's transpose
+    auto lam_prime = [&](C l) -> C {
         if (a.vc2 != 0.0) {
             const double x = a.x0 + (gi + 0.5) * a.dx, y = a.y0 + (gj + 0.5) * a.dy;
             const double f = -a.vc2 * rcp(x * x + y * y + a.rc2);
@@ -129,7 +131,7 @@ __global__ __launch_bounds__(BX * kF_Y, 2) void adjoint_fused_kernel(AdjArgs a, 
 
     // states of the cell and of the ring, lam' of the cell
     C lam = zero_c();
-    if ((a.bcx == 0 || (i >= 0 && i < a.nx)) && (a.bcy == 0 || (j >= 0 && j < a.ny))) lam = lam_prime_here();
+    if ((a.bcx == 0 || (i >= 0 && i < a.nx)) && (a.bcy == 0 || (j >= 0 && j < a.ny))) lam = lam_prime(Lp.load(cell));
     const P W0 = to_prim(Up.load(cell));
     const double ir = rcp(W0.r);
     put_state(lx, ly, W0);
@@ -170,15 +172,18 @@ __global__ __launch_bounds__(BX * kF_Y, 2) void adjoint_fused_kernel(AdjArgs a, 
     if (ly > 0) fb.ylo = lds_get(Yrow, BX, 0, lx);
 
     // the face-state reverse pass of the cells next to an output, inside the extended ring
+    const bool inner = lx >= 1 && lx <= BX - 2 && ly >= 1 && ly <= kF_Y - 2 && i >= -1 && i <= a.nx && j >= -1 &&
+                       j <= a.ny;
+    const P Wc = state(lx, ly);  // W0 again: a register set less through the fluxes
     P self = zero_p(), left = zero_p(), right = zero_p(), down = zero_p(), up = zero_p();
-    if (lx >= 1 && lx <= BX - 2 && ly >= 1 && ly <= kF_Y - 2 && i >= -1 && i <= a.nx && j >= -1 && j <= a.ny) {
-        face_states_vjp_y(W0, state(lx, ly - 1), state(lx, ly + 1), a.ky, fb, self, down, up);
-        face_states_vjp_x<true>(W0, state(lx - 1, ly), state(lx + 1, ly), a.kx, fb, self, left, right);
-    }
-    lds_put(Yrow, BX, 0, lx, down);
+    if (inner) face_states_vjp_y(Wc, state(lx, ly - 1), state(lx, ly + 1), a.ky, fb, self, down, up);
+    lds_put(Yrow, BX, 0, lx, down);  // at once: kept through the x part they would spill
     lds_put(Mrow, BX, 0, lx, up);
+    if (inner) face_states_vjp_x<true>(Wc, state(lx - 1, ly), state(lx + 1, ly), a.kx, fb, self, left, right);
     acc(self, lane_shift<+1>(left));
     acc(self, lane_shift<-1>(right));
+    // the state and lam^{n+1} again from the caches: kept in registers they would spill
+    const C Uc = Up.load(cell), lc = Lp.load(cell);
     __syncthreads();
     // what lands on this position
     if (ly < kF_Y - 1) acc(self, lds_get(Yrow + 6 * BX, BX, 0, lx));
@@ -209,9 +214,8 @@ __global__ __launch_bounds__(BX * kF_Y, 2) void adjoint_fused_kernel(AdjArgs a, 
         }
     }
     if (lx < 2 || lx >= BX - 2 || ly < 2 || ly >= kF_Y - 2 || i >= a.nx || j >= a.ny) return;
-    // the state and lam' again from the caches: kept in registers they would spill
-    C out = lam_prime_here();
-    to_prim_vjp(Up.load(cell), self, out);
+    C out = lam_prime(lc);
+    to_prim_vjp(Uc, self, out);
     OutPlanes<double>(a.lam0, (size_t)a.nx * a.ny).store(cell, out);
 }
 
@@ -266,9 +270,9 @@ int csh_adjoint_impl(csh_grid_view v, double dt, const void* U, const void* lam_
         // Blocks of 16 columns, two on a CU at a time, or of 32, one on a CU: the wider
         // ones trace fewer cells twice (28 x 12 outputs of 32 x 16 cells against
         // 12 x 12 of 16 x 16), the narrower ones overlap two blocks' barriers.  A round
-        // of them takes 8.5 and 11 us; the launch takes the fewer (us, 16 / 32 columns:
-        // 131 x 93 8.6 / 11.6, 300 x 200 13.1 / 13.0, 400^2 25.8 / 23.3, 512^2
-        // 39.4 / 43.5, 1024^2 126 / 138).
+        // of them takes 8 to 10 and 10.6 us; the launch takes the fewer (us, 16 / 32 columns:
+        // 131 x 93 7.9 / 10.8, 300 x 200 11.8 / 11.6, 400^2 24.3 / 21.4, 480^2
+        // 32.5 / 31.4, 512^2 38.8 / 41.7, 560^2 41.0 / 41.6, 1024^2 122 / 130).
         auto tiles = [&](int n, int o) { return (long)((n + o - 1) / o); };
         const long n16 = tiles(v.nx, 12) * tiles(v.ny, kF_OY), n32 = tiles(v.nx, 28) * tiles(v.ny, kF_OY);
         if (10 * ((n16 + 511) / 512) <= 13 * ((n32 + 255) / 256))
