@@ -3,7 +3,7 @@
 A step is one full sweep of the grid: slopes, characteristic limiting and
 tracing, HLL fluxes, unsplit update, external-potential kick and the fused
 CFL reduction that sets the next timestep on the device.  The timed region
-replays the captured graph of K steps from the initial state, already
+is one run of K steps (csh_run_cfl) from the initial state, already
 resident in HBM.  Prints one JSON line.
 
   python bench.py [--gpus 1] [--steps 50] [--warmup 3]
@@ -83,7 +83,7 @@ def log(*a):
     print("[bench]", *a, file=sys.stderr, flush=True)
 
 
-def time_graph(g, U0, steps, cfl=0.8):
+def time_run(g, U0, steps, cfl=0.8):
     import torch
     g.U.copy_(U0)
     torch.cuda.synchronize()
@@ -203,10 +203,10 @@ def cpu_baseline(w, seconds=(8.0, 4.0, 4.0)):
 
 
 def bench_batched(steps=200):
-    """512 uneven tubes x 200 steps: one persistent graph launch against the
+    """512 uneven tubes x 200 steps: one persistent launch against the
     plain one-grid-per-launch path.  The plain reference is each tube's own
-    handle running its device-timed 200 steps as a replayed graph (handles and
-    graphs made before the timed region, all tubes back to back on one
+    handle running its device-timed 200 steps in one call (handles and what they
+    record made before the timed region, all tubes back to back on one
     stream); a host-stepped variant (per step a host round trip for the
     timestep and one launch) is reported beside it."""
     import numpy as np
@@ -218,7 +218,7 @@ def bench_batched(steps=200):
     b = csh.Batch(W, t.offsets)
     U0 = b.U.clone()
     best = b.autotune(probe_steps=8)
-    b.run(steps, 0.8)                       # records the graph
+    b.run(steps, 0.8)                       # warm
     b.U.copy_(U0)
     torch.cuda.synchronize()
     e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
@@ -237,7 +237,7 @@ def bench_batched(steps=200):
                      (csh.BC_OUTFLOW, csh.BC_OUTFLOW))
         starts.append(g.U.clone())
         logs.append(torch.empty(steps, dtype=torch.float64, device="cuda"))
-        g.run_cfl(steps, 0.8, dt_log=logs[-1])   # records this handle's graph
+        g.run_cfl(steps, 0.8, dt_log=logs[-1])   # warm: records what this handle replays
         grids.append(g)
     for g, u0 in zip(grids, starts):
         g.U.copy_(u0)
@@ -253,7 +253,7 @@ def bench_batched(steps=200):
         ref = g.U.cpu().numpy()
         got = Ub[:, int(t.offsets[k]):int(t.offsets[k + 1])]
         worst = max(worst, float(np.abs(got - ref).max() / np.abs(ref).max()))
-    log(f"plain (graph per tube): {t_plain * 1e3:.1f} ms; max scaled difference {worst:.1e}")
+    log(f"plain (a handle per tube): {t_plain * 1e3:.1f} ms; max scaled difference {worst:.1e}")
     # host-stepped: max_signal_speed (a sync) and one step per launch
     for g, u0 in zip(grids, starts):
         g.U.copy_(u0)
@@ -272,7 +272,7 @@ def bench_batched(steps=200):
                         f"{steps} steps, own CFL dt per tube, FP64",
             "batched_value": cells / t_batch, "plain_value": cells / t_plain, "unit": "cell-updates/s",
             "speedup": t_plain / t_batch, "batched_ms": t_batch * 1e3, "plain_ms": t_plain * 1e3,
-            "plain": "per tube its own handle and a replayed graph of its 200 device-timed steps, "
+            "plain": "per tube its own handle and one call of its 200 device-timed steps, "
                      "tubes back to back on one stream",
             "host_stepped_value": cells / t_host, "host_stepped_s": t_host,
             "speedup_vs_host_stepped": t_host / t_batch,
@@ -300,7 +300,7 @@ def bench_adjoint(n=512, steps=200, K=20, ndirs=64):
         (gr,) = torch.autograd.grad(L, W0)
         return gr, dts
 
-    grad_once()  # warm (graph capture, workspace)
+    grad_once()  # warm (handles, workspaces)
     torch.cuda.synchronize()
     t0 = time.perf_counter()
     gr, dts = grad_once()
@@ -328,7 +328,7 @@ def bench_adjoint(n=512, steps=200, K=20, ndirs=64):
     dirs = [torch.from_numpy(d).to("cuda") for d in wl.fd_directions(n, ndirs)]
     eps = 1e-6
     runner = cag.FrozenRunner(Wd, w0.dx, w0.dy, (0, 0), dts)
-    runner.run(Wd)  # records the graph
+    runner.run(Wd)  # warm
     torch.cuda.synchronize()
     t0 = time.perf_counter()
     fds = []
@@ -391,8 +391,8 @@ def bench_fourier(w, reps=20):
 
 
 def bench_3d(n=256, steps=10):
-    """The 3-D ten-moment sweep on a periodic n^3 random state (FP64): graph-
-    replayed device-timed steps; bandwidth at the design's bytes per cell."""
+    """The 3-D ten-moment sweep on a periodic n^3 random state (FP64):
+    device-timed steps; bandwidth at the design's bytes per cell."""
     import torch
     import workloads as wl
     import paper_1210_5246_amd as csh
@@ -400,7 +400,7 @@ def bench_3d(n=256, steps=10):
     G = csh.Grid3(torch.from_numpy(w.W).to("cuda"), w.h, w.bc)
     del w
     U0 = G.U.clone()
-    G.run_cfl(steps, 0.8)                   # records the graph
+    G.run_cfl(steps, 0.8)                   # warm
     G.U.copy_(U0)
     torch.cuda.synchronize()
     e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
@@ -499,9 +499,9 @@ def main():
         if Wm > 0:
             g.run_cfl(Wm, 0.8)
         g.U.copy_(U0)
-        g.run_cfl(K, 0.8)          # records the graph of K steps
+        g.run_cfl(K, 0.8)          # warm: the run of K steps
         torch.cuda.synchronize()
-        secs, dts = time_graph(g, U0, K)
+        secs, dts = time_run(g, U0, K)
         dt_first = float(dts[0].item())
         log(f"{name}: {K} steps in {secs * 1e3:.2f} ms")
         kern = time_kernel(g, U0, max(K, 10), dt_first)
@@ -557,7 +557,7 @@ def main():
         g.U.copy_(U0)
         g.run_cfl(K, 0.8)
         torch.cuda.synchronize()
-        secs, dts = time_graph(g, U0, K)
+        secs, dts = time_run(g, U0, K)
         log(f"hllc: {K} steps in {secs * 1e3:.2f} ms")
         kern = time_kernel(g, U0, max(K, 10), float(dts[0].item()))
         out["hllc"] = {"value": K * cells / secs, "unit": "cell-updates/s", "ms_per_step": secs / K * 1e3,
@@ -575,7 +575,7 @@ def main():
         g.U.copy_(U0)
         g.run_cfl(K, KT_CFL)
         torch.cuda.synchronize()
-        secs, dts = time_graph(g, U0, K, KT_CFL)
+        secs, dts = time_run(g, U0, K, KT_CFL)
         log(f"kt: {K} steps in {secs * 1e3:.2f} ms")
         kern = time_kernel(g, U0, max(K, 10), float(dts[0].item()))
         sim_t = float(dts.sum().item())

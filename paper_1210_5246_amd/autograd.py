@@ -22,8 +22,8 @@ import torch
 from . import BC_PERIODIC, Grid
 
 # Grid handles reused by consecutive sweeps with the same geometry (the usual
-# pattern of an optimisation loop): the handle's captured graph, reduction
-# slots and adjoint workspace are then set up once.  At most _CACHE_SIZE
+# pattern of an optimisation loop): the handle's recorded runs, reduction
+# slots and workspaces are then set up once.  At most _CACHE_SIZE
 # handles are kept (least recently used dropped); clear_cache() frees them.
 _CACHE_SIZE = 2
 _cache: OrderedDict = OrderedDict()
@@ -50,8 +50,7 @@ def _grid(W0: torch.Tensor, dx: float, dy: float, bc, potential, checkpoint_ever
     _cache[key] = g
     while len(_cache) > _CACHE_SIZE:
         _cache.popitem(last=False)
-    # one timestep log buffer per handle: the graph captured for a segment
-    # length is reused as long as its buffers are the same
+    # one timestep log buffer per handle, for every segment of a run
     if getattr(g, "_seg_log", None) is None or g._seg_log.numel() < checkpoint_every:
         g._seg_log = torch.empty(checkpoint_every, dtype=torch.float64, device=W0.device)
     return g
@@ -74,7 +73,7 @@ class AdjointSweep(torch.autograd.Function):
         else:
             dts_dev = torch.empty(max(nsteps, 1), dtype=torch.float64, device=U.device)
         if K == 1 and dts is None and nsteps > 0:
-            # every state kept (nsteps states in device memory): one graph launch
+            # every state kept (nsteps states in device memory): one call
             # writes the whole trajectory and the reverse pass recomputes nothing
             states, _ = g.run_cfl_states(nsteps, cfl, U0=U, dt_log=dts_dev)
             ckpts = [U.clone()] + [states[k] for k in range(nsteps - 1)]
@@ -129,7 +128,7 @@ def sweep(W0: torch.Tensor, dx: float, dy: float = 1.0, bc=(BC_PERIODIC, BC_PERI
 
 def run_frozen(W0: torch.Tensor, dx: float, dy: float, bc, dts, potential=None) -> torch.Tensor:
     """Forward only, with a given timestep list (for finite-difference checks):
-    one graph launch of len(dts) steps reading the timesteps on the device."""
+    one call of len(dts) steps reading the timesteps on the device."""
     g = Grid(W0.contiguous(), dx, dy, bc)
     if potential is not None:
         g.set_potential(*potential)
@@ -138,8 +137,8 @@ def run_frozen(W0: torch.Tensor, dx: float, dy: float, bc, dts, potential=None) 
 
 
 class FrozenRunner:
-    """Repeated forward runs with one timestep list on one grid handle (the
-    captured graph is reused across runs): run(W0) -> final conserved state."""
+    """Repeated forward runs with one timestep list on one grid handle (what the
+    handle recorded or allocated is reused across runs): run(W0) -> final conserved state."""
 
     def __init__(self, W_like: torch.Tensor, dx: float, dy: float, bc, dts, potential=None):
         self.g = Grid(W_like.contiguous(), dx, dy, bc)
