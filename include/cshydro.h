@@ -36,7 +36,7 @@
  *                    every 2-D launch (a recorded graph keeps the value it
  *                    was recorded with);
  *       CSH_PLANES   the most planes the 3-D sweep marches in one piece;
- *       CSH_WG3      workgroups of the 3-D sweep;
+ *       CSH_WG3      workgroups of the 3-D sweep (in equal shares);
  *     the last two are read at every step of csh3_step and csh3_run_cfl.
  */
 #ifndef CSHYDRO_H

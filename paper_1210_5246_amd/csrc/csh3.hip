@@ -111,6 +111,7 @@ struct SArgs {
     int nstrips, ngroups;  // strips of kStrip3 columns, groups of kOut rows
     long long units;       // nstrips * ngroups * nz plane-columns
     int max_planes;        // longest run of planes taken in one piece
+    int pieces;            // if set, every column is cut into this many runs, one per workgroup
 };
 
 // 10-vectors in LDS as [row slot][component][column]: the 32 lanes of a row
@@ -175,13 +176,19 @@ __global__ __launch_bounds__(256) void sweep3_kernel(SArgs q)
     // gives each workgroup one whole column: all march in step, and the
     // XCD-aware numbering puts neighbouring row groups, which read two rows
     // in common, on one L2 at the same planes.  The second pass deals the
-    // remaining plane-columns in equal contiguous shares.
+    // remaining plane-columns in equal contiguous shares, or (small grids) each
+    // column in equal runs.
     const long long g = xcd_block(blockIdx.x, gridDim.x), nwg = gridDim.x;
-    const long long ncols = q.units / nz, full = ncols >= nwg ? nwg : 0;
+    const long long ncols = q.units / nz, full = q.pieces == 0 && ncols >= nwg ? nwg : 0;
     const long long rest = q.units - full * nz;
     for (int pass = 0; pass < 2; ++pass) {
         long long u = pass == 0 ? g * nz : full * nz + rest * g / nwg;
-        const long long u_end = pass == 0 ? (g < full ? (g + 1) * nz : g * nz) : full * nz + rest * (g + 1) / nwg;
+        long long u_end = pass == 0 ? (g < full ? (g + 1) * nz : g * nz) : full * nz + rest * (g + 1) / nwg;
+        if (q.pieces > 0 && pass == 1) {
+            const long long cidx = g / q.pieces, cut = g - cidx * q.pieces;
+            u = cidx * nz + nz * cut / q.pieces;
+            u_end = cidx * nz + nz * (cut + 1) / q.pieces;
+        }
         while (u < u_end) {  // wave-uniform: every wavefront takes the same runs
             const long long cidx = u / nz;
             const int z0 = (int)(u - cidx * nz);
@@ -426,7 +433,7 @@ d3::Args args(csh3_grid* h, const double* U, double* Un, int dev_dt, double dt, 
 // Workgroups of the sweep: one per CU (four wavefronts at one per SIMD fill
 // a CU), each taking whole columns of planes and then an equal share of the
 // rest, so that every CU marches the same number of planes (plus two halo
-// planes per run).
+// planes per run); on small grids a run of one column each.
 long long sweep_units(const csh3_grid* h)
 {
     const long long nstrips = (h->n[0] + d3::kStrip3 - 1) / d3::kStrip3;
@@ -452,9 +459,21 @@ hipError_t enqueue_step3(csh3_grid* h, const double* U, double* Un, int dev_dt, 
         if (v >= 1) m.max_planes = v;
     }
     long long wg = h->ncu;
-    if (const char* e = std::getenv("CSH_WG3")) {  // tuning override
-        const int v = std::atoi(e);
-        if (v >= 1) wg = v;
+    const char* e = std::getenv("CSH_WG3");  // tuning override
+    if (e && std::atoi(e) >= 1) {
+        wg = std::atoi(e);
+    } else {
+        // Every run of planes costs two halo planes, and an equal share usually ends in
+        // another column than it began: two runs.  Cut every column into the same
+        // number of runs instead where the longest is at most two planes longer than a
+        // share (us per step, shares / runs: 61 x 47 x 33, 4 planes of either, 40 /
+        // 33; 80^3, 14, 79 / 70; 56 x 60 x 200, 16 and 17, 90 / 83; 84 x 90 x 120, 22 and
+        // 24, 113 / 108; 100^3, 27 and 34, 135 / 146).
+        const long long ncols = (long long)m.nstrips * m.ngroups, pieces = std::min<long long>(wg / ncols, h->n[2]);
+        if (pieces > 0 && (h->n[2] + pieces - 1) / pieces <= (m.units + wg - 1) / wg + 2) {
+            m.pieces = (int)pieces;
+            wg = ncols * pieces;
+        }
     }
     wg = std::min(wg, m.units);
     h->phase = m.a.s_out;
