@@ -283,10 +283,12 @@ int csh_batch_init(csh_batch **b, int ntubes, const int64_t *offsets, int dtype,
 /*
  * Advance every tube nsteps steps, each with its own CFL timestep
  * dt = cfl / s_k recomputed on the device after every step, in one persistent
- * launch (workgroups take whole tubes, longest first, from a device queue).
+ * launch (workgroups take whole tubes, longest first, from a device queue;
+ * where all start at once, long ones beside short ones).
  * U is updated in place (U_work: caller buffer of the same size).  dt_out: device array [ntubes][nsteps] of the
  * timesteps taken, or NULL.  threads: workgroup size (64, 128, 256, 512 or
- * 1024), or 0 for the size chosen by csh_batch_autotune (256 if never tuned).
+ * 1024), or 0 for the size chosen by csh_batch_autotune (if never tuned 256 or 512 by
+ * the number and length of the tubes).  Results are bitwise the same for all.
  */
 int csh_batch_run(csh_batch *b, int nsteps, double cfl, void *U, void *U_work, double *dt_out,
                   int threads);

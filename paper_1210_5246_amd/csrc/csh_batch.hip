@@ -1,8 +1,9 @@
 // Many independent 1-D problems of uneven length in one persistent launch.
 //
-// Each workgroup takes a whole tube from a device queue (tubes ordered longest
-// first, so the queue hands out work in LPT order) and advances it nsteps
-// steps: for every step, its wavefronts sweep the tube in chunks of 60 cells
+// Each workgroup takes a whole tube, first the one of its own number, then from a
+// device queue (tubes ordered longest first, so the queue hands out work in LPT
+// order; where every tube starts at once, in the order of tube_orders), and
+// advances it nsteps steps: for every step, its wavefronts sweep the tube in chunks of 60 cells
 // (the 1-D device sweep of the plain path), the workgroup reduces the CFL
 // rate of the new state, and every thread forms the tube's next timestep
 // dt = C / s itself.  Steps alternate between the tube's cells in U and in
@@ -25,7 +26,7 @@ namespace csh {
 
 struct BatchArgs {
     const int64_t* offsets;  // [ntubes + 1]
-    const int* order;        // tubes, longest first
+    const int* order;        // tubes in the order they are handed out
     int* counter;            // queue head
     double* U;               // [6][N]
     double* Uw;              // [6][N]
@@ -66,12 +67,8 @@ __global__ __launch_bounds__(NT) void batch_kernel(BatchArgs a)
     const int lane = threadIdx.x & 63, wave = wave_in_block();  // wave-uniform chunk loop
     const size_t plane = (size_t)a.N;
 
-    for (;;) {
-        if (threadIdx.x == 0) s_q = atomicAdd(a.counter, 1);
-        __syncthreads();
-        const int q = s_q;
-        __syncthreads();
-        if (q >= a.ntubes) break;  // uniform: every thread read the same q
+    int q = blockIdx.x;  // the first tube by number, so that the order decides who shares a compute unit
+    while (q < a.ntubes) {  // uniform: every thread read the same q
         const int k = a.order[q];
         const int64_t off = a.offsets[k];
         const int n = (int)(a.offsets[k + 1] - off);
@@ -117,6 +114,10 @@ __global__ __launch_bounds__(NT) void batch_kernel(BatchArgs a)
             __syncthreads();
         }
         if (__any(bad) && lane == 0) raise_flag(a.flag);
+        if (threadIdx.x == 0) s_q = (int)gridDim.x + atomicAdd(a.counter, 1);
+        __syncthreads();
+        q = __builtin_amdgcn_readfirstlane(s_q);
+        __syncthreads();
     }
 }
 
@@ -160,7 +161,7 @@ struct csh_batch {
     int64_t N = 0;
     hipStream_t stream = nullptr;
     int64_t* offsets = nullptr;
-    int* order = nullptr;
+    int* order = nullptr;  // the two orders of tube_orders
     int* counter = nullptr;
     csh::HostCell* cell = nullptr;  // pinned: the non-physical flag
     int best_threads = 256;
@@ -170,18 +171,51 @@ struct csh_batch {
 
 namespace {
 
+// The tubes longest first, then the order for launches that start every tube at
+// once: the same, but every second layer of ncu tubes reversed.  Workgroups b and
+// b + ncu share a compute unit (the dispatcher fills the chip in layers), so the
+// longest tube of the first layer runs beside the shortest of the second and every
+// compute unit has about the same number of cells.  With the tubes taken in the
+// order the workgroups happened to start, 512 tubes of 128-4096 cells and 200 steps
+// took 4.9 ms with 512 threads, 3.37 with 1024 (one tube after another on a compute
+// unit), now 3.17 and 3.22; 400 tubes, 256 threads 1660 -> 1225 us; 700 tubes 790 -> 600.
+std::vector<int> tube_orders(const std::vector<int>& len, int ncu)
+{
+    const int n = (int)len.size();
+    std::vector<int> order(n);
+    std::iota(order.begin(), order.end(), 0);
+    std::stable_sort(order.begin(), order.end(), [&](int a, int c) { return len[a] > len[c]; });
+    order.resize(2 * (size_t)n);
+    for (int lo = 0; lo < n; lo += ncu) {
+        const auto first = order.begin() + lo, last = order.begin() + std::min(lo + ncu, n), to = first + n;
+        if (lo / ncu % 2 == 0) std::copy(first, last, to);
+        else std::reverse_copy(first, last, to);
+    }
+    return order;
+}
+
+// Workgroup size of a batch that is not tuned: 512 threads where every tube starts
+// at once and has a chunk of 60 cells for each of the eight wavefronts, or a compute
+// unit to itself; else 256 (us per run, 256 / 512: 24 tubes of 128-300 cells 227 /
+// 203, 256 of 128-2000 428 / 347, 512 of 128-4096 3740 / 3170, 500 of 128-300
+// 248 / 278, 512 of 128-700 393 / 398, 700 of 128-1000 600 / 640).
+int default_threads(int ntubes, int64_t cells, int ncu)
+{
+    return ntubes <= ncu || (ntubes <= 2 * ncu && cells >= 8LL * csh::kStrip * ntubes) ? 512 : 256;
+}
+
 bool valid_threads(int t) { return t == 64 || t == 128 || t == 256 || t == 512 || t == 1024; }
 
-csh::BatchArgs batch_args(csh_batch* b, int nsteps, double cfl, void* U, void* Uw, double* dt_out)
+csh::BatchArgs batch_args(csh_batch* b, int blocks, int nsteps, double cfl, void* U, void* Uw, double* dt_out)
 {
     csh::BatchArgs a{};
     a.offsets = b->offsets;
-    a.order = b->order;
     a.counter = b->counter;
     a.U = static_cast<double*>(U);
     a.Uw = static_cast<double*>(Uw);
     a.dt_out = dt_out;
     a.N = b->N;
+    a.order = b->order + (blocks >= b->ntubes ? b->ntubes : 0);
     a.ntubes = b->ntubes;
     a.nsteps = nsteps;
     a.cfl = cfl;
@@ -206,12 +240,15 @@ extern "C" int csh_batch_init(csh_batch** out, int ntubes, const int64_t* offset
         if (l < 1 || l > (1LL << 30)) return csh_fail(CSH_ERR_ARG, "every tube needs 1 .. 2^30 cells");
         len[k] = (int)l;
     }
-    std::vector<int> order(ntubes);
-    std::iota(order.begin(), order.end(), 0);
-    std::stable_sort(order.begin(), order.end(), [&](int a, int c) { return len[a] > len[c]; });
+    int dev = 0, ncu = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || ncu < 1)
+        ncu = 256;
+    const std::vector<int> order = tube_orders(len, ncu);
 
     csh_batch* b = new csh_batch;
     b->ntubes = ntubes;
+    b->best_threads = default_threads(ntubes, offsets[ntubes], ncu);
     b->N = offsets[ntubes];
     b->max_len = *std::max_element(len.begin(), len.end());
     b->stream = static_cast<hipStream_t>(stream);
@@ -220,11 +257,11 @@ extern "C" int csh_batch_init(csh_batch** out, int ntubes, const int64_t* offset
         return code;
     };
     if (hipMalloc(&b->offsets, sizeof(int64_t) * (ntubes + 1)) != hipSuccess ||
-        hipMalloc(&b->order, sizeof(int) * ntubes) != hipSuccess || hipMalloc(&b->counter, sizeof(int)) != hipSuccess ||
+        hipMalloc(&b->order, sizeof(int) * order.size()) != hipSuccess || hipMalloc(&b->counter, sizeof(int)) != hipSuccess ||
         !(b->cell = csh::acquire_cell()))
         return cleanup(csh_fail(CSH_ERR_HIP, "allocation of the batch tables failed"));
     hipError_t e = hipMemcpyAsync(b->offsets, offsets, sizeof(int64_t) * (ntubes + 1), hipMemcpyHostToDevice, b->stream);
-    if (e == hipSuccess) e = hipMemcpyAsync(b->order, order.data(), sizeof(int) * ntubes, hipMemcpyHostToDevice, b->stream);
+    if (e == hipSuccess) e = hipMemcpyAsync(b->order, order.data(), sizeof(int) * order.size(), hipMemcpyHostToDevice, b->stream);
     if (e == hipSuccess)
         e = csh::launch_init<double>(static_cast<const double*>(W), static_cast<double*>(U), b->N, &b->cell->flag, b->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(b->stream);
@@ -246,7 +283,7 @@ extern "C" int csh_batch_run(csh_batch* b, int nsteps, double cfl, void* U, void
         b->blocks = std::min(b->ntubes, csh::resident_blocks(threads));
         b->blocks_threads = threads;
     }
-    CSH_HIP(csh::launch_batch(batch_args(b, nsteps, cfl, U, U_work, dt_out), threads, b->blocks, b->stream));
+    CSH_HIP(csh::launch_batch(batch_args(b, b->blocks, nsteps, cfl, U, U_work, dt_out), threads, b->blocks, b->stream));
     return CSH_OK;
 }
 
@@ -343,7 +380,7 @@ extern "C" int csh_batch_autotune(csh_batch* b, int probe_steps, double cfl, con
     int best = 0;
     for (int t : cands) {
         const int blocks = std::min(b->ntubes, csh::resident_blocks(t));
-        const auto a = batch_args(b, probe_steps, cfl, A, B, nullptr);
+        const auto a = batch_args(b, blocks, probe_steps, cfl, A, B, nullptr);
         float ms = 0;
         hipError_t e = hipMemcpyAsync(A, U, bytes, hipMemcpyDeviceToDevice, b->stream);
         if (e == hipSuccess) e = csh::launch_batch(a, t, blocks, b->stream);  // warm
