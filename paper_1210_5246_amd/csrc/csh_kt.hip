@@ -270,8 +270,10 @@ __global__ __launch_bounds__(64 * kWaves) void kt_fused_kernel(StepArgs<T> p)
 // one after the other on one wavefront per SIMD; here that is four rows per eight
 // wavefronts, and the eight share the rows of both stages: 100^2 15.5 -> 9.4 us per
 // step, 512^2 24.5 -> 18.9, 1000 x 700 33.0 -> 30.8 (FP32 13.3 -> 7.4, 21.4 -> 14.4,
-// 26.4 -> 22.2).  Bound by the latency of a wavefront's few rows on small grids, by FP64
-// issue (0.9 of it) on the larger.  One workgroup on a CU in FP64 (LDS), two in FP32;
+// 26.4 -> 22.2).  Bound by the latency of a wavefront's few rows on small grids; on the
+// larger ones FP64 issue takes 18 of 30 us (1000 x 700: 10.1 M wave instructions) and
+// the wavefronts wait 31% of their cycles (two on a SIMD, the uneven shares at the
+// barrier and the end).  One workgroup on a CU in FP64 (LDS), two in FP32;
 // twelve wavefronts measured 5% slower (each adds a face per stage), sixteen spill.
 constexpr int kBlockWaves = 8;
 constexpr int kBlockCols = 60;  // U* columns kept: lanes 2..61
