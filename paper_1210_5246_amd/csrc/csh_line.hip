@@ -98,18 +98,21 @@ __global__ __launch_bounds__(64 * kMaxWaves) void line_run_kernel(LineArgs<T> p)
         if (threadIdx.x == 0 && p.dt_log) p.dt_log[k] = dt;
         t += dt;
         const int b = SCHEME == 2 ? 0 : k & 1;
+        // rounded as a single step's factors dt / dx and dt / (2 dx) (halving is exact), not as
+        // dt * idx: csh_step repeats a run's states bit for bit, as the reverse pass does
+        const double q = dt / p.dx;
         Cons<T> Un;
         if constexpr (SCHEME == 2) {
             // the midpoint state through buffer 1, then the full step (coefficients: the fluxes are 2H)
             Cons<T> F = kt_flux2_1d(U);
-            const Cons<T> Us = update(U, T(0.25 * (dt * idx)), F, lane_shift<-1>(F));
+            const Cons<T> Us = update(U, T(0.25 * q), F, lane_shift<-1>(F));
             if (own) put(1, Us);
             __syncthreads();
             F = kt_flux2_1d(get(1));
-            Un = update(U, T(0.5 * (dt * idx)), F, lane_shift<-1>(F));
+            Un = update(U, T(0.5 * q), F, lane_shift<-1>(F));
         } else {
-            const Cons<T> F = flux_1d<T, SCHEME>(U, T(0.5 * (dt * idx)));
-            Un = update(U, T(dt * idx), F, lane_shift<-1>(F));
+            const Cons<T> F = flux_1d<T, SCHEME>(U, T(0.5 * q));
+            Un = update(U, T(q), F, lane_shift<-1>(F));
         }
         kick(Un, p, dt, c, 0, false);
         if (own) {
