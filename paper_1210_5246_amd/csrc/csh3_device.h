@@ -69,26 +69,25 @@ CSH_HD V10 to_cons(const V10& w)
 // base - k A d with A the primitive Jacobian along N:
 //   A d = (u_n d_rho + rho d_un, u_n d_ui + d_Pin / rho,
 //          u_n d_Pij + P_ij d_un + P_in d_uj + P_jn d_ui),
-// k folded into the factors the components share.
+// summed before it leaves the base, which is so rounded once (as in two dimensions).
 template <int N>
 CSH_HD V10 sub_jac(const V10& base, double k, const V10& w, double ir, const V10& d)
 {
     constexpr int t1 = Axes<N>::t1, t2 = Axes<N>::t2;
     constexpr int nn = P(N, N), n1 = P(N, t1), n2 = P(N, t2), s11 = P(t1, t1), s12 = P(t1, t2), s22 = P(t2, t2);
-    const double un = w.v[1 + N], ku = k * un, kir = k * ir;
-    const double dn = k * d.v[1 + N], d1 = k * d.v[1 + t1], d2 = k * d.v[1 + t2];
-    const double p1 = 2.0 * w.v[n1], p2 = 2.0 * w.v[n2];
+    const double un = w.v[1 + N], dn = d.v[1 + N], d1 = d.v[1 + t1], d2 = d.v[1 + t2];
+    const double p1 = 2.0 * w.v[n1], p2 = 2.0 * w.v[n2], p3 = 3.0 * w.v[nn];
     V10 o;
-    o.v[0] = base.v[0] - ku * d.v[0] - w.v[0] * dn;
-    o.v[1 + N] = base.v[1 + N] - un * dn - kir * d.v[nn];
-    o.v[1 + t1] = base.v[1 + t1] - un * d1 - kir * d.v[n1];
-    o.v[1 + t2] = base.v[1 + t2] - un * d2 - kir * d.v[n2];
-    o.v[nn] = base.v[nn] - ku * d.v[nn] - (3.0 * w.v[nn]) * dn;
-    o.v[n1] = base.v[n1] - ku * d.v[n1] - p1 * dn - w.v[nn] * d1;
-    o.v[n2] = base.v[n2] - ku * d.v[n2] - p2 * dn - w.v[nn] * d2;
-    o.v[s11] = base.v[s11] - ku * d.v[s11] - w.v[s11] * dn - p1 * d1;
-    o.v[s12] = base.v[s12] - ku * d.v[s12] - w.v[s12] * dn - w.v[n1] * d2 - w.v[n2] * d1;
-    o.v[s22] = base.v[s22] - ku * d.v[s22] - w.v[s22] * dn - p2 * d2;
+    o.v[0] = base.v[0] - k * (un * d.v[0] + w.v[0] * dn);
+    o.v[1 + N] = base.v[1 + N] - k * (un * dn + ir * d.v[nn]);
+    o.v[1 + t1] = base.v[1 + t1] - k * (un * d1 + ir * d.v[n1]);
+    o.v[1 + t2] = base.v[1 + t2] - k * (un * d2 + ir * d.v[n2]);
+    o.v[nn] = base.v[nn] - k * (un * d.v[nn] + p3 * dn);
+    o.v[n1] = base.v[n1] - k * (un * d.v[n1] + p1 * dn + w.v[nn] * d1);
+    o.v[n2] = base.v[n2] - k * (un * d.v[n2] + p2 * dn + w.v[nn] * d2);
+    o.v[s11] = base.v[s11] - k * (un * d.v[s11] + w.v[s11] * dn + p1 * d1);
+    o.v[s12] = base.v[s12] - k * (un * d.v[s12] + w.v[s12] * dn + w.v[n1] * d2 + w.v[n2] * d1);
+    o.v[s22] = base.v[s22] - k * (un * d.v[s22] + w.v[s22] * dn + p2 * d2);
     return o;
 }
 
