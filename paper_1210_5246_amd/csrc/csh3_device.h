@@ -244,13 +244,10 @@ CSH_HD V10 hll(const V10& wl, const V10& wr)
 // CFL rate: sum over the axes of (|u_k| + sqrt(3 P_kk / rho)) / h_k
 CSH_HD double signal_rate(const V10& w, const double ih[3])
 {
-    const double ir = rcp(w.v[0]);
+    const double ir3 = 3.0 * rcp(w.v[0]);
     double s = 0.0;
 #pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        const double c = sqrt_pos(w.v[P(k, k)] * ir);
-        s = s + fabs(w.v[1 + k]) * ih[k] + c * (1.7320508075688772935 * ih[k]);
-    }
+    for (int k = 0; k < 3; ++k) s = s + fabs(w.v[1 + k]) * ih[k] + sqrt_pos(w.v[P(k, k)] * ir3) * ih[k];
     return s;
 }
 

@@ -489,13 +489,16 @@ __device__ __forceinline__ void kick(Cons<T>& U, const P& p, double dt, int i, i
 // CFL rate of a cell (the timestep is C / max over cells of this):
 // (|u| + a_x)/dx + (|v| + a_y)/dy, 1-D: (|u| + a_x)/dx.  Evaluated in the
 // state's precision (FP32 for an FP32 state: a relative rounding of ~1e-7 in
-// a quantity that only sets the timestep) and returned as a double.
+// a quantity that only sets the timestep) and returned as a double.  The 3 stays
+// under the root: sqrt(3) / dx, rounded twice, turned every timestep of a grid the
+// same way (rms error of 20 steps' timesteps 3.4e-16 -> 4.1e-16, with the
+// Kurganov-Tadmor step 3.2e-16 -> 4.6e-16), for one multiplication less.
 template <typename T, bool TWOD>
 CSH_HD double signal_rate(const Prim<T>& w, double idx, double idy)
 {
-    const T ir = rcp(w.r), s3 = T(1.7320508075688772935);
-    T s = fabs(w.u) * T(idx) + sqrt_pos(w.pxx * ir) * (s3 * T(idx));
-    if (TWOD) s = s + fabs(w.v) * T(idy) + sqrt_pos(w.pyy * ir) * (s3 * T(idy));
+    const T ir3 = T(3) * rcp(w.r);
+    T s = fabs(w.u) * T(idx) + sqrt_pos(w.pxx * ir3) * T(idx);
+    if (TWOD) s = s + fabs(w.v) * T(idy) + sqrt_pos(w.pyy * ir3) * T(idy);
     return double(s);
 }
 
