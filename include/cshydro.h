@@ -310,9 +310,10 @@ int csh_batch_status(csh_batch *b);
  * The choice is persisted: one line "<key> <threads>" per batch shape in the
  * file CSH_TUNE_CACHE names (the value "off" disables it; default
  * $HOME/.cache/cshydro/batch_autotune.txt), with key
- * "arch=<gcnArchName>;cus=<compute units>;tubes=<ntubes>;cells=<total cells>;maxlen=<longest tube>";
- * a later call for the same shape on the same kind of device takes the
- * recorded size without probing (the last record of a key wins).
+ * "schedule=<n>;arch=<gcnArchName>;cus=<compute units>;tubes=<ntubes>;cells=<total cells>;maxlen=<longest tube>",
+ * n the version of the library's batch schedule; a later call for the same
+ * shape on the same kind of device takes the recorded size without probing (the
+ * last record of a key wins), but not one made with another schedule.
  */
 int csh_batch_autotune(csh_batch *b, int probe_steps, double cfl, const void *U, int *best_threads);
 

@@ -300,7 +300,7 @@ namespace {
 // ---- persisted choices of the autotuner --------------------------------------------------------
 //
 // One line per tuned batch shape, "<key> <threads>", key =
-// "arch=<gcnArchName>;cus=<compute units>;tubes=<ntubes>;cells=<total cells>;maxlen=<longest tube>".
+// "schedule=<n>;arch=<gcnArchName>;cus=<compute units>;tubes=<ntubes>;cells=<total cells>;maxlen=<longest tube>".
 // The file is CSH_TUNE_CACHE if set ("off" disables the cache), else
 // $HOME/.cache/cshydro/batch_autotune.txt.  Unreadable or malformed lines are
 // ignored; a failed write loses nothing but the record.
@@ -316,14 +316,19 @@ std::string tune_cache_path()
     return dir + "/batch_autotune.txt";
 }
 
+// Raised whenever batch_kernel, its launch or tube_orders changes: a size that an
+// earlier library timed need not be the fastest any more (512 tubes of 128-4096
+// cells took 1024 threads before their second layer was reversed, 512 since).
+constexpr int kSchedule = 2;
+
 std::string tune_key(const csh_batch* b)
 {
     int dev = 0;
     hipDeviceProp_t prop{};
     if (hipGetDevice(&dev) != hipSuccess || hipGetDeviceProperties(&prop, dev) != hipSuccess) return std::string();
     char buf[512];
-    std::snprintf(buf, sizeof buf, "arch=%s;cus=%d;tubes=%d;cells=%lld;maxlen=%d", prop.gcnArchName,
-                  prop.multiProcessorCount, b->ntubes, (long long)b->N, b->max_len);
+    std::snprintf(buf, sizeof buf, "schedule=%d;arch=%s;cus=%d;tubes=%d;cells=%lld;maxlen=%d", kSchedule,
+                  prop.gcnArchName, prop.multiProcessorCount, b->ntubes, (long long)b->N, b->max_len);
     return std::string(buf);
 }
 
