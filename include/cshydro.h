@@ -250,7 +250,7 @@ int csh_run_dts(csh_grid *h, int nsteps, const double *dts, void *U, void *U_wor
  * argument), external kick included.  U, lam_next: device, read only;
  * lam: device output; all [6][ny][nx] of the handle's dtype (CSH_F64 only).
  * Does not touch the handle's CFL state.  On a 1-D grid the first call allocates
- * a workspace of 66 (nx + 2) + 6 (nx + 4) doubles that the handle keeps until
+ * a workspace of 24 (nx + 2) + 6 (nx + 4) doubles that the handle keeps until
  * csh_destroy; a 2-D grid needs none.  Asynchronous.
  */
 int csh_adjoint_step(csh_grid *h, double dt, const void *U, const void *lam_next, void *lam);

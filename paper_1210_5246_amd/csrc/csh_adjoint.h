@@ -334,6 +334,16 @@ CSH_HD void set_step_factors(AdjArgs& a)
     a.cy = a.ey > 1 ? a.dt / a.dy : 0.0;
 }
 
+// the workspace of a 1-D grid: the two x-face states of every extended cell, their
+// adjoints, the sums per padded position
+CSH_HD size_t workspace_1d(int nx) { return 24 * (size_t)(nx + 2) + 6 * (size_t)(nx + 4); }
+CSH_HD void set_workspace_1d(AdjArgs& a, double* ws)
+{
+    a.FS = ws;
+    a.FSb = ws + 12 * (size_t)a.ex;
+    a.XS = ws + 24 * (size_t)a.ex;
+}
+
 enum { XHI = 0, XLO = 1, YHI = 2, YLO = 3 };
 enum { SELF = 0, DOWN = 1, UP = 2 };
 

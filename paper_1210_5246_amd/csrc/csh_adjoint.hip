@@ -238,8 +238,7 @@ __global__ __launch_bounds__(256) void init_adjoint_kernel(const double* W, cons
 
 size_t csh_adjoint_workspace_doubles(int nx, int ny)
 {
-    if (ny > 1) return 0;
-    return (size_t)(nx + 2) * 6 * (4 + 4 + 3) + (size_t)(nx + 4) * 6;
+    return ny > 1 ? 0 : csh::workspace_1d(nx);
 }
 
 int csh_adjoint_impl(csh_grid_view v, double dt, const void* U, const void* lam_next, void* lam, double* ws,
@@ -265,7 +264,6 @@ int csh_adjoint_impl(csh_grid_view v, double dt, const void* U, const void* lam_
     a.U = static_cast<const double*>(U);
     a.lam1 = static_cast<const double*>(lam_next);
     a.lam0 = static_cast<double*>(lam);
-    const size_t ne = (size_t)a.ex * a.ey;
     if (twod) {
         // Blocks of 16 columns, two on a CU at a time, or of 32, one on a CU: the wider
         // ones trace fewer cells twice (28 x 12 outputs of 32 x 16 cells against
@@ -280,11 +278,8 @@ int csh_adjoint_impl(csh_grid_view v, double dt, const void* U, const void* lam_
         else
             adjoint_fused_kernel<32><<<(unsigned)n32, 32 * kF_Y, 0, s>>>(a, (int)tiles(v.nx, 28));
     } else {
-        a.FS = ws;
-        a.FSb = ws + 24 * ne;
-        a.Cs = ws + 48 * ne;
-        a.XS = ws + 66 * ne;
-        const unsigned be = (unsigned)((ne + 255) / 256), bi = (unsigned)(((size_t)v.nx + 255) / 256);
+        set_workspace_1d(a, ws);
+        const unsigned be = (unsigned)(((size_t)a.ex + 255) / 256), bi = (unsigned)(((size_t)v.nx + 255) / 256);
         const unsigned bx = (unsigned)(((a.nx + 4 + kXsOwned - 1) / kXsOwned + 3) / 4);
         adjoint_kernel<1><<<be, 256, 0, s>>>(a);
         adjoint_kernel<2><<<be, 256, 0, s>>>(a);

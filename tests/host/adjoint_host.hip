@@ -72,11 +72,16 @@ extern "C" int host_adjoint_step(int nx, int ny, int bcx, int bcy, double dx, do
     AdjArgs a = make_args(nx, ny, bcx, bcy, dx, dy, dt, vc, rc, x0, y0, U);
     const size_t ne = (size_t)a.ex * a.ey;
     // NaN-filled: every slot the reverse pass reads must have been written by it
-    std::vector<double> ws(66 * ne + 6 * (size_t)(nx + 4) * a.ey, std::numeric_limits<double>::quiet_NaN());
-    a.FS = ws.data();
-    a.FSb = ws.data() + 24 * ne;
-    a.Cs = ws.data() + 48 * ne;
-    a.XS = ws.data() + 66 * ne;
+    std::vector<double> ws(ny > 1 ? 66 * ne + 6 * (size_t)(nx + 4) * a.ey : workspace_1d(nx),
+                           std::numeric_limits<double>::quiet_NaN());
+    if (ny > 1) {
+        a.FS = ws.data();
+        a.FSb = ws.data() + 24 * ne;
+        a.Cs = ws.data() + 48 * ne;
+        a.XS = ws.data() + 66 * ne;
+    } else {
+        set_workspace_1d(a, ws.data());  // the device's own layout, no double more
+    }
     a.lam1 = lam1;
     a.lam0 = lam0;
     if (ny > 1) adjoint_loops<true>(a);
