@@ -1,6 +1,7 @@
 // Reverse-mode pieces of the sweep (FP64): vector-Jacobian products of every
 // stage of csh_device.h, written out by hand statement by statement in reverse
-// order, and the per-cell bodies of the adjoint kernels.
+// order, and the bodies of the adjoint kernels: per cell (1-D) and per thread of a
+// block (2-D).
 //
 // Conventions: a function foo_vjp(inputs..., ybar, xbar...) ADDS the
 // contribution of ybar to the adjoints xbar of foo's inputs.  At the kinks of
@@ -306,11 +307,10 @@ CSH_HD C kick_vjp(const C& lb, double h, double ax, double ay)
     return o;
 }
 
-// ---- per-cell bodies of the adjoint kernels ----------------------------------------------
+// ---- bodies of the adjoint kernels ---------------------------------------------------------
 
 struct AdjArgs {
     int nx, ny, bcx, bcy;
-    int ex, ey;          // extended grid: ex = nx + 2, ey = ny + 2 (1-D: 1)
     double dx, dy, dt;
     double kx, ky;       // dt / (2 dx), dt / (2 dy) (1-D: ky = 0)
     double cx, cy;       // dt / dx, dt / dy
@@ -318,34 +318,30 @@ struct AdjArgs {
     const double* U;     // [6][ny][nx]
     const double* lam1;  // lam^{n+1}
     double* lam0;        // lam^n
-    double* FS;          // [4 faces][6][ext]
-    double* FSb;         // [4][6][ext]
-    double* Cs;          // [3 roles][6][ext]: the y part's shares (SELF, DOWN, UP)
-    double* XS;          // [6][ey][nx + 4]: per padded position (column -2 .. nx + 1 of an extended
-                         // row), SELF and the x part's shares summed
+    // 1-D, over the nx + 2 extended cells
+    double* FS;          // [high, low][6][nx + 2]: face states
+    double* FSb;         // [high, low][6][nx + 2]: their adjoints
+    double* XS;          // [6][nx + 4]: per padded position (-2 .. nx + 1), the shares summed
 };
 
 // the step factors of AdjArgs from dt, dx, dy (IEEE divisions, once per call)
 CSH_HD void set_step_factors(AdjArgs& a)
 {
     a.kx = a.dt / (2.0 * a.dx);
-    a.ky = a.ey > 1 ? a.dt / (2.0 * a.dy) : 0.0;
+    a.ky = a.ny > 1 ? a.dt / (2.0 * a.dy) : 0.0;
     a.cx = a.dt / a.dx;
-    a.cy = a.ey > 1 ? a.dt / a.dy : 0.0;
+    a.cy = a.ny > 1 ? a.dt / a.dy : 0.0;
 }
 
-// the workspace of a 1-D grid: the two x-face states of every extended cell, their
-// adjoints, the sums per padded position
+// the workspace of a 1-D grid
 CSH_HD size_t workspace_1d(int nx) { return 24 * (size_t)(nx + 2) + 6 * (size_t)(nx + 4); }
 CSH_HD void set_workspace_1d(AdjArgs& a, double* ws)
 {
+    const size_t ne = (size_t)a.nx + 2;
     a.FS = ws;
-    a.FSb = ws + 12 * (size_t)a.ex;
-    a.XS = ws + 24 * (size_t)a.ex;
+    a.FSb = ws + 12 * ne;
+    a.XS = ws + 24 * ne;
 }
-
-enum { XHI = 0, XLO = 1, YHI = 2, YLO = 3 };
-enum { SELF = 0, DOWN = 1, UP = 2 };
 
 CSH_HD P load_p(const double* B, size_t plane, size_t slot, size_t idx)
 {
@@ -363,6 +359,26 @@ CSH_HD void store_p(double* B, size_t plane, size_t slot, size_t idx, const P& v
     b[5 * plane + idx] = v.pyy;
 }
 
+CSH_HD C csub(const C& p, const C& q, double s)
+{
+    return {s * (p.r - q.r), s * (p.mx - q.mx), s * (p.my - q.my), s * (p.exx - q.exx), s * (p.exy - q.exy),
+            s * (p.eyy - q.eyy)};
+}
+
+// the transpose of the kick at (x, y)
+CSH_HD C kick_adjoint(const AdjArgs& a, const C& l, double x, double y)
+{
+    const double f = -a.vc2 * rcp(x * x + y * y + a.rc2);
+    return kick_vjp(l, a.dt, f * x, f * y);
+}
+
+// ---- 1-D, per cell --------------------------------------------------------------------------
+//
+// Extended cell i in [-1, nx] lies at index i + 1 of the workspace's arrays; XHI and
+// XLO are its high and low face.
+
+enum { XHI = 0, XLO = 1 };
+
 // map_index for -2n <= i < 3n (the reverse pass reads at most two cells past
 // the extended ring, so any n >= 1 is covered): no division
 CSH_HD int map_wide(int i, int n, int bc)
@@ -377,136 +393,58 @@ CSH_HD int map_wide(int i, int n, int bc)
     return i < 0 ? 0 : (i >= n ? n - 1 : i);
 }
 
-// primitive state of the (possibly ghost) cell (i, j)
-CSH_HD P prim_at(const AdjArgs& a, int i, int j, bool twod)
+// primitive state of the (possibly ghost) cell i
+CSH_HD P prim_at(const AdjArgs& a, int i)
 {
-    const int gi = map_wide(i, a.nx, a.bcx);
-    const int gj = twod ? map_wide(j, a.ny, a.bcy) : 0;
-    return to_prim(load_cons<double>(a.U, (size_t)a.nx * a.ny, (size_t)gj * a.nx + gi));
+    return to_prim(load_cons<double>(a.U, (size_t)a.nx, (size_t)map_wide(i, a.nx, a.bcx)));
 }
 
-CSH_HD size_t ext_index(const AdjArgs& a, int i, int j) { return (size_t)(j + (a.ey > 1 ? 1 : 0)) * a.ex + (i + 1); }
-
-// lam' of interior cell (i, j): the kick's transpose applied to lam^{n+1}
-CSH_HD C lam_prime(const AdjArgs& a, int i, int j, bool twod)
+// lam' of interior cell i: the kick's transpose applied to lam^{n+1}
+CSH_HD C lam_prime(const AdjArgs& a, int i)
 {
-    const C l = load_cons<double>(a.lam1, (size_t)a.nx * a.ny, (size_t)j * a.nx + i);
-    if (a.vc2 == 0.0) return l;
-    const double x = a.x0 + (i + 0.5) * a.dx;
-    const double y = twod ? a.y0 + (j + 0.5) * a.dy : 0.0;
-    const double f = -a.vc2 * rcp(x * x + y * y + a.rc2);
-    return kick_vjp(l, a.dt, f * x, f * y);
+    const C l = load_cons<double>(a.lam1, (size_t)a.nx, (size_t)i);
+    return a.vc2 == 0.0 ? l : kick_adjoint(a, l, a.x0 + (i + 0.5) * a.dx, 0.0);
 }
 
-template <bool TWOD>
-CSH_HD void faces_cell(const AdjArgs& a, int i, int j)
+CSH_HD void faces_cell(const AdjArgs& a, int i)
 {
-    const double kx = a.kx, ky = TWOD ? a.ky : 0.0;
-    const P W0 = prim_at(a, i, j, TWOD);
-    const P Wl = prim_at(a, i - 1, j, TWOD), Wr = prim_at(a, i + 1, j, TWOD);
-    const P Wm = TWOD ? prim_at(a, i, j - 1, TWOD) : W0, Wp = TWOD ? prim_at(a, i, j + 1, TWOD) : W0;
-    const Faces<double> f = face_states<double, TWOD>(W0, rcp(W0.r), Wl, Wr, Wm, Wp, kx, ky);
-    const size_t ne = (size_t)a.ex * a.ey, e = ext_index(a, i, j);
+    const P W0 = prim_at(a, i);
+    const Faces<double> f =
+        face_states<double, false>(W0, rcp(W0.r), prim_at(a, i - 1), prim_at(a, i + 1), W0, W0, a.kx, 0.0);
+    const size_t ne = (size_t)a.nx + 2, e = (size_t)(i + 1);
     store_p(a.FS, ne, XHI, e, f.xhi);
     store_p(a.FS, ne, XLO, e, f.xlo);
-    if (TWOD) {
-        store_p(a.FS, ne, YHI, e, f.yhi);
-        store_p(a.FS, ne, YLO, e, f.ylo);
-    }
 }
 
-CSH_HD C csub(const C& p, const C& q, double s)
+CSH_HD void hll_cell(const AdjArgs& a, int i)
 {
-    return {s * (p.r - q.r), s * (p.mx - q.mx), s * (p.my - q.my), s * (p.exx - q.exx), s * (p.exy - q.exy),
-            s * (p.eyy - q.eyy)};
-}
-
-template <bool TWOD>
-CSH_HD void hll_cell(const AdjArgs& a, int i, int j)
-{
-    const size_t ne = (size_t)a.ex * a.ey;
-    const size_t e = ext_index(a, i, j);
+    const size_t ne = (size_t)a.nx + 2, e = (size_t)(i + 1);
     const C z = zero_c();
-    // face-state adjoint slots of this cell that no face writes (the outer
-    // faces of the ring) are cleared here; every other slot is written by the
-    // one face that uses that state
-    const bool jin = !TWOD || (j >= 0 && j < a.ny), iin = i >= 0 && i < a.nx;
-    if (!(i <= a.nx - 1 && jin)) store_p(a.FSb, ne, XHI, e, zero_p());
-    if (!(i >= 0 && jin)) store_p(a.FSb, ne, XLO, e, zero_p());
-    if (TWOD) {
-        if (!(j <= a.ny - 1 && iin)) store_p(a.FSb, ne, YHI, e, zero_p());
-        if (!(j >= 0 && iin)) store_p(a.FSb, ne, YLO, e, zero_p());
-    }
-    // x face i + 1/2 in an interior row: between extended cells (i, j) and (i + 1, j)
-    if (i <= a.nx - 1 && (!TWOD || (j >= 0 && j < a.ny))) {
-        const int jj = TWOD ? j : 0;
-        const C lp = (i + 1 <= a.nx - 1) ? lam_prime(a, i + 1, jj, TWOD) : z;
-        const C lm = (i >= 0) ? lam_prime(a, i, jj, TWOD) : z;
+    // the outer faces of the ring, which no flux uses; every other slot is written
+    // by the one face that uses that state
+    if (i > a.nx - 1) store_p(a.FSb, ne, XHI, e, zero_p());
+    if (i < 0) store_p(a.FSb, ne, XLO, e, zero_p());
+    // face i + 1/2: between extended cells i and i + 1
+    if (i <= a.nx - 1) {
+        const C lp = (i + 1 <= a.nx - 1) ? lam_prime(a, i + 1) : z;
+        const C lm = (i >= 0) ? lam_prime(a, i) : z;
         const C Fb = csub(lp, lm, a.cx);
         P wlb = zero_p(), wrb = zero_p();
         hll_vjp(load_p(a.FS, ne, XHI, e), load_p(a.FS, ne, XLO, e + 1), Fb, wlb, wrb);
         store_p(a.FSb, ne, XHI, e, wlb);
         store_p(a.FSb, ne, XLO, e + 1, wrb);
     }
-    if (TWOD && j <= a.ny - 1 && i >= 0 && i < a.nx) {
-        const C lp = (j + 1 <= a.ny - 1) ? lam_prime(a, i, j + 1, true) : z;
-        const C lm = (j >= 0) ? lam_prime(a, i, j, true) : z;
-        const C Gb = csub(lp, lm, a.cy);
-        P wlb = zero_p(), wrb = zero_p();
-        hll_vjp(swap(load_p(a.FS, ne, YHI, e)), swap(load_p(a.FS, ne, YLO, e + a.ex)), swap(Gb), wlb, wrb);
-        store_p(a.FSb, ne, YHI, e, swapb(wlb));
-        store_p(a.FSb, ne, YLO, e + a.ex, swapb(wrb));
-    }
 }
 
-CSH_HD Faces<double> load_face_adjoints(const AdjArgs& a, size_t ne, size_t e, bool twod)
+// the face-state reverse pass of extended cell i: b0 its share of itself, bl, br its
+// shares of positions i - 1, i + 1
+CSH_HD void cells_x_vjp(const AdjArgs& a, int i, P& b0, P& bl, P& br)
 {
-    Faces<double> fb;
-    fb.xhi = load_p(a.FSb, ne, XHI, e);
-    fb.xlo = load_p(a.FSb, ne, XLO, e);
-    if (twod) {
-        fb.yhi = load_p(a.FSb, ne, YHI, e);
-        fb.ylo = load_p(a.FSb, ne, YLO, e);
-    } else {
-        fb.yhi = fb.ylo = zero_p();
-    }
-    return fb;
+    const size_t ne = (size_t)a.nx + 2, e = (size_t)(i + 1);
+    const Faces<double> fb{load_p(a.FSb, ne, XHI, e), load_p(a.FSb, ne, XLO, e), zero_p(), zero_p()};
+    b0 = bl = br = zero_p();
+    face_states_vjp_x<false>(prim_at(a, i), prim_at(a, i - 1), prim_at(a, i + 1), a.kx, fb, b0, bl, br);
 }
-
-// y part of the face-state adjoint of extended cell (i, j) (2-D): slots SELF
-// (its share), DOWN, UP
-CSH_HD void cells_cell_y(const AdjArgs& a, int i, int j)
-{
-    const double ky = a.ky;
-    const size_t ne = (size_t)a.ex * a.ey, e = ext_index(a, i, j);
-    const P W0 = prim_at(a, i, j, true);
-    const P Wm = prim_at(a, i, j - 1, true), Wp = prim_at(a, i, j + 1, true);
-    const Faces<double> fb = load_face_adjoints(a, ne, e, true);
-    P b0 = zero_p(), bm = zero_p(), bp = zero_p();
-    face_states_vjp_y(W0, Wm, Wp, ky, fb, b0, bm, bp);
-    store_p(a.Cs, ne, SELF, e, b0);
-    store_p(a.Cs, ne, DOWN, e, bm);
-    store_p(a.Cs, ne, UP, e, bp);
-}
-
-// x part of extended cell (i, j): b0 = its SELF share (2-D: the y part's plus
-// this part's), bl, br its LEFT and RIGHT shares (to positions i - 1, i + 1)
-template <bool TWOD>
-CSH_HD void cells_x_vjp(const AdjArgs& a, int i, int j, P& b0, P& bl, P& br)
-{
-    const double kx = a.kx;
-    const size_t ne = (size_t)a.ex * a.ey, e = ext_index(a, i, j);
-    const P W0 = prim_at(a, i, j, TWOD);
-    const P Wl = prim_at(a, i - 1, j, TWOD), Wr = prim_at(a, i + 1, j, TWOD);
-    const Faces<double> fb = load_face_adjoints(a, ne, e, TWOD);
-    b0 = TWOD ? load_p(a.Cs, ne, SELF, e) : zero_p();
-    bl = zero_p();
-    br = zero_p();
-    face_states_vjp_x<TWOD>(W0, Wl, Wr, kx, fb, b0, bl, br);
-}
-
-// index of padded position (px, j), px in [-2, nx + 1], j an extended row, in XS
-CSH_HD size_t xs_index(const AdjArgs& a, int px, int j) { return (size_t)(j + (a.ey > 1 ? 1 : 0)) * (a.nx + 4) + (px + 2); }
 
 // positions p in [-2, n+1] (the ghost-padded range the stencil reads) with
 // map(p) == i; returns their count (at most 5)
@@ -525,70 +463,18 @@ CSH_HD int preimages(int i, int n, int bc, int* p)
     return k;
 }
 
-// sum of the shares that land on padded position (pi, pj): the x-part sum of
-// its row (extended rows only) and the y part's DOWN and UP shares of the
-// extended cells above and below
-template <bool TWOD>
-CSH_HD P pad_sum(const AdjArgs& a, int pi, int pj)
+CSH_HD void gather_cell(const AdjArgs& a, int i)
 {
-    const size_t ne = (size_t)a.ex * a.ey, nxs = (size_t)(a.nx + 4) * a.ey;
-    auto in_ext = [&](int i, int j) { return i >= -1 && i <= a.nx && (!TWOD || (j >= -1 && j <= a.ny)); };
-    P s = zero_p();
-    if (!TWOD || (pj >= -1 && pj <= a.ny)) acc(s, load_p(a.XS, nxs, 0, xs_index(a, pi, pj)));
-    if (TWOD) {
-        if (in_ext(pi, pj + 1)) acc(s, load_p(a.Cs, ne, DOWN, ext_index(a, pi, pj + 1)));
-        if (in_ext(pi, pj - 1)) acc(s, load_p(a.Cs, ne, UP, ext_index(a, pi, pj - 1)));
-    }
-    return s;
-}
-
-template <bool TWOD>
-CSH_HD void gather_cell(const AdjArgs& a, int i, int j)
-{
-    int px[5], py[5];
-    const int nx_ = preimages(i, a.nx, a.bcx, px);
-    const int ny_ = TWOD ? preimages(j, a.ny, a.bcy, py) : 1;
-    if (!TWOD) py[0] = 0;
+    int px[5];
+    const int n = preimages(i, a.nx, a.bcx, px);
     P wb = zero_p();
-    for (int u = 0; u < nx_; ++u)
-        for (int v = 0; v < ny_; ++v) acc(wb, pad_sum<TWOD>(a, px[u], py[v]));
-    const size_t plane = (size_t)a.nx * a.ny, c = (size_t)j * a.nx + i;
-    C out = lam_prime(a, i, j, TWOD);
-    to_prim_vjp(load_cons<double>(a.U, plane, c), wb, out);
-    store_cons(a.lam0, plane, c, out);
+    for (int u = 0; u < n; ++u) acc(wb, load_p(a.XS, (size_t)a.nx + 4, 0, (size_t)(px[u] + 2)));
+    C out = lam_prime(a, i);
+    to_prim_vjp(load_cons<double>(a.U, (size_t)a.nx, (size_t)i), wb, out);
+    store_cons(a.lam0, (size_t)a.nx, (size_t)i, out);
 }
 
-// ---- the reverse pass by tiles, on the CPU (2-D) -----------------------------------------
-//
-// The phases of a tiled reverse pass in two kernels, A (faces and fluxes) and B
-// (face states and gather), as bodies a CPU loop over tiles, phases and threads
-// runs (tests/host).  The device runs both phases in one kernel with the same
-// treatment of the boundaries; these bodies show it equal to the per-cell
-// reference above.  Only the face-state adjoints (FSb) pass from A to B.
-//
-// Periodic axes are treated as a pure wrap: a virtual cell outside [0, n) is
-// the wrapped cell (its state, its lam' and its face-state adjoints), every
-// face is a real face, and an output cell gathers only the shares that land on
-// itself.  Outflow axes keep the extended ring (cells -1 and n, lam' = 0
-// outside [0, n)), and the shares landing on ghost positions (-2, -1, n,
-// n + 1) are folded into the boundary cell.  Both are the transpose of the
-// same forward step; they differ from the five-stage pass only in the order
-// of the sums.
-//
-// kernel A: a tile of kA_TX x kA_TY extended cells, one thread per cell
-constexpr int kA_TX = 32, kA_TY = 8, kA_THREADS = kA_TX * kA_TY;
-constexpr int kA_WX = kA_TX + 3, kA_WY = kA_TY + 3;  // states: cells [X0 - 1, X0 + TX + 2)
-constexpr int kA_FX = kA_TX + 1, kA_FY = kA_TY + 1;  // face states: cells [X0, X0 + TX + 1)
-constexpr int kA_NW = kA_WX * kA_WY, kA_NF = kA_FX * kA_FY;
-constexpr int kA_LDS = 6 * kA_NW + 12 * kA_NF;       // doubles of LDS: states, low x and y face states
-
-// kernel B: a tile of kB_W x kB_H virtual cells (four rows per wavefront),
-// the outputs its inner (kB_W - 2) x (kB_H - 2) cells
-constexpr int kB_W = 16, kB_H = 16, kB_THREADS = kB_W * kB_H;
-constexpr int kB_OX = kB_W - 2, kB_OY = kB_H - 2;
-enum { SH_LEFT = 0, SH_RIGHT = 1, SH_DOWN = 2, SH_UP = 3, SH_TOT = 4 };
-constexpr int kB_SX = kB_W + 2, kB_SY = kB_H + 2, kB_NS = kB_SX * kB_SY;  // states: the tile and a ring
-constexpr int kB_LDS = 5 * 6 * kB_THREADS + 6 * kB_NS;  // doubles of LDS (the states after the shares)
+// ---- 2-D, per thread of a block -------------------------------------------------------------
 
 CSH_HD void lds_put(double* L, int stride, int base, int k, const P& v)
 {
@@ -605,215 +491,181 @@ CSH_HD P lds_get(const double* L, int stride, int base, int k)
             L[base + 4 * stride + k], L[base + 5 * stride + k]};
 }
 
-// lam' of a virtual cell: wrapped on periodic axes; zero outside the grid on outflow ones
-CSH_HD C lam_prime_virtual(const AdjArgs& a, int i, int j)
-{
-    if (a.bcx != 0 && (i < 0 || i >= a.nx)) return zero_c();
-    if (a.bcy != 0 && (j < 0 || j >= a.ny)) return zero_c();
-    return lam_prime(a, map_wide(i, a.nx, a.bcx), map_wide(j, a.ny, a.bcy), true);
-}
+// One thread of the 2-D reverse step (adjoint_fused_kernel): a block of BX x 16 cells,
+// its inner (BX - 4) x 12 the outputs, cell (lx, ly) of it this thread's.  The methods
+// are the phases between the kernel's barriers and lane shifts, in its order; they hold
+// all of its indexing (the boundary maps, the ring, the slots in LDS, the ghost folds),
+// so that a CPU loop over blocks, phases and threads runs the same code (tests/host).
+constexpr int kF_Y = 16, kF_OY = kF_Y - 4;
 
-// A1: primitive states of the cells [X0 - 1, X0 + TX + 2) x [Y0 - 1, Y0 + TY + 2)
-// (coordinates past [-2, n + 1] are clamped into it: those cells only feed
-// face states of cells beyond the extended ring, which no face uses)
-CSH_HD void tileA_states(const AdjArgs& a, int X0, int Y0, int t, double* L)
-{
-    for (int k = t; k < kA_NW; k += kA_THREADS) {
-        const int i0 = X0 - 1 + k % kA_WX, j0 = Y0 - 1 + k / kA_WX;
-        const int i = i0 < -2 ? -2 : (i0 > a.nx + 1 ? a.nx + 1 : i0);
-        const int j = j0 < -2 ? -2 : (j0 > a.ny + 1 ? a.ny + 1 : j0);
-        lds_put(L, kA_NW, 0, k, prim_at(a, i, j, true));
-    }
-}
+template <int BX>
+struct AdjointThread {
+    static constexpr int SX = BX + 2, OX = BX - 4;
+    static constexpr int kStates = (kF_Y + 2) * 6 * SX, kRows = kF_Y * 6 * BX;  // doubles of S; of Y and of M
 
-// face states of cell k of the face-state block [X0, X0 + TX + 1) x [Y0, Y0 + TY + 1)
-CSH_HD Faces<double> tileA_face_states(const AdjArgs& a, int k, const double* L)
-{
-    const int lx = k % kA_FX + 1, ly = k / kA_FX + 1;  // position in the state block
-    const int c = ly * kA_WX + lx;
-    const P W0 = lds_get(L, kA_NW, 0, c);
-    return face_states<double, true>(W0, rcp(W0.r), lds_get(L, kA_NW, 0, c - 1), lds_get(L, kA_NW, 0, c + 1),
-                                     lds_get(L, kA_NW, 0, c - kA_WX), lds_get(L, kA_NW, 0, c + kA_WX), a.kx, a.ky);
-}
+    const AdjArgs& a;
+    double* const S;  // states; later the totals of the positions
+    double* const Y;  // low y-face states, their adjoints, the shares downwards
+    double* const M;  // lam', then the shares upwards
+    int X0, Y0, lx, ly, i, j, gi, gj;
+    unsigned cell;
+    C lam, Uc, lc;
+    P W0, self, left, right;
+    double ir;
+    Faces<double> f, fb;
 
-// A2: the face states of the thread's own cell e = (X0 + t % TX, Y0 + t / TX):
-// the high ones kept (returned), the low ones written to LDS for the faces of
-// the cells to the left and below; then the low x face states of the column
-// to the right of the tile and the low y face states of the row above it
-CSH_HD void tileA_faces(const AdjArgs& a, int t, double* L, P& xhi, P& yhi)
-{
-    double* X = L + 6 * kA_NW;
-    double* Y = X + 6 * kA_NF;
-    const int k = (t / kA_TX) * kA_FX + t % kA_TX;
-    const Faces<double> f = tileA_face_states(a, k, L);
-    xhi = f.xhi;
-    yhi = f.yhi;
-    lds_put(X, kA_NF, 0, k, f.xlo);
-    lds_put(Y, kA_NF, 0, k, f.ylo);
-    if (t < kA_TY + kA_TX) {
-        const bool col = t < kA_TY;  // the column x = X0 + TX, else the row y = Y0 + TY
-        const int k2 = col ? t * kA_FX + kA_TX : kA_TY * kA_FX + (t - kA_TY);
-        const Faces<double> g = tileA_face_states(a, k2, L);
-        if (col) lds_put(X, kA_NF, 0, k2, g.xlo);
-        else lds_put(Y, kA_NF, 0, k2, g.ylo);
-    }
-}
-
-// A3: the extended cell e of the thread: the flux adjoints of its high x and
-// y faces, through HLL into the adjoints of the two face states of each
-// (written to FSb); the slots of the ring that no face writes are cleared
-CSH_HD void tileA_fluxes(const AdjArgs& a, int X0, int Y0, int t, const double* L, const P& xhi, const P& yhi)
-{
-    const double* X = L + 6 * kA_NW;
-    const double* Y = X + 6 * kA_NF;
-    const int i = X0 + t % kA_TX, j = Y0 + t / kA_TX;
-    if (i > a.nx || j > a.ny) return;  // outside the extended grid
-    const size_t ne = (size_t)a.ex * a.ey, e = ext_index(a, i, j);
-    const int k = (t / kA_TX) * kA_FX + t % kA_TX;  // e in the face-state block
-    if (i == a.nx) store_p(a.FSb, ne, XHI, e, zero_p());
-    if (i == -1) store_p(a.FSb, ne, XLO, e, zero_p());
-    if (j == a.ny) store_p(a.FSb, ne, YHI, e, zero_p());
-    if (j == -1) store_p(a.FSb, ne, YLO, e, zero_p());
-    if (i == a.nx && j == a.ny) return;
-    const C l0 = lam_prime_virtual(a, i, j);
-    if (i <= a.nx - 1) {  // x face i + 1/2
-        const C Fb = csub(lam_prime_virtual(a, i + 1, j), l0, a.cx);
-        P wlb = zero_p(), wrb = zero_p();
-        hll_vjp(xhi, lds_get(X, kA_NF, 0, k + 1), Fb, wlb, wrb);
-        store_p(a.FSb, ne, XHI, e, wlb);
-        store_p(a.FSb, ne, XLO, e + 1, wrb);
-    }
-    if (j <= a.ny - 1) {  // y face j + 1/2
-        const C Gb = csub(lam_prime_virtual(a, i, j + 1), l0, a.cy);
-        P wlb = zero_p(), wrb = zero_p();
-        hll_vjp(swap(yhi), swap(lds_get(Y, kA_NF, 0, k + kA_FX)), swap(Gb), wlb, wrb);
-        store_p(a.FSb, ne, YHI, e, swapb(wlb));
-        store_p(a.FSb, ne, YLO, e + a.ex, swapb(wrb));
-    }
-}
-
-// index of a virtual cell in the extended face-state arrays, -1 for a cell
-// beyond the ring [-1, n] (its shares reach no output: on an outflow axis its
-// face states feed no face, on a periodic one it is not next to an output);
-// a ring cell of a periodic axis is the wrapped cell
-CSH_HD long ext_of_virtual(const AdjArgs& a, int i, int j)
-{
-    if (i < -1 || i > a.nx || j < -1 || j > a.ny) return -1;
-    if (a.bcx == 0) i = map_wide(i, a.nx, 0);
-    if (a.bcy == 0) j = map_wide(j, a.ny, 0);
-    return (long)ext_index(a, i, j);
-}
-
-// B0: primitive states of the tile and its ring, cells [X0 - 2, X0 + kB_W) x
-// [Y0 - 2, Y0 + kB_H) (coordinates clamped into [-2, n + 1], as in A1)
-CSH_HD void tileB_states(const AdjArgs& a, int X0, int Y0, int t, double* L)
-{
-    double* S = L + 5 * 6 * kB_THREADS;
-    for (int k = t; k < kB_NS; k += kB_THREADS) {
-        const int i0 = X0 - 2 + k % kB_SX, j0 = Y0 - 2 + k / kB_SX;
-        const int i = i0 < -2 ? -2 : (i0 > a.nx + 1 ? a.nx + 1 : i0);
-        const int j = j0 < -2 ? -2 : (j0 > a.ny + 1 ? a.ny + 1 : j0);
-        lds_put(S, kB_NS, 0, k, prim_at(a, i, j, true));
-    }
-}
-
-// the face-state adjoints of the thread's cell; zero beyond the ring
-CSH_HD Faces<double> tileB_face_adjoints(const AdjArgs& a, int X0, int Y0, int t)
-{
-    const long e = ext_of_virtual(a, X0 - 1 + t % kB_W, Y0 - 1 + t / kB_W);
-    if (e < 0) return {zero_p(), zero_p(), zero_p(), zero_p()};
-    return load_face_adjoints(a, (size_t)a.ex * a.ey, (size_t)e, true);
-}
-
-// B1: the face-state reverse pass of the virtual cell at column l, row w of the
-// tile (X0 - 1 + l, Y0 - 1 + w) from its face-state adjoints fb: its own share
-// returned, the four it gives its neighbours written to LDS
-CSH_HD P tileB_shares(const AdjArgs& a, int X0, int Y0, int t, double* L, const Faces<double>& fb)
-{
-    const double* S = L + 5 * 6 * kB_THREADS;
-    const int l = t % kB_W, w = t / kB_W;
-    const int i = X0 - 1 + l, j = Y0 - 1 + w;
-    const int c = (w + 1) * kB_SX + (l + 1);  // the cell in the state block
-    P b0 = zero_p();
-    const long e = ext_of_virtual(a, i, j);
-    // the y part first, its two neighbour shares stored before the x part
-    // starts (fewer values live at once)
-    const P W0 = e >= 0 ? lds_get(S, kB_NS, 0, c) : zero_p();
+    CSH_HD AdjointThread(const AdjArgs& args, double* s, double* y, double* m, unsigned block, int tiles_x, int thread)
+        : a(args), S(s), Y(y), M(m)
     {
-        P bm = zero_p(), bp = zero_p();
-        if (e >= 0)
-            face_states_vjp_y(W0, lds_get(S, kB_NS, 0, c - kB_SX), lds_get(S, kB_NS, 0, c + kB_SX), a.ky, fb, b0, bm,
-                              bp);
-        lds_put(L, kB_THREADS, SH_DOWN * 6 * kB_THREADS, t, bm);
-        lds_put(L, kB_THREADS, SH_UP * 6 * kB_THREADS, t, bp);
+        X0 = (int)(block % (unsigned)tiles_x) * OX;
+        Y0 = (int)(block / (unsigned)tiles_x) * kF_OY;
+        lx = thread % BX;
+        ly = thread / BX;
+        i = X0 - 2 + lx;
+        j = Y0 - 2 + ly;
+        gi = map(i, a.nx, a.bcx);
+        gj = map(j, a.ny, a.bcy);
+        cell = (unsigned)(gj * a.nx + gi);
     }
-    P bl = zero_p(), br = zero_p();
-    if (e >= 0)
-        face_states_vjp_x<true>(W0, lds_get(S, kB_NS, 0, c - 1), lds_get(S, kB_NS, 0, c + 1), a.kx, fb, b0, bl, br);
-    lds_put(L, kB_THREADS, SH_LEFT * 6 * kB_THREADS, t, bl);
-    lds_put(L, kB_THREADS, SH_RIGHT * 6 * kB_THREADS, t, br);
-    return b0;
-}
 
-// B2: everything that lands on the position of column l, row w from inside the tile
-CSH_HD P tileB_total(int t, const P& self, const double* L)
-{
-    const int l = t % kB_W, w = t / kB_W;
-    P s = self;
-    if (l + 1 < kB_W) acc(s, lds_get(L, kB_THREADS, SH_LEFT * 6 * kB_THREADS, t + 1));
-    if (l >= 1) acc(s, lds_get(L, kB_THREADS, SH_RIGHT * 6 * kB_THREADS, t - 1));
-    if (w >= 1) acc(s, lds_get(L, kB_THREADS, SH_UP * 6 * kB_THREADS, t - kB_W));
-    if (w + 1 < kB_H) acc(s, lds_get(L, kB_THREADS, SH_DOWN * 6 * kB_THREADS, t + kB_W));
-    return s;
-}
-
-CSH_HD void tileB_put_total(int t, const P& s, double* L) { lds_put(L, kB_THREADS, SH_TOT * 6 * kB_THREADS, t, s); }
-
-// what lands on tile position (lp, wp), lp in [-1, kB_W], wp in [-1, kB_H]:
-// the total inside the tile, or the one share a tile cell gives a position just
-// outside it (the cells beyond it feed only ghost positions of outflow axes
-// through shares that are zero: they lie past the extended ring)
-CSH_HD P tileB_landing(int lp, int wp, const double* L)
-{
-    const bool xin = lp >= 0 && lp < kB_W, yin = wp >= 0 && wp < kB_H;
-    if (xin && yin) return lds_get(L, kB_THREADS, SH_TOT * 6 * kB_THREADS, wp * kB_W + lp);
-    if (yin && lp == -1) return lds_get(L, kB_THREADS, SH_LEFT * 6 * kB_THREADS, wp * kB_W);
-    if (yin && lp == kB_W) return lds_get(L, kB_THREADS, SH_RIGHT * 6 * kB_THREADS, wp * kB_W + kB_W - 1);
-    if (xin && wp == -1) return lds_get(L, kB_THREADS, SH_DOWN * 6 * kB_THREADS, lp);
-    if (xin && wp == kB_H) return lds_get(L, kB_THREADS, SH_UP * 6 * kB_THREADS, (kB_H - 1) * kB_W + lp);
-    return zero_p();
-}
-
-// positions whose shares belong to output coordinate i on one axis: itself, and
-// on an outflow axis the ghost positions the boundary cell stands for
-CSH_HD int fold_positions(int i, int n, int bc, int* p)
-{
-    int k = 0;
-    p[k++] = i;
-    if (bc != 0) {
-        if (i == 0) { p[k++] = -1; p[k++] = -2; }
-        if (i == n - 1) { p[k++] = n; p[k++] = n + 1; }
+    // cells past [-3, n + 2] feed nothing that is used
+    static CSH_HD int map(int k, int n, int bc)
+    {
+        const int c = k < -3 ? -3 : k;
+        return map_index(c < n + 2 ? c : n + 2, n, bc);
     }
-    return k;
-}
+    CSH_HD C state_of(unsigned c) const { return Planes<double>(a.U, (size_t)a.nx * a.ny).load(c); }
+    CSH_HD C lam_of(unsigned c) const { return Planes<double>(a.lam1, (size_t)a.nx * a.ny).load(c); }
+    // rows and columns of S are those of the block, shifted by one
+    CSH_HD void put_state(int col, int row, const P& v) { lds_put(S + (row + 1) * 6 * SX, SX, 0, col + 1, v); }
+    CSH_HD P state(int col, int row) const { return lds_get(S + (row + 1) * 6 * SX, SX, 0, col + 1); }
+    CSH_HD double* yrow(int row) const { return Y + row * 6 * BX; }
+    CSH_HD double* mrow(int row) const { return M + row * 6 * BX; }
+    // lam' of the mapped cell from its lam^{n+1}
+    CSH_HD C lam_prime(const C& l) const
+    {
+        if (a.vc2 == 0.0) return l;
+        return kick_adjoint(a, l, a.x0 + (gi + 0.5) * a.dx, a.y0 + (gj + 0.5) * a.dy);
+    }
 
-// B3: the output cell at column l, row w (inner cells only): the folded total of
-// the shares on its positions, through W(U), plus lam' itself
-CSH_HD void tileB_gather(const AdjArgs& a, int X0, int Y0, int t, const double* L)
-{
-    const int l = t % kB_W, w = t / kB_W;
-    if (l < 1 || l > kB_OX || w < 1 || w > kB_OY) return;
-    const int i = X0 - 1 + l, j = Y0 - 1 + w;
-    if (i >= a.nx || j >= a.ny) return;
-    int px[5], py[5];
-    const int nx_ = fold_positions(i, a.nx, a.bcx, px), ny_ = fold_positions(j, a.ny, a.bcy, py);
-    P wb = zero_p();
-    for (int u = 0; u < nx_; ++u)
-        for (int v = 0; v < ny_; ++v) acc(wb, tileB_landing(px[u] - (X0 - 1), py[v] - (Y0 - 1), L));
-    const size_t plane = (size_t)a.nx * a.ny, c = (size_t)j * a.nx + i;
-    C out = lam_prime(a, i, j, true);
-    to_prim_vjp(load_cons<double>(a.U, plane, c), wb, out);
-    store_cons(a.lam0, plane, c, out);
-}
+    // states of the cell and of the ring, lam' of the cell
+    CSH_HD void load()
+    {
+        lam = zero_c();
+        if ((a.bcx == 0 || (i >= 0 && i < a.nx)) && (a.bcy == 0 || (j >= 0 && j < a.ny))) lam = lam_prime(lam_of(cell));
+        W0 = to_prim(state_of(cell));
+        ir = rcp(W0.r);
+        put_state(lx, ly, W0);
+        if (lx == 0 || lx == BX - 1) {
+            const int d = lx == 0 ? -1 : 1;
+            put_state(lx + d, ly, to_prim(state_of((unsigned)(gj * a.nx + map(i + d, a.nx, a.bcx)))));
+        }
+        if (ly == 0 || ly == kF_Y - 1) {
+            const int d = ly == 0 ? -1 : 1;
+            put_state(lx, ly + d, to_prim(state_of((unsigned)(map(j + d, a.ny, a.bcy) * a.nx + gi))));
+        }
+        lds_put(mrow(ly), BX, 0, lx, {lam.r, lam.mx, lam.my, lam.exx, lam.exy, lam.eyy});
+    }
+
+    // face states
+    CSH_HD void faces()
+    {
+        const P dlx = sub(W0, state(lx - 1, ly)), drx = sub(state(lx + 1, ly), W0);
+        f = face_states_d<double, true>(W0, ir, dlx, drx, sub(W0, state(lx, ly - 1)), sub(state(lx, ly + 1), W0), a.kx,
+                                        a.ky);
+        lds_put(yrow(ly), BX, 0, lx, f.ylo);
+        fb = {zero_p(), zero_p(), zero_p(), zero_p()};
+    }
+
+    // the high x face, from the low face state and lam' of the cell to the right:
+    // returns the adjoint of that face state
+    CSH_HD P x_face(const P& xlo, const C& lam_right)
+    {
+        P low = zero_p();
+        hll_vjp(f.xhi, xlo, csub(lam_right, lam, a.cx), fb.xhi, low);
+        return low;
+    }
+
+    // the high y face, through the row above's slots
+    CSH_HD void y_face()
+    {
+        if (ly == kF_Y - 1) return;
+        const P l = lds_get(mrow(ly + 1), BX, 0, lx);
+        const C above = {l.r, l.u, l.v, l.pxx, l.pxy, l.pyy};
+        P low = zero_p(), high = zero_p();
+        hll_vjp(swap(f.yhi), swap(lds_get(yrow(ly + 1), BX, 0, lx)), swap(csub(above, lam, a.cy)), low, high);
+        fb.yhi = swapb(low);
+        lds_put(yrow(ly + 1), BX, 0, lx, swapb(high));
+    }
+
+    // the face-state reverse pass of the cells next to an output, inside the extended ring
+    CSH_HD void shares()
+    {
+        if (ly > 0) fb.ylo = lds_get(yrow(ly), BX, 0, lx);
+        const bool inner = lx >= 1 && lx <= BX - 2 && ly >= 1 && ly <= kF_Y - 2 && i >= -1 && i <= a.nx && j >= -1 &&
+                           j <= a.ny;
+        const P Wc = state(lx, ly);  // W0 again: a register set less through the fluxes
+        P down = zero_p(), up = zero_p();
+        self = left = right = zero_p();
+        if (inner) face_states_vjp_y(Wc, state(lx, ly - 1), state(lx, ly + 1), a.ky, fb, self, down, up);
+        lds_put(yrow(ly), BX, 0, lx, down);  // at once: kept through the x part they would spill
+        lds_put(mrow(ly), BX, 0, lx, up);
+        if (inner) face_states_vjp_x<true>(Wc, state(lx - 1, ly), state(lx + 1, ly), a.kx, fb, self, left, right);
+    }
+
+    // what lands on this position from the cells beside it; the state and lam^{n+1}
+    // again from the caches: kept in registers they would spill
+    CSH_HD void land_x(const P& from_right, const P& from_left)
+    {
+        acc(self, from_right);
+        acc(self, from_left);
+        Uc = state_of(cell);
+        lc = lam_of(cell);
+    }
+    // and from those above and below
+    CSH_HD void land_y()
+    {
+        if (ly < kF_Y - 1) acc(self, lds_get(yrow(ly + 1), BX, 0, lx));
+        if (ly > 0) acc(self, lds_get(mrow(ly - 1), BX, 0, lx));
+    }
+
+    // outflow axes: the two ghost positions on either side belong to the boundary cell
+    // (the conditions are uniform in the block); l1, l2, r1, r2: the totals one and two
+    // to the left and right
+    CSH_HD bool folds_x() const { return a.bcx != 0 && (X0 == 0 || X0 + OX >= a.nx); }
+    CSH_HD void fold_x(const P& l1, const P& l2, const P& r1, const P& r2)
+    {
+        if (i == 0) {
+            acc(self, l1);
+            acc(self, l2);
+        }
+        if (i == a.nx - 1) {
+            acc(self, r1);
+            acc(self, r2);
+        }
+    }
+    CSH_HD bool folds_y() const { return a.bcy != 0 && (Y0 == 0 || Y0 + kF_OY >= a.ny); }
+    CSH_HD void put_total() { put_state(lx, ly, self); }  // over the states, last read before the barrier of land_y
+    CSH_HD void fold_y()
+    {
+        if (j == 0 && ly >= 2) {
+            acc(self, state(lx, ly - 1));
+            acc(self, state(lx, ly - 2));
+        }
+        if (j == a.ny - 1 && ly <= kF_Y - 3) {
+            acc(self, state(lx, ly + 1));
+            acc(self, state(lx, ly + 2));
+        }
+    }
+
+    // the output cells: W(U) reverse and lam'
+    CSH_HD void store() const
+    {
+        if (lx < 2 || lx >= BX - 2 || ly < 2 || ly >= kF_Y - 2 || i >= a.nx || j >= a.ny) return;
+        C out = lam_prime(lc);
+        to_prim_vjp(Uc, self, out);
+        OutPlanes<double>(a.lam0, (size_t)a.nx * a.ny).store(cell, out);
+    }
+};
 
 }  // namespace csh

@@ -21,8 +21,7 @@
 //   4. gather: per interior cell, sum the XS of the padded positions that the
 //              boundary mapping sends to this cell, chain through W(U) and add
 //              lam' itself.
-// (The per-cell bodies of that scheme with a y part, csh_adjoint.h, are the CPU
-// reference the 2-D kernel is tested against.)
+// (tests/host holds that scheme with a y part, the CPU reference of the 2-D kernel.)
 //
 // The kernels take their workgroup numbers XCD-aware (xcd_block), so blocks that
 // share halo cells sit in the same L2.
@@ -42,12 +41,12 @@ __global__ __launch_bounds__(256) void adjoint_kernel(AdjArgs a)
     // cell counts stay below 2^31 (a plane is smaller than 4 GiB): 32-bit index arithmetic
     const unsigned t = xcd_block(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
     if (STAGE == 4) {  // interior cells
-        if (t < (unsigned)a.nx) gather_cell<false>(a, (int)t, 0);
+        if (t < (unsigned)a.nx) gather_cell(a, (int)t);
         return;
     }
-    if (t >= (unsigned)a.ex) return;  // extended cells
-    if (STAGE == 1) faces_cell<false>(a, (int)t - 1, 0);
-    if (STAGE == 2) hll_cell<false>(a, (int)t - 1, 0);
+    if (t >= (unsigned)a.nx + 2) return;  // extended cells
+    if (STAGE == 1) faces_cell(a, (int)t - 1);
+    if (STAGE == 2) hll_cell(a, (int)t - 1);
 }
 
 // Stage 3, summed per padded position: a wavefront covers the extended cells
@@ -65,12 +64,12 @@ __global__ __launch_bounds__(256) void adjoint_xsum_kernel(AdjArgs a)
     if (w >= (a.nx + 4 + kXsOwned - 1) / kXsOwned) return;  // uniform per wavefront
     const int i = (int)w * kXsOwned - 3 + lane;
     P b0 = zero_p(), bl = zero_p(), br = zero_p();
-    if (i >= -1 && i <= a.nx) cells_x_vjp<false>(a, i, 0, b0, bl, br);
+    if (i >= -1 && i <= a.nx) cells_x_vjp(a, i, b0, bl, br);
     const P l = lane_shift<+1>(bl), r = lane_shift<-1>(br);  // from the cells at i + 1, i - 1
     const P sum = {b0.r + l.r + r.r,       b0.u + l.u + r.u,       b0.v + l.v + r.v,
                    b0.pxx + l.pxx + r.pxx, b0.pxy + l.pxy + r.pxy, b0.pyy + l.pyy + r.pyy};
     if (lane >= 1 && lane <= kXsOwned && i >= -2 && i <= a.nx + 1)
-        store_p(a.XS, (size_t)(a.nx + 4), 0, xs_index(a, i, 0), sum);
+        store_p(a.XS, (size_t)(a.nx + 4), 0, (size_t)(i + 2), sum);
 }
 
 // The reverse pass of 2-D grids, one launch.  A workgroup holds a block of
@@ -83,7 +82,7 @@ __global__ __launch_bounds__(256) void adjoint_xsum_kernel(AdjArgs a)
 // W(U) reverse and lam'.  x neighbours exchange by lane shifts (a shift that
 // crosses from one row of the block to the next lands on a cell whose value is not
 // used or is zero), y neighbours through LDS, where a slot read by one thread only
-// is overwritten by it: three barriers.
+// is overwritten by it: four barriers (a fifth in the blocks that fold a y boundary).
 //
 // Two launches with the face-state adjoints in between (192 B per cell written and
 // read with a ring) moved 663 B per cell-step, 49 us at 512^2 whatever their
@@ -94,129 +93,34 @@ __global__ __launch_bounds__(256) void adjoint_xsum_kernel(AdjArgs a)
 // registers: values are put into LDS as soon as they are known and read again after
 // the fluxes; kept through the reverse pass they spilled 44 B a thread, 131 x 93
 // 8.5 us, 400^2 23.2 against 21.3).
-constexpr int kF_Y = 16, kF_OY = kF_Y - 4;
-
 template <int BX>
 __global__ __launch_bounds__(BX * kF_Y, 2) void adjoint_fused_kernel(AdjArgs a, int tiles_x)
 {
-    constexpr int SX = BX + 2, OX = BX - 4;
-    __shared__ double S[(kF_Y + 2) * 6 * SX];  // states; later the totals of the positions
-    __shared__ double Y[kF_Y * 6 * BX];        // low y-face states, their adjoints, the shares downwards
-    __shared__ double M[kF_Y * 6 * BX];        // lam', then the shares upwards
-    const unsigned b = xcd_block(blockIdx.x, gridDim.x);
-    const int X0 = (int)(b % (unsigned)tiles_x) * OX, Y0 = (int)(b / (unsigned)tiles_x) * kF_OY;
-    const int lx = threadIdx.x % BX, ly = threadIdx.x / BX;
-    const int i = X0 - 2 + lx, j = Y0 - 2 + ly;
-    // cells past [-3, n + 2] feed nothing that is used
-    auto map = [](int k, int n, int bc) { return map_index(min(max(k, -3), n + 2), n, bc); };
-    const int gi = map(i, a.nx, a.bcx), gj = map(j, a.ny, a.bcy);
-    const Planes<double> Up(a.U, (size_t)a.nx * a.ny), Lp(a.lam1, (size_t)a.nx * a.ny);
-    const unsigned cell = (unsigned)(gj * a.nx + gi);
-
-    // rows and columns of S are those of the block, shifted by one
-    auto put_state = [&](int col, int row, const P& v) { lds_put(S + (row + 1) * 6 * SX, SX, 0, col + 1, v); };
-    auto state = [&](int col, int row) -> P { return lds_get(S + (row + 1) * 6 * SX, SX, 0, col + 1); };
-    double* const Yrow = Y + ly * 6 * BX;
-    double* const Mrow = M + ly * 6 * BX;
-
-    // lam' of the mapped cell from its lam^{n+1}: the kick's transpose
-    auto lam_prime = [&](C l) -> C {
-        if (a.vc2 != 0.0) {
-            const double x = a.x0 + (gi + 0.5) * a.dx, y = a.y0 + (gj + 0.5) * a.dy;
-            const double f = -a.vc2 * rcp(x * x + y * y + a.rc2);
-            l = kick_vjp(l, a.dt, f * x, f * y);
-        }
-        return l;
-    };
-
-    // states of the cell and of the ring, lam' of the cell
-    C lam = zero_c();
-    if ((a.bcx == 0 || (i >= 0 && i < a.nx)) && (a.bcy == 0 || (j >= 0 && j < a.ny))) lam = lam_prime(Lp.load(cell));
-    const P W0 = to_prim(Up.load(cell));
-    const double ir = rcp(W0.r);
-    put_state(lx, ly, W0);
-    if (lx == 0 || lx == BX - 1) {
-        const int d = lx == 0 ? -1 : 1;
-        put_state(lx + d, ly, to_prim(Up.load((unsigned)(gj * a.nx + map(i + d, a.nx, a.bcx)))));
-    }
-    if (ly == 0 || ly == kF_Y - 1) {
-        const int d = ly == 0 ? -1 : 1;
-        put_state(lx, ly + d, to_prim(Up.load((unsigned)(map(j + d, a.ny, a.bcy) * a.nx + gi))));
-    }
-    lds_put(Mrow, BX, 0, lx, {lam.r, lam.mx, lam.my, lam.exx, lam.exy, lam.eyy});
+    using Thread = AdjointThread<BX>;
+    __shared__ double S[Thread::kStates], Y[Thread::kRows], M[Thread::kRows];
+    Thread t(a, S, Y, M, xcd_block(blockIdx.x, gridDim.x), tiles_x, (int)threadIdx.x);
+    t.load();
     __syncthreads();
-
-    // face states; the adjoints of those at the cell's high x face, and of its low x
-    // face from the thread to the left
-    const P dlx = sub(W0, state(lx - 1, ly)), drx = sub(state(lx + 1, ly), W0);
-    Faces<double> f = face_states_d<double, true>(W0, ir, dlx, drx, sub(W0, state(lx, ly - 1)),
-                                                  sub(state(lx, ly + 1), W0), a.kx, a.ky);
-    lds_put(Yrow, BX, 0, lx, f.ylo);
-    Faces<double> fb{zero_p(), zero_p(), zero_p(), zero_p()};
-    {
-        P right = zero_p();
-        hll_vjp(f.xhi, lane_shift<+1>(f.xlo), csub(lane_shift<+1>(lam), lam, a.cx), fb.xhi, right);
-        fb.xlo = lane_shift<-1>(right);
-    }
+    t.faces();
+    const P low = t.x_face(lane_shift<+1>(t.f.xlo), lane_shift<+1>(t.lam));
+    t.fb.xlo = lane_shift<-1>(low);
     __syncthreads();
-    // the same for the y faces, through the row above's slots
-    if (ly < kF_Y - 1) {
-        const P l = lds_get(Mrow + 6 * BX, BX, 0, lx);
-        const C above = {l.r, l.u, l.v, l.pxx, l.pxy, l.pyy};
-        P low = zero_p(), high = zero_p();
-        hll_vjp(swap(f.yhi), swap(lds_get(Yrow + 6 * BX, BX, 0, lx)), swap(csub(above, lam, a.cy)), low, high);
-        fb.yhi = swapb(low);
-        lds_put(Yrow + 6 * BX, BX, 0, lx, swapb(high));
-    }
+    t.y_face();
     __syncthreads();
-    if (ly > 0) fb.ylo = lds_get(Yrow, BX, 0, lx);
-
-    // the face-state reverse pass of the cells next to an output, inside the extended ring
-    const bool inner = lx >= 1 && lx <= BX - 2 && ly >= 1 && ly <= kF_Y - 2 && i >= -1 && i <= a.nx && j >= -1 &&
-                       j <= a.ny;
-    const P Wc = state(lx, ly);  // W0 again: a register set less through the fluxes
-    P self = zero_p(), left = zero_p(), right = zero_p(), down = zero_p(), up = zero_p();
-    if (inner) face_states_vjp_y(Wc, state(lx, ly - 1), state(lx, ly + 1), a.ky, fb, self, down, up);
-    lds_put(Yrow, BX, 0, lx, down);  // at once: kept through the x part they would spill
-    lds_put(Mrow, BX, 0, lx, up);
-    if (inner) face_states_vjp_x<true>(Wc, state(lx - 1, ly), state(lx + 1, ly), a.kx, fb, self, left, right);
-    acc(self, lane_shift<+1>(left));
-    acc(self, lane_shift<-1>(right));
-    // the state and lam^{n+1} again from the caches: kept in registers they would spill
-    const C Uc = Up.load(cell), lc = Lp.load(cell);
+    t.shares();
+    t.land_x(lane_shift<+1>(t.left), lane_shift<-1>(t.right));
     __syncthreads();
-    // what lands on this position
-    if (ly < kF_Y - 1) acc(self, lds_get(Yrow + 6 * BX, BX, 0, lx));
-    if (ly > 0) acc(self, lds_get(Mrow - 6 * BX, BX, 0, lx));
-    // outflow axes: the two ghost positions on either side belong to the boundary cell
-    // (the branches are uniform in the workgroup)
-    if (a.bcx != 0 && (X0 == 0 || X0 + OX >= a.nx)) {
-        const P l1 = lane_shift<-1>(self), l2 = lane_shift<-1>(l1), r1 = lane_shift<+1>(self), r2 = lane_shift<+1>(r1);
-        if (i == 0) {
-            acc(self, l1);
-            acc(self, l2);
-        }
-        if (i == a.nx - 1) {
-            acc(self, r1);
-            acc(self, r2);
-        }
+    t.land_y();
+    if (t.folds_x()) {
+        const P l1 = lane_shift<-1>(t.self), r1 = lane_shift<+1>(t.self);
+        t.fold_x(l1, lane_shift<-1>(l1), r1, lane_shift<+1>(r1));
     }
-    if (a.bcy != 0 && (Y0 == 0 || Y0 + kF_OY >= a.ny)) {
-        put_state(lx, ly, self);  // the states were last read before the barrier above
+    if (t.folds_y()) {
+        t.put_total();
         __syncthreads();
-        if (j == 0 && ly >= 2) {
-            acc(self, state(lx, ly - 1));
-            acc(self, state(lx, ly - 2));
-        }
-        if (j == a.ny - 1 && ly <= kF_Y - 3) {
-            acc(self, state(lx, ly + 1));
-            acc(self, state(lx, ly + 2));
-        }
+        t.fold_y();
     }
-    if (lx < 2 || lx >= BX - 2 || ly < 2 || ly >= kF_Y - 2 || i >= a.nx || j >= a.ny) return;
-    C out = lam_prime(lc);
-    to_prim_vjp(Uc, self, out);
-    OutPlanes<double>(a.lam0, (size_t)a.nx * a.ny).store(cell, out);
+    t.store();
 }
 
 __global__ __launch_bounds__(256) void init_adjoint_kernel(const double* W, const double* lamU, double* lamW, int64_t n)
@@ -251,8 +155,6 @@ int csh_adjoint_impl(csh_grid_view v, double dt, const void* U, const void* lam_
     a.ny = v.ny;
     a.bcx = v.bcx;
     a.bcy = v.bcy;
-    a.ex = v.nx + 2;
-    a.ey = twod ? v.ny + 2 : 1;
     a.dx = v.dx;
     a.dy = v.dy;
     a.dt = dt;
@@ -279,7 +181,7 @@ int csh_adjoint_impl(csh_grid_view v, double dt, const void* U, const void* lam_
             adjoint_fused_kernel<32><<<(unsigned)n32, 32 * kF_Y, 0, s>>>(a, (int)tiles(v.nx, 28));
     } else {
         set_workspace_1d(a, ws);
-        const unsigned be = (unsigned)(((size_t)a.ex + 255) / 256), bi = (unsigned)(((size_t)v.nx + 255) / 256);
+        const unsigned be = (unsigned)(((size_t)v.nx + 2 + 255) / 256), bi = (unsigned)(((size_t)v.nx + 255) / 256);
         const unsigned bx = (unsigned)(((a.nx + 4 + kXsOwned - 1) / kXsOwned + 3) / 4);
         adjoint_kernel<1><<<be, 256, 0, s>>>(a);
         adjoint_kernel<2><<<be, 256, 0, s>>>(a);

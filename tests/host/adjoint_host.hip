@@ -1,26 +1,26 @@
-// CPU harness for the adjoint: runs the per-cell bodies of the adjoint kernels
-// and the forward face/flux arithmetic in host loops, so the tests can check
-// the hand-written reverse pass against finite differences and the oracle's
-// dense Jacobian without a GPU.  Test infrastructure only.
+// CPU harness for the adjoint: runs the bodies of the adjoint kernels and the forward
+// face/flux arithmetic in host loops, so the tests can check the hand-written reverse
+// pass against finite differences and the oracle's dense Jacobian without a GPU, and
+// the device's 2-D blocks against the reverse step cell by cell.  Test infrastructure
+// only.
 #include <algorithm>
+#include <cmath>
 #include <cstring>
 #include <limits>
 #include <vector>
 
+#include "adjoint_reference.h"
 #include "csh_adjoint.h"
 
 using namespace csh;
 
-static AdjArgs make_args(int nx, int ny, int bcx, int bcy, double dx, double dy, double dt, double vc, double rc,
-                         double x0, double y0, const double* U)
+static void set_args(AdjArgs& a, int nx, int ny, int bcx, int bcy, double dx, double dy, double dt, double vc,
+                     double rc, double x0, double y0, const double* U)
 {
-    AdjArgs a{};
     a.nx = nx;
     a.ny = ny;
     a.bcx = bcx;
     a.bcy = bcy;
-    a.ex = nx + 2;
-    a.ey = ny > 1 ? ny + 2 : 1;
     a.dx = dx;
     a.dy = ny > 1 ? dy : 1.0;
     a.dt = dt;
@@ -30,135 +30,226 @@ static AdjArgs make_args(int nx, int ny, int bcx, int bcy, double dx, double dy,
     a.x0 = x0;
     a.y0 = y0;
     a.U = U;
-    return a;
 }
 
-template <bool TWOD>
-static void adjoint_loops(AdjArgs& a)
+static P plus3(const P& a, const P& b, const P& c)
 {
-    const int j0 = TWOD ? -1 : 0, j1 = TWOD ? a.ny : 0;
-    for (int j = j0; j <= j1; ++j)
-        for (int i = -1; i <= a.nx; ++i) faces_cell<TWOD>(a, i, j);
-    for (int j = j0; j <= j1; ++j)
-        for (int i = -1; i <= a.nx; ++i) hll_cell<TWOD>(a, i, j);
-    if constexpr (TWOD)
-        for (int j = j0; j <= j1; ++j)
-            for (int i = -1; i <= a.nx; ++i) cells_cell_y(a, i, j);
-    // x part: self, left and right shares per extended cell, then one sum per
-    // padded position in the kernel's order (self, left share of the cell to
-    // the right, right share of the cell to the left; zero outside the range)
+    return {a.r + b.r + c.r, a.u + b.u + c.u, a.v + b.v + c.v, a.pxx + b.pxx + c.pxx, a.pxy + b.pxy + c.pxy,
+            a.pyy + b.pyy + c.pyy};
+}
+
+static const double kNan = std::numeric_limits<double>::quiet_NaN();
+
+// the 1-D kernels, a loop per stage; the workspace has the device's size and is
+// NaN-filled: every slot the reverse pass reads must have been written by it
+static void adjoint_1d(AdjArgs a)
+{
+    std::vector<double> ws(workspace_1d(a.nx), kNan);
+    set_workspace_1d(a, ws.data());
+    for (int i = -1; i <= a.nx; ++i) faces_cell(a, i);
+    for (int i = -1; i <= a.nx; ++i) hll_cell(a, i);
+    // self, left and right shares per extended cell, then one sum per padded position
+    // in the kernel's order (self, left share of the cell to the right, right share of
+    // the cell to the left; zero outside the range)
+    const size_t ne = (size_t)a.nx + 2;
+    std::vector<P> b0(ne), bl(ne), br(ne);
+    for (int i = -1; i <= a.nx; ++i) cells_x_vjp(a, i, b0[i + 1], bl[i + 1], br[i + 1]);
+    auto share = [&](const std::vector<P>& v, int i) { return i >= -1 && i <= a.nx ? v[i + 1] : zero_p(); };
+    for (int p = -2; p <= a.nx + 1; ++p)
+        store_p(a.XS, (size_t)a.nx + 4, 0, (size_t)(p + 2), plus3(share(b0, p), share(bl, p + 1), share(br, p - 1)));
+    for (int i = 0; i < a.nx; ++i) gather_cell(a, i);
+}
+
+// the 2-D reference, cell by cell
+static void adjoint_2d(ref::Args& a)
+{
+    a.ex = a.nx + 2;
+    a.ey = a.ny + 2;
     const size_t ne = (size_t)a.ex * a.ey, nxs = (size_t)(a.nx + 4) * a.ey;
-    std::vector<P> b0(ne, zero_p()), bl(ne, zero_p()), br(ne, zero_p());
-    for (int j = j0; j <= j1; ++j)
-        for (int i = -1; i <= a.nx; ++i) {
-            const size_t e = ext_index(a, i, j);
-            cells_x_vjp<TWOD>(a, i, j, b0[e], bl[e], br[e]);
-        }
-    auto share = [&](const std::vector<P>& v, int i, int j) { return i >= -1 && i <= a.nx ? v[ext_index(a, i, j)] : zero_p(); };
-    for (int j = j0; j <= j1; ++j)
-        for (int px = -2; px <= a.nx + 1; ++px) {
-            const P s0 = share(b0, px, j), l = share(bl, px + 1, j), r = share(br, px - 1, j);
-            const P sum = {s0.r + l.r + r.r,       s0.u + l.u + r.u,       s0.v + l.v + r.v,
-                           s0.pxx + l.pxx + r.pxx, s0.pxy + l.pxy + r.pxy, s0.pyy + l.pyy + r.pyy};
-            store_p(a.XS, nxs, 0, xs_index(a, px, j), sum);
-        }
-    for (int j = 0; j < (TWOD ? a.ny : 1); ++j)
-        for (int i = 0; i < a.nx; ++i) gather_cell<TWOD>(a, i, j);
+    std::vector<double> ws(66 * ne + 6 * nxs, kNan);
+    a.FS = ws.data();
+    a.FSb = ws.data() + 24 * ne;
+    a.Cs = ws.data() + 48 * ne;
+    a.XS = ws.data() + 66 * ne;
+    auto extended = [&](auto body) {
+        for (int j = -1; j <= a.ny; ++j)
+            for (int i = -1; i <= a.nx; ++i) body(i, j);
+    };
+    extended([&](int i, int j) { ref::faces_cell(a, i, j); });
+    extended([&](int i, int j) { ref::hll_cell(a, i, j); });
+    extended([&](int i, int j) { ref::cells_cell_y(a, i, j); });
+    std::vector<P> b0(ne), bl(ne), br(ne);
+    extended([&](int i, int j) {
+        const size_t e = ref::ext_index(a, i, j);
+        ref::cells_x_vjp(a, i, j, b0[e], bl[e], br[e]);
+    });
+    auto share = [&](const std::vector<P>& v, int i, int j) {
+        return i >= -1 && i <= a.nx ? v[ref::ext_index(a, i, j)] : zero_p();
+    };
+    for (int j = -1; j <= a.ny; ++j)
+        for (int px = -2; px <= a.nx + 1; ++px)
+            store_p(a.XS, nxs, 0, ref::xs_index(a, px, j),
+                    plus3(share(b0, px, j), share(bl, px + 1, j), share(br, px - 1, j)));
+    for (int j = 0; j < a.ny; ++j)
+        for (int i = 0; i < a.nx; ++i) ref::gather_cell(a, i, j);
 }
 
 extern "C" int host_adjoint_step(int nx, int ny, int bcx, int bcy, double dx, double dy, double dt, double vc,
                                  double rc, double x0, double y0, const double* U, const double* lam1, double* lam0)
 {
-    AdjArgs a = make_args(nx, ny, bcx, bcy, dx, dy, dt, vc, rc, x0, y0, U);
-    const size_t ne = (size_t)a.ex * a.ey;
-    // NaN-filled: every slot the reverse pass reads must have been written by it
-    std::vector<double> ws(ny > 1 ? 66 * ne + 6 * (size_t)(nx + 4) * a.ey : workspace_1d(nx),
-                           std::numeric_limits<double>::quiet_NaN());
-    if (ny > 1) {
-        a.FS = ws.data();
-        a.FSb = ws.data() + 24 * ne;
-        a.Cs = ws.data() + 48 * ne;
-        a.XS = ws.data() + 66 * ne;
-    } else {
-        set_workspace_1d(a, ws.data());  // the device's own layout, no double more
-    }
+    ref::Args a{};
+    set_args(a, nx, ny, bcx, bcy, dx, dy, dt, vc, rc, x0, y0, U);
     a.lam1 = lam1;
     a.lam0 = lam0;
-    if (ny > 1) adjoint_loops<true>(a);
-    else adjoint_loops<false>(a);
+    if (ny > 1) adjoint_2d(a);
+    else adjoint_1d(a);
     return 0;
 }
 
-// The tiled two-kernel reverse pass of 2-D grids (kernels A and B) run on the
-// CPU: per tile, each phase for every thread, a host array standing for LDS;
-// the tiles in the GPU's numbering order.  NaN-filled buffers: a slot read
-// before it is written shows in the result.
+// The values of a block's threads moved by one lane, D = +1 or -1, within each
+// wavefront of 64; 0 where the shift has no source (lane_shift on the device).
+template <int D, class V>
+static std::vector<V> shifted(const std::vector<V>& x)
+{
+    std::vector<V> out(x.size(), V{0, 0, 0, 0, 0, 0});
+    for (size_t t = 0; t < x.size(); ++t) {
+        const int l = (int)(t % 64) + D;
+        if (l >= 0 && l < 64 && t + D < x.size()) out[t] = x[t + D];
+    }
+    return out;
+}
+
+// The device's 2-D reverse step on the CPU: per block each phase of adjoint_fused_kernel
+// for every thread, heap arrays of the exact sizes standing for LDS (a slot read before
+// it is written shows as NaN, one outside under the sanitizer), the lane shifts
+// wavefront by wavefront.  False if a cell is not written by exactly one block.
+template <int BX>
+static bool adjoint_blocks(AdjArgs a)
+{
+    const double unwritten = -7.25e300;
+    const size_t cells = 6 * (size_t)a.nx * a.ny;
+    double* const lam0 = a.lam0;
+    std::vector<double> own(cells, unwritten);
+    std::vector<int> writers(cells, 0);
+    a.lam0 = own.data();
+
+    using Thread = AdjointThread<BX>;
+    const int tiles_x = (a.nx + Thread::OX - 1) / Thread::OX, tiles_y = (a.ny + kF_OY - 1) / kF_OY;
+    const int n = BX * kF_Y;
+    for (int block = 0; block < tiles_x * tiles_y; ++block) {
+        std::vector<double> S(Thread::kStates, kNan), Y(Thread::kRows, kNan), M(Thread::kRows, kNan);
+        std::vector<Thread> t;
+        t.reserve(n);
+        for (int k = 0; k < n; ++k) t.emplace_back(a, S.data(), Y.data(), M.data(), (unsigned)block, tiles_x, k);
+        auto every = [&](auto phase) {
+            for (int k = 0; k < n; ++k) phase(t[k], k);
+        };
+        auto values = [&](auto of) {
+            std::vector<decltype(of(t[0]))> v;
+            for (int k = 0; k < n; ++k) v.push_back(of(t[k]));
+            return v;
+        };
+        every([](Thread& q, int) { q.load(); });
+        every([](Thread& q, int) { q.faces(); });
+        {
+            const auto xlo = shifted<+1>(values([](const Thread& q) { return q.f.xlo; }));
+            const auto lam = shifted<+1>(values([](const Thread& q) { return q.lam; }));
+            std::vector<P> low(n);
+            every([&](Thread& q, int k) { low[k] = q.x_face(xlo[k], lam[k]); });
+            low = shifted<-1>(low);
+            every([&](Thread& q, int k) { q.fb.xlo = low[k]; });
+        }
+        every([](Thread& q, int) { q.y_face(); });
+        every([](Thread& q, int) { q.shares(); });
+        {
+            const auto l = shifted<+1>(values([](const Thread& q) { return q.left; }));
+            const auto r = shifted<-1>(values([](const Thread& q) { return q.right; }));
+            every([&](Thread& q, int k) { q.land_x(l[k], r[k]); });
+        }
+        every([](Thread& q, int) { q.land_y(); });
+        if (t[0].folds_x()) {
+            const auto self = values([](const Thread& q) { return q.self; });
+            const auto l1 = shifted<-1>(self), l2 = shifted<-1>(l1), r1 = shifted<+1>(self), r2 = shifted<+1>(r1);
+            every([&](Thread& q, int k) { q.fold_x(l1[k], l2[k], r1[k], r2[k]); });
+        }
+        if (t[0].folds_y()) {
+            every([](Thread& q, int) { q.put_total(); });
+            every([](Thread& q, int) { q.fold_y(); });
+        }
+        every([](Thread& q, int) { q.store(); });
+        for (size_t c = 0; c < cells; ++c) {
+            if (own[c] == unwritten) continue;
+            lam0[c] = own[c];
+            own[c] = unwritten;
+            ++writers[c];
+        }
+    }
+    return std::all_of(writers.begin(), writers.end(), [](int k) { return k == 1; });
+}
+
+// blocks of `width` columns (16 or 32)
+extern "C" int host_adjoint_step_blocks(int width, int nx, int ny, int bcx, int bcy, double dx, double dy, double dt,
+                                        double vc, double rc, double x0, double y0, const double* U,
+                                        const double* lam1, double* lam0)
+{
+    if (ny < 2) return -1;
+    AdjArgs a{};
+    set_args(a, nx, ny, bcx, bcy, dx, dy, dt, vc, rc, x0, y0, U);
+    a.lam1 = lam1;
+    a.lam0 = lam0;
+    if (width == 16) return adjoint_blocks<16>(a) ? 0 : 2;
+    return width == 32 ? (adjoint_blocks<32>(a) ? 0 : 2) : -1;
+}
+
+// both widths, which agree to rounding; the narrow one's result
 extern "C" int host_adjoint_step_tiled(int nx, int ny, int bcx, int bcy, double dx, double dy, double dt, double vc,
                                        double rc, double x0, double y0, const double* U, const double* lam1,
                                        double* lam0)
 {
-    if (ny < 2) return -1;
-    AdjArgs a = make_args(nx, ny, bcx, bcy, dx, dy, dt, vc, rc, x0, y0, U);
-    const size_t ne = (size_t)a.ex * a.ey;
-    const double nan = std::numeric_limits<double>::quiet_NaN();
-    std::vector<double> fsb(24 * ne, nan);
-    a.FSb = fsb.data();
-    a.lam1 = lam1;
-    a.lam0 = lam0;
-    std::vector<double> L((size_t)(kA_LDS > kB_LDS ? kA_LDS : kB_LDS));
-    const int tax = (a.ex + kA_TX - 1) / kA_TX, tay = (a.ey + kA_TY - 1) / kA_TY;
-    std::vector<P> xhi(kA_THREADS), yhi(kA_THREADS);
-    for (int ty = 0; ty < tay; ++ty)
-        for (int tx = 0; tx < tax; ++tx) {
-            const int X0 = -1 + tx * kA_TX, Y0 = -1 + ty * kA_TY;
-            std::fill(L.begin(), L.end(), nan);
-            for (int t = 0; t < kA_THREADS; ++t) tileA_states(a, X0, Y0, t, L.data());
-            for (int t = 0; t < kA_THREADS; ++t) tileA_faces(a, t, L.data(), xhi[t], yhi[t]);
-            for (int t = 0; t < kA_THREADS; ++t) tileA_fluxes(a, X0, Y0, t, L.data(), xhi[t], yhi[t]);
-        }
-    const int tbx = (nx + kB_OX - 1) / kB_OX, tby = (ny + kB_OY - 1) / kB_OY;
-    std::vector<P> self(kB_THREADS), tot(kB_THREADS);
-    std::vector<Faces<double>> fbs(kB_THREADS);
-    for (int ty = 0; ty < tby; ++ty)
-        for (int tx = 0; tx < tbx; ++tx) {
-            const int X0 = tx * kB_OX, Y0 = ty * kB_OY;
-            std::fill(L.begin(), L.end(), nan);
-            for (int t = 0; t < kB_THREADS; ++t) {
-                fbs[t] = tileB_face_adjoints(a, X0, Y0, t);
-                tileB_states(a, X0, Y0, t, L.data());
-            }
-            for (int t = 0; t < kB_THREADS; ++t) self[t] = tileB_shares(a, X0, Y0, t, L.data(), fbs[t]);
-            for (int t = 0; t < kB_THREADS; ++t) tot[t] = tileB_total(t, self[t], L.data());
-            for (int t = 0; t < kB_THREADS; ++t) tileB_put_total(t, tot[t], L.data());
-            for (int t = 0; t < kB_THREADS; ++t) tileB_gather(a, X0, Y0, t, L.data());
-        }
+    std::vector<double> wide(6 * (size_t)nx * ny, kNan);
+    const int e = host_adjoint_step_blocks(32, nx, ny, bcx, bcy, dx, dy, dt, vc, rc, x0, y0, U, lam1, wide.data()) |
+                  host_adjoint_step_blocks(16, nx, ny, bcx, bcy, dx, dy, dt, vc, rc, x0, y0, U, lam1, lam0);
+    if (e) return e;
+    double most = 0.0;
+    for (size_t k = 0; k < wide.size(); ++k) most = std::max(most, std::fabs(lam0[k]));
+    for (size_t k = 0; k < wide.size(); ++k)
+        if (!(std::fabs(wide[k] - lam0[k]) <= 1e-12 * most)) return 1;
     return 0;
 }
 
-// the forward step with the same face-state, HLL, update and kick arithmetic
-template <bool TWOD>
-static void step_loops(AdjArgs& a, double* Un)
+// the forward step with the same face-state, HLL, update and kick arithmetic, from the
+// face states of the extended cells: [4 faces][6][ex * ey] in both dimensions
+extern "C" int host_step(int nx, int ny, int bcx, int bcy, double dx, double dy, double dt, double vc, double rc,
+                         double x0, double y0, const double* U, double* Un)
 {
-    const int j0 = TWOD ? -1 : 0, j1 = TWOD ? a.ny : 0;
-    for (int j = j0; j <= j1; ++j)
-        for (int i = -1; i <= a.nx; ++i) faces_cell<TWOD>(a, i, j);
-    const size_t ne = (size_t)a.ex * a.ey, plane = (size_t)a.nx * a.ny;
-    const double cx = a.dt / a.dx, cy = a.dt / a.dy;
-    for (int j = 0; j < (TWOD ? a.ny : 1); ++j)
-        for (int i = 0; i < a.nx; ++i) {
-            const size_t e = ext_index(a, i, j);
-            const C Fp = hll_x(make_face_x(load_p(a.FS, ne, XHI, e)), make_face_x(load_p(a.FS, ne, XLO, e + 1)));
-            const C Fm = hll_x(make_face_x(load_p(a.FS, ne, XHI, e - 1)), make_face_x(load_p(a.FS, ne, XLO, e)));
-            C u = update(load_cons<double>(a.U, plane, (size_t)j * a.nx + i), cx, Fp, Fm);
-            if (TWOD) {
-                const C Gp = swap(hll_x(make_face_x(swap(load_p(a.FS, ne, YHI, e))),
-                                        make_face_x(swap(load_p(a.FS, ne, YLO, e + a.ex)))));
-                const C Gm = swap(hll_x(make_face_x(swap(load_p(a.FS, ne, YHI, e - a.ex))),
-                                        make_face_x(swap(load_p(a.FS, ne, YLO, e)))));
-                u = update(u, cy, Gp, Gm);
-            }
+    const bool twod = ny > 1;
+    ref::Args a{};
+    set_args(a, nx, ny, bcx, bcy, dx, dy, dt, vc, rc, x0, y0, U);
+    a.ex = nx + 2;
+    a.ey = twod ? ny + 2 : 1;
+    const size_t ne = (size_t)a.ex * a.ey, plane = (size_t)nx * ny;
+    std::vector<double> fs(24 * ne, 0.0);
+    a.FS = a.AdjArgs::FS = fs.data();
+    if (twod) {
+        for (int j = -1; j <= ny; ++j)
+            for (int i = -1; i <= nx; ++i) ref::faces_cell(a, i, j);
+    } else {
+        for (int i = -1; i <= nx; ++i) faces_cell(a, i);
+    }
+    for (int j = 0; j < ny; ++j)
+        for (int i = 0; i < nx; ++i) {
+            const size_t e = twod ? ref::ext_index(a, i, j) : (size_t)(i + 1);
+            auto face = [&](int hi, int lo, size_t below, size_t above) {
+                return hll_x(make_face_x(hi == ref::XHI ? load_p(a.FS, ne, hi, below) : swap(load_p(a.FS, ne, hi, below))),
+                             make_face_x(lo == ref::XLO ? load_p(a.FS, ne, lo, above) : swap(load_p(a.FS, ne, lo, above))));
+            };
+            C u = update(load_cons<double>(U, plane, (size_t)j * nx + i), a.cx, face(ref::XHI, ref::XLO, e, e + 1),
+                         face(ref::XHI, ref::XLO, e - 1, e));
+            if (twod)
+                u = update(u, a.cy, swap(face(ref::YHI, ref::YLO, e, e + a.ex)),
+                           swap(face(ref::YHI, ref::YLO, e - a.ex, e)));
             if (a.vc2 != 0.0) {
-                const double x = a.x0 + (i + 0.5) * a.dx, y = TWOD ? a.y0 + (j + 0.5) * a.dy : 0.0;
+                const double x = a.x0 + (i + 0.5) * a.dx, y = twod ? a.y0 + (j + 0.5) * a.dy : 0.0;
                 const double f = -a.vc2 / (x * x + y * y + a.rc2), ax = f * x, ay = f * y, h = a.dt;
                 const double mx = u.mx, my = u.my;
                 u.mx = mx + h * u.r * ax;
@@ -167,19 +258,8 @@ static void step_loops(AdjArgs& a, double* Un)
                 u.exy = u.exy + h * (ax * my + mx * ay + h * u.r * ax * ay);
                 u.eyy = u.eyy + h * ay * (2.0 * my + h * u.r * ay);
             }
-            store_cons(Un, plane, (size_t)j * a.nx + i, u);
+            store_cons(Un, plane, (size_t)j * nx + i, u);
         }
-}
-
-extern "C" int host_step(int nx, int ny, int bcx, int bcy, double dx, double dy, double dt, double vc, double rc,
-                         double x0, double y0, const double* U, double* Un)
-{
-    AdjArgs a = make_args(nx, ny, bcx, bcy, dx, dy, dt, vc, rc, x0, y0, U);
-    const size_t ne = (size_t)a.ex * a.ey;
-    std::vector<double> fs(24 * ne, 0.0);
-    a.FS = fs.data();
-    if (ny > 1) step_loops<true>(a, Un);
-    else step_loops<false>(a, Un);
     return 0;
 }
 

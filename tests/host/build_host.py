@@ -1,5 +1,5 @@
 """Build the CPU harnesses of tests/host with hipcc: adjoint_host.hip (the
-adjoint's per-cell bodies in host loops) and device_host.hip (the forward
+adjoint kernels' bodies in host loops) and device_host.hip (the forward
 sweep's per-state arithmetic).  Rebuilt when a source or header is newer."""
 import os
 import subprocess
@@ -39,7 +39,7 @@ def _build(src: str, lib: str, headers) -> str:
 
 
 def build() -> str:
-    return _build(SRC, LIB, ("csh_adjoint.h", "csh_device.h"))
+    return _build(SRC, LIB, ("csh_adjoint.h", "csh_device.h", os.path.join(HERE, "adjoint_reference.h")))
 
 
 def build_device() -> str:
