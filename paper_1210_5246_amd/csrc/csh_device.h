@@ -127,6 +127,12 @@ CSH_HD Prim<T> sub(const Prim<T>& a, const Prim<T>& b)
     return {a.r - b.r, a.u - b.u, a.v - b.v, a.pxx - b.pxx, a.pxy - b.pxy, a.pyy - b.pyy};
 }
 
+template <typename T>
+CSH_HD Prim<T> plus(const Prim<T>& a, const Prim<T>& b)
+{
+    return {a.r + b.r, a.u + b.u, a.v + b.v, a.pxx + b.pxx, a.pxy + b.pxy, a.pyy + b.pyy};
+}
+
 // Sec. 2: E_ij = P_ij + rho u_i u_j
 template <typename T>
 CSH_HD Prim<T> to_prim(const Cons<T>& U, T ir)

@@ -33,12 +33,6 @@ __device__ __forceinline__ double kt_dt(const StepArgs<T>& p, double* t_now)
     return dt;
 }
 
-template <typename T>
-__device__ __forceinline__ Prim<T> plus(const Prim<T>& w, const Prim<T>& d)
-{
-    return {w.r + d.r, w.u + d.u, w.v + d.v, w.pxx + d.pxx, w.pxy + d.pxy, w.pyy + d.pyy};
-}
-
 // 1-D grids: one launch per stage, a wavefront per 60 cells (2 halo lanes per
 // side); the first stage records the step's timestep in its input slot for
 // the second

@@ -19,19 +19,13 @@ namespace {
 
 constexpr int kMaxWaves = 16;
 
-template <typename T>
-__device__ __forceinline__ Prim<T> add(const Prim<T>& w, const Prim<T>& d)
-{
-    return {w.r + d.r, w.u + d.u, w.v + d.v, w.pxx + d.pxx, w.pxy + d.pxy, w.pyy + d.pyy};
-}
-
 // twice the Kurganov-Tadmor flux through the high face of the lane's cell
 template <typename T>
 __device__ __forceinline__ Cons<T> kt_flux2_1d(const Cons<T>& U)
 {
     const Prim<T> W = to_prim(U);
     const Prim<T> s = mc_half_slope(lane_shift<-1>(W), W, lane_shift<+1>(W));
-    return kt_flux2_x(add(W, s), lane_shift<+1>(sub(W, s)));
+    return kt_flux2_x(plus(W, s), lane_shift<+1>(sub(W, s)));
 }
 
 // SCHEME: 0 characteristic with HLL, 1 with HLLC, 2 Kurganov-Tadmor
