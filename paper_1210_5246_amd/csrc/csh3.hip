@@ -514,8 +514,8 @@ extern "C" int csh3_init_state(csh3_grid** out, int nx, int ny, int nz, double d
     if (!out) return fail3(CSH_ERR_ARG, "h is NULL");
     *out = nullptr;
     if (nx < 1 || ny < 1 || nz < 1) return fail3(CSH_ERR_ARG, "nx, ny, nz must be >= 1");
-    // the kernels index with 64 bits; the limit is that of the 2-D path, kept for
-    // symmetry (3-D grids are tested up to 256^3)
+    // the sweep addresses a component with a 32-bit byte offset (load32, store32); 3-D
+    // grids are tested up to 256^3
     if ((long long)nx * ny * nz * 8 >= (1LL << 32))
         return fail3(CSH_ERR_ARG, "one component of the state must be smaller than 4 GiB");
     if (!(dx > 0) || !(dy > 0) || !(dz > 0)) return fail3(CSH_ERR_ARG, "cell sizes must be > 0");

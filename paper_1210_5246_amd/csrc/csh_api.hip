@@ -471,8 +471,9 @@ hipError_t enqueue_run_states(csh_grid* h, int nsteps, double cfl, const void* U
     return e;
 }
 
-// Short 1-D grids take their whole run in one launch, which a recorded graph of
-// a launch per step does not match (256 cells: 1.8 against 3.5 us per step, 960: 3.4 against 3.6).
+// Short 1-D grids take their whole run in one launch, which a recorded graph of a
+// launch per step does not match (us per step: 256 cells 1.7 against 3.3, 960 cells 3.2
+// against 3.4, with the Kurganov-Tadmor step 4.0 against 5.9, with HLLC 3.5 either way).
 bool one_launch(const csh_grid* h)
 {
     return h->ny == 1 && h->nx <= csh::kLineCells;

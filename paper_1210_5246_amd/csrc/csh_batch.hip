@@ -198,7 +198,9 @@ std::vector<int> tube_orders(const std::vector<int>& len, int ncu)
 // at once and has a chunk of 60 cells for each of the eight wavefronts, or a compute
 // unit to itself; else 256 (us per run, 256 / 512: 24 tubes of 128-300 cells 227 /
 // 203, 256 of 128-2000 428 / 347, 512 of 128-4096 3740 / 3170, 500 of 128-300
-// 248 / 278, 512 of 128-700 393 / 398, 700 of 128-1000 600 / 640).
+// 248 / 278, 512 of 128-700 393 / 398, 700 of 128-1000 600 / 640; down to tubes of a
+// single chunk, where all but one wavefront idle, 512 is no slower: 24 of 5-20 cells
+// 243 / 234, 256 of 20-60 243 / 238, 100 of 60-128 259 / 251).
 int default_threads(int ntubes, int64_t cells, int ncu)
 {
     return ntubes <= ncu || (ntubes <= 2 * ncu && cells >= 8LL * csh::kStrip * ntubes) ? 512 : 256;

@@ -103,11 +103,12 @@ __global__ __launch_bounds__(64 * kWaves) void sweep1d_kernel(StepArgs<T> p)
 // wavefront: a small grid leaves a few rows to each wavefront, and with one
 // wavefront per SIMD a row takes ~2900 cycles (2280 of them issue).
 // Else each wavefront has a segment of its own, as many independent wavefronts
-// as fit: for grids with many rows per SIMD, bound by FP64 issue (VALU busy 0.88
-// at 4096^2, 434 us per step).  The stacked workgroups are numbered XCD-aware:
+// as fit: for grids with many rows per SIMD, bound by FP64 issue (VALU busy 0.86
+// at 4096^2, 0.42-0.43 ms per step).  The stacked workgroups are numbered XCD-aware:
 // neighbouring strips share the 128-byte lines at their edges, in reads and in
-// partial writes, and so meet in one L2 (1024^2 37.2 -> 35.1 us, FP32 2048^2
-// 70 -> 67 us against the hardware's order).
+// partial writes, and so meet in one L2 (us per step in the hardware's order / so:
+// FP64 300 x 200 8.6 / 7.7, 512^2 15.0 / 14.0, 700 x 500 16.6 / 16.0; FP32 2048^2
+// 62.7 / 60.4, 4096^2 259 / 237).
 template <typename T, bool FLUXES, int RS, bool STACKED>
 __global__ __launch_bounds__(64 * kWaves) void sweep_kernel(StepArgs<T> p)
 {

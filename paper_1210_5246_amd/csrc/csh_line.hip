@@ -6,10 +6,11 @@
 // wavefronts publish their new cells in LDS, one barrier, every lane reads its
 // cell (the halo lanes their neighbours' or boundary cells), and every thread
 // forms the next timestep from the wavefronts' CFL maxima.  A launch per step
-// is bound by the launch and by the reduction through memory (3.6 us per step
-// at 256 cells); here a step is the serial chain of one cell-update, an LDS
-// exchange and a barrier (1.1 us at 60 cells, 1.8 at 256, 3.4 at 960).  Above kLineCells a workgroup
-// would need more wavefronts than a CU holds.
+// is bound by the launch and by the reduction through memory (256 cells: 3.3 us per
+// step in a replayed graph, 4.5 launched one by one); here a step is the serial chain
+// of one cell-update, an LDS exchange and a barrier (1.0 us at 60 cells, 1.3 at 240,
+// 1.7 at 256, where the fifth wavefront shares a SIMD, 3.2 at 960).  Above kLineCells
+// a workgroup would need more wavefronts than a CU holds.
 #include "csh_device.h"
 #include "csh_internal.h"
 
@@ -94,7 +95,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) void line_run_kernel(LineArgs<T> p)
         const int b = SCHEME == 2 ? 0 : k & 1;
         // rounded as a single step's factors dt / dx and dt / (2 dx) (halving is exact), not as
         // dt * idx: csh_step repeats a run's states bit for bit, as the reverse pass does
-        const double q = dt / p.dx;
+        const double q = div_by(dt, p.dx, idx);
         Cons<T> Un;
         if constexpr (SCHEME == 2) {
             // the midpoint state through buffer 1, then the full step (coefficients: the fluxes are 2H)

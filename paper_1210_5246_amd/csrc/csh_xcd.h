@@ -10,7 +10,7 @@ namespace csh {
 // each XCD with its own L2; renumbered this way each XCD takes one contiguous
 // range of logical workgroups, so tiles that share stencil rows run on the
 // same L2 at the same time.  A bijection of [0, nb) for any nb.  The stacked
-// 2-D sweep runs 4-6% faster with it (1024^2 37.2 -> 35.1 us), the adjoint's
+// 2-D sweep runs 4-11% faster with it (FP64 512^2 15.0 -> 14.0 us), the adjoint's
 // one-thread-per-cell kernels 10%, and the 3-D sweep reads 2.6x fewer bytes past
 // L2 (3% slower); the sweep and Kurganov-Tadmor kernels of a wavefront per
 // segment measured 4-8% slower and keep the hardware order.
