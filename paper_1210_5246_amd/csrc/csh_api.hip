@@ -2,9 +2,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <algorithm>
-#include <mutex>
 #include <string>
-#include <vector>
 
 #include "cshydro.h"
 #include "csh_api_util.h"
@@ -16,52 +14,6 @@ using csh::Slot;
 thread_local std::string csh_err_msg;
 
 extern "C" const char* csh_last_error(void) { return csh_err_msg.c_str(); }
-
-namespace csh {
-
-namespace {
-
-struct CellPage {
-    HostCell* cells;
-    uint64_t used;  // bit k: cell k is handed out
-};
-std::mutex cell_mutex;
-std::vector<CellPage>& cell_pages = *new std::vector<CellPage>;  // outlives every handle, also at process exit
-
-}  // namespace
-
-HostCell* acquire_cell()
-{
-    std::lock_guard<std::mutex> lock(cell_mutex);
-    auto page = std::find_if(cell_pages.begin(), cell_pages.end(), [](const CellPage& p) { return ~p.used != 0; });
-    if (page == cell_pages.end()) {
-        void* cells = nullptr;  // portable: a page serves the handles of every device
-        if (hipHostMalloc(&cells, 64 * sizeof(HostCell), hipHostMallocPortable) != hipSuccess) return nullptr;
-        cell_pages.push_back({static_cast<HostCell*>(cells), 0});
-        page = cell_pages.end() - 1;
-    }
-    const int k = __builtin_ctzll(~page->used);
-    page->used |= 1ull << k;
-    page->cells[k] = HostCell{0.0, 0};
-    return page->cells + k;
-}
-
-void release_cell(HostCell* cell)
-{
-    if (!cell) return;
-    std::lock_guard<std::mutex> lock(cell_mutex);
-    for (auto page = cell_pages.begin(); page != cell_pages.end(); ++page) {
-        if (cell < page->cells || cell >= page->cells + 64) continue;
-        page->used &= ~(1ull << (cell - page->cells));
-        if (page->used == 0 && cell_pages.size() > 1) {
-            (void)hipHostFree(page->cells);
-            cell_pages.erase(page);
-        }
-        return;
-    }
-}
-
-}  // namespace csh
 
 struct csh_grid {
     int nx = 0, ny = 0, bcx = 0, bcy = 0, dtype = CSH_F64;
