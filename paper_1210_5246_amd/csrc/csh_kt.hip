@@ -10,6 +10,7 @@
 // in registers (large grids) or in LDS; a 1-D grid takes one launch per stage.
 // The kernels carry half slopes (face states w -+ h) and twice the flux (the
 // update coefficients take the 1/2).
+#include <algorithm>
 #include <cstdlib>
 
 #include "csh_device.h"
@@ -392,7 +393,8 @@ __global__ __launch_bounds__(64 * kBlockWaves, 2) void kt_block_kernel(StepArgs<
     if (__any(bad) && lane == 0) raise_flag(p.flag);
 }
 
-// Which kernel, and how many rows per segment: the least of the times (ns) below.
+// Which kernel, and how many rows per segment (at most the grid's): the least of the
+// times (ns) below.
 //
 // March: the critical-path rule of the sweep, with its halo (stage 1 forms six rows
 // more than the segment's, stage 2 two, an average of four per row) and rounds of
@@ -402,9 +404,11 @@ __global__ __launch_bounds__(64 * kBlockWaves, 2) void kt_block_kernel(StepArgs<
 // wavefronts on the SIMD (FP32 1.17, with four 1.5), the launch, the barrier and the
 // faces of a share 6.5 (5, 8).
 // Measured, march / block, us: FP64 100^2 15.5 / 9.4, 512^2 24.5 / 18.9, 700^2
-// 26.5 / 24.6, 1000 x 700 33.0 / 30.8; two rounds 1024^2 44 / 51.5, four 1500^2
-// 80 / 111.  FP32 1400^2 (two rounds) 53 / 46, 2048^2 (three) 104 / 87, 3000^2 (seven)
-// 171 / 195: past three rounds the march, whose wavefronts then overlap, is taken.
+// 26.5 / 24.6, 1000 x 700 33.0 / 30.8; in more than one round, whose workgroups follow
+// one another on a CU, barrier and launch each time, 1024^2 44 / 51.5, 1500^2 80 / 111,
+// 100000 x 2 27 / 57, 30000 x 8 24 / 31, 60000 x 20 59 / 74: the march.  FP32 1400^2
+// (two rounds) 53 / 46, 2048^2 (three) 104 / 87, 3000^2 (seven) 171 / 195: past three
+// rounds the march, whose wavefronts then overlap, is taken.
 KtPlan kt_plan(int nx, int ny, bool f64)
 {
     const long strips = (nx + kFusedStrip - 1) / kFusedStrip;
@@ -417,16 +421,15 @@ KtPlan kt_plan(int nx, int ny, bool f64)
             best = {block, t};
         }
     };
-    for (int t = segs(8) >= 256 ? 8 : 4; t <= 96; ++t) {
+    for (int t = std::min(segs(8) >= 256 ? 8 : 4, ny); t <= std::min(96, ny); ++t) {
         const long rows = ((segs(t) + 1023) / 1024) * (t + 4);
         offer(false, t, f64 ? 3000 + 1740 * rows : 4000 + 1300 * rows);
     }
     auto share = [](int n) { return (n + kBlockWaves - 1) / kBlockWaves; };
-    for (int t = kBlockRows - 4; t >= 1; --t) {
+    for (int t = std::min(kBlockRows - 4, ny); t >= 1; --t) {
         const long n = segs(t), rows = share(t + 4) + share(t);
-        if (f64) offer(true, t, 6500 + 1750 * rows * ((n + 255) / 256));
-        else if (n <= 256) offer(true, t, 5000 + 1170 * rows);
-        else if (n <= 3 * 512) offer(true, t, (8000 + 1500 * rows) * ((n + 511) / 512));
+        if (n <= 256) offer(true, t, f64 ? 6500 + 1750 * rows : 5000 + 1170 * rows);
+        else if (!f64 && n <= 3 * 512) offer(true, t, (8000 + 1500 * rows) * ((n + 511) / 512));
     }
     return best;
 }
