@@ -213,7 +213,8 @@ int csh_fluxes(csh_grid *h, double dt, const void *U, void *Fx, void *Fy);
  * same size).  dt_log: device array of nsteps doubles receiving each step's
  * timestep, or NULL.  No host synchronisation between steps; on small grids the
  * sequence is captured once as a HIP graph per (nsteps, state buffers, cfl,
- * t_end) and replayed, on larger ones the steps are launched one by one.
+ * t_end) and replayed, on larger ones and in runs of up to four steps the steps
+ * are launched one by one.
  * A 1-D grid of at most 960 cells takes the whole run in one launch instead, on
  * the handle's stream (U_work is then not written).
  */

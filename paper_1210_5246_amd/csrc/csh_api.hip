@@ -474,9 +474,14 @@ int line_run(csh_grid* h, int nsteps, double cfl, double t_end, const void* U0, 
 // 4 strip rows per SIMD (a step of 13 us, 512^2) the plain launches are as fast
 // (100 steps of 512^2: 1389 against 1396 us, 64^2: 549 against 509 us) and the
 // first run is spared the recording (1480 against 1750 us).
-bool worth_recording(const csh_grid* h)
+// Nor is a run of up to four launches worth it: a graph's launch takes as long as those
+// of about six kernels, and its log is copied by one more (us per run, recorded / launched
+// one by one, alone: one step of 64^2 45 / 25, of a 1-D grid of 961 cells 45 / 25, four
+// steps 47 / 40 and 44 / 33, eight 64 / 71 and 52 / 65).
+bool worth_recording(const csh_grid* h, int nsteps)
 {
-    return (long)((h->nx + csh::kStrip - 1) / csh::kStrip) * h->ny <= 4L * 1024;
+    const int launches = h->scheme == CSH_SCHEME_KT && h->ny == 1 ? 2 : 1;  // of a step
+    return nsteps > 4 / launches && (long)((h->nx + csh::kStrip - 1) / csh::kStrip) * h->ny <= 4L * 1024;
 }
 
 // All steps of csh_run_cfl (mode 0, lg: the log or null) or csh_run_dts (mode 1,
@@ -489,7 +494,7 @@ int run_steps(csh_grid* h, int mode, int nsteps, double cfl, double t_end, void*
         return mode == 0 ? enqueue_run(h, nsteps, cfl, t_end, U, U_work, (double*)l, nullptr, s)
                          : enqueue_run(h, nsteps, 1.0, 0.0, U, U_work, nullptr, (const double*)l, s);
     };
-    if (!worth_recording(h)) {
+    if (!worth_recording(h, nsteps)) {
         const hipError_t e = enqueue(lg, h->stream);
         if (e != hipSuccess) return csh_fail(CSH_ERR_HIP, std::string("run: ") + hipGetErrorString(e));
         return CSH_OK;
