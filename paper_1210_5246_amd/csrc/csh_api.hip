@@ -53,12 +53,16 @@ namespace {
 // (us per step, stacked / a wavefront per segment: 64^2 5.5 / 10.3, 131 x 93
 // 6.1 / 10.5, 300 x 200 8.3 / 12.0, 512^2 13.9 / 17.0, 700 x 500 16.1 / 17.6,
 // 800^2 23.4 / 23.0, 1024^2 35.7 / 35.0): the line lies at 8 strip rows per
-// SIMD.  In FP32, whose rows are too short for the latency of one or two
+// SIMD.  Not on wide grids of few rows, whose strips alone are more than the two
+// workgroups a CU holds: there most of a workgroup's rows are halo (60000 x 2 13.6 /
+// 9.6, 120000 x 3 28.6 / 16.6, 54000 x 8 21.5 / 18.2, their fluxes 10.1 / 8.4, 22.2 /
+// 15.8, 19.5 / 17.0; 30000 x 2 8.1 / 8.2, 36000 x 10 17.9 / 19.5).  In FP32, whose rows are too short for the latency of one or two
 // wavefronts per SIMD, always (2048^2 66 / 86, 4096^2 240 / 242).
 void split_rows(csh_grid* h)
 {
     const long strips = (h->nx + csh::kStrip - 1) / csh::kStrip, ny = h->ny;
-    const bool stacked = h->dtype == CSH_F32 || strips * ny <= 8L * 1024;
+    const bool thin = strips > 2 * 256 && ny <= 8;
+    const bool stacked = h->dtype == CSH_F32 || (strips * ny <= 8L * 1024 && !thin);
     int rows = 0;
     if (const char* e = std::getenv("CSH_ROWS")) rows = std::max(0, std::atoi(e));
     long best_cost = -1;
